@@ -28,12 +28,27 @@
 //   cover dx >= 0 only (dx < 0 follows from hermiticity,
 //   Lc[dR][(ab,cd)] = conj(Lc[-dR][(cd,ab)])).  At the end of a kx chunk the
 //   lanes' values are transposed through LDS and contracted with e^{-i ky dy}.
-// Partial sums per (ky block, kx chunk) go to HBM in FP64; a finalising kernel
-// adds them in a fixed order (deterministic, no atomics).
+// Partial sums per (ky block, kx chunk) go to HBM; a finalising kernel adds
+// them in a fixed order (deterministic, no atomics).
+//
+// Half of the sum follows from the other (every model; all loop kernels, see
+// loop_sym.h):
+// * pp: k and q - k carry the same two points with the orbital pairs
+//   exchanged, Lc(q)[dR][abcd] = H[abcd] + e^{-iq.dR} conj(H[dcba]) with H
+//   the sum over the kx rows of one of each pair (kx, qx - kx): rows from qx/2
+//   to qx/2 + Lf/2, a row that is its own partner with weight 1/2;
+// * ph: Lc(-q)[dR][abcd] = e^{iq.dR} Lc(q)[dR][dcba]: one of q, -q is summed.
+// With time reversal, Pi(-k) = T Pi(k)^* T^t and e(-k) = e(k) (checked on the
+// hopping table at creation; T real, one entry +-1 per row), both hold in both
+// channels: Lc(-q)[abcd] = tttt conj(Lc(q)[a'b'c'd']) (a' the partner of a),
+// and the ph rows (kx, qx - kx) pair up with d'c'b'a' in place of dcba.  The
+// loop kernels are bound by vector issue, so the time follows the points:
+// half of them for every model, a quarter with time reversal.
 #include <vector>
 
 #include "common.h"
 #include "kernels.h"
+#include "loop_sym.h"
 
 namespace tufrg {
 
@@ -94,12 +109,13 @@ __device__ inline V4<double> ld4d_buf(i32x4 r, unsigned voff, unsigned soff) {
 // Loop body of one channel (CH = 0: pp, k' = q - k; CH = 1: ph, k' = k - q).
 // ekv[k] = (e_0, e_1, K(e_0), K(e_1)), pi4[k] = (Pi_0[00], Pi_0[11], Re Pi_0[01], Im Pi_0[01]);
 // shell scheme: K is the fixed-temperature J and cv[k] = (a_0, a_1, b_0, b_1)
-// the shell factors; twk: exp(-2 pi i j / Lf) in the arithmetic type.
+// the shell factors; twk: exp(-2 pi i j / Lf) in the arithmetic type.  nx kx rows
+// from x0 (mod Lf); the rows hx0, hx1 (-1: none) count half.
 template <typename T, int NDX, int SCHEME, int CH>
 __device__ inline void loop_no2_body(const T *__restrict__ ekv, const T *__restrict__ pi4,
                                      const T *__restrict__ cvp,
                                      const T *__restrict__ twk, int Lf, int qfx, int qfy, int ky, int x0,
-                                     int x1, T lam, int deriv, T (&Sr)[NREAL], T (&Sc)[NCPLX][2],
+                                     int nx, int hx0, int hx1, T lam, int deriv, T (&Sr)[NREAL], T (&Sc)[NCPLX][2],
                                      T (&Ar)[NDX - 1][NREAL], T (&Br)[NDX - 1][NREAL],
                                      T (&Ac)[NDX - 1][NCPLX][2], T (&Bc)[NDX - 1][NCPLX][2]) {
   constexpr T sg = (CH == 0) ? T(1) : T(-1);
@@ -140,7 +156,7 @@ __device__ inline void loop_no2_body(const T *__restrict__ ekv, const T *__restr
     kpx = kpx < 0 ? kpx + Lf : (kpx >= Lf ? kpx - Lf : kpx);
   };
   // arithmetic of one k-point (k data ck, k' data cp), in kx order
-  auto point = [&](const Pt &ck, const Pt &cp) {
+  auto point = [&](const Pt &ck, const Pt &cp, int kx) {
       const T ekm[2] = {ck.ek.x, ck.ek.y}, Kkm[2] = {ck.ek.z, ck.ek.w};
       const T P0 = ck.pk.x, P1 = ck.pk.y, Pr = ck.pk.z, Pi = ck.pk.w;
       const T epn[2] = {cp.ek.x, cp.ek.y}, Kpn[2] = {cp.ek.z, cp.ek.w};
@@ -173,6 +189,12 @@ __device__ inline void loop_no2_body(const T *__restrict__ ekv, const T *__restr
         for (int m = 0; m < 2; ++m)
 #pragma unroll
           for (int n = 0; n < 2; ++n) L[m][n] *= fma(ak[m], bp[n], bk[m] * ap[n]);
+      }
+      if (kx == hx0 || kx == hx1) {  // wave-uniform, at most two rows of a q
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+          for (int n = 0; n < 2; ++n) L[m][n] *= T(0.5);
       }
       // W_1 = alpha_1 X_0 + L_11 1, D = W_0 - W_1 = (alpha_0 - alpha_1) X_0 + (L_01 - L_11) 1
       const T al0 = L[0][0] - L[0][1], al1 = L[1][0] - L[1][1];
@@ -233,39 +255,44 @@ __device__ inline void loop_no2_body(const T *__restrict__ ekv, const T *__restr
     Pt ak, ap, bk, bp;
     load(x0, uky, ak);
     load(kpx, ukpy, ap);
-    int kx = x0;
-    for (; kx + 1 < x1; kx += 2) {
+    int kx = x0, i = 0;
+    for (; i + 1 < nx; i += 2) {
+      const int kb = kx + 1 == Lf ? 0 : kx + 1;
       next_kpx();
-      load(kx + 1, uky, bk);
+      load(kb, uky, bk);
       load(kpx, ukpy, bp);
-      point(ak, ap);
-      const bool more = kx + 2 < x1;
+      point(ak, ap, kx);
+      const bool more = i + 2 < nx;
       if (more) next_kpx();
-      load(more ? kx + 2 : kx + 1, uky, ak);
+      kx = kb + 1 == Lf ? 0 : kb + 1;
+      load(more ? kx : kb, uky, ak);
       load(kpx, ukpy, ap);
-      point(bk, bp);
+      point(bk, bp, kb);
     }
-    if (kx < x1) point(ak, ap);
+    if (i < nx) point(ak, ap, kx);
   } else {
     // plain order, one register set: FP32 with dx < 3 then fits four waves per
     // SIMD, which hide the load latency better than the second set did at three
     // (rashba_s9_L24: 2.26 -> 2.18 ms); FP64 is at one or two waves per SIMD anyway
-    for (int kx = x0; kx < x1; ++kx) {
+    int kx = x0;
+    for (int i = 0; i < nx; ++i) {
       Pt ck, cp;
       load(kx, uky, ck);
       load(kpx, ukpy, cp);
-      point(ck, cp);
+      point(ck, cp, kx);
       next_kpx();
+      kx = kx + 1 == Lf ? 0 : kx + 1;
     }
   }
 }
 
-// A workgroup holds QW waves that share the ky block, q_x, kx chunk and
-// channel and take QW consecutive q_y: they read the same k addresses and
-// overlapping k -/+ q rows at the same time.  Workgroups are handed to the 8
-// XCDs round-robin by linear id; each XCD is given a contiguous slice of the
-// work items, ordered (ky block, q_y group, q_x, kx chunk, channel) from
-// fastest to slowest, so that co-resident workgroups share rows in its L2.
+// A workgroup holds QW waves that share the ky block and kx chunk and take QW
+// consecutive items (channel and coarse q) of the item list: they read nearly
+// the same k addresses and overlapping k -/+ q rows at the same time.
+// Workgroups are handed to the 8 XCDs round-robin by linear id; each XCD is
+// given a contiguous slice of the work, ordered (ky block, item group, kx
+// chunk, channel) from fastest to slowest, so that co-resident workgroups
+// share rows in its L2.
 constexpr int N_XCD = 8;
 
 template <typename T>
@@ -273,42 +300,41 @@ struct loop_waves {
   static constexpr int v = (sizeof(T) == 4) ? 4 : 2;
 };
 
-// One work item (ky block, q_y group, q_x, kx chunk, channel) of QW waves,
-// w its index among the n_items of one instance; bufs and phy are the
-// workgroup's LDS.
+// One work item (ky block, item group, kx chunk, channel) of QW waves, w its
+// index; bufs and phy are the workgroup's LDS.
 template <typename T, int NDX, int NDY, int SCHEME, int QW>
 __device__ __forceinline__ void loop_no2_item(const T *__restrict__ ekv, const T *__restrict__ pi4,
                                               const T *__restrict__ cvp, const double *__restrict__ tw,
                                               const T *__restrict__ twk, int Lq, int n_ref, int Lf, int nkyb,
-                                              int nkxc, int kxper, int q_first, int n_q,
-                                              const int *__restrict__ rows, int ch_first, int w, T lam, int deriv,
+                                              int kxper, int nparts, int half, const int *__restrict__ items, int n_pp,
+                                              int n_ph, int w, T lam, int deriv,
                                               T *__restrict__ partial, T (&bufs)[QW][32][65],
                                               T (&phy)[2 * NDY + 1][2][64]) {
   constexpr int NDY2 = 2 * NDY + 1;
   const int tid = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int kyb = w % nkyb;
   w /= nkyb;
-  const int nqyg = (Lq + QW - 1) / QW;
-  const int qyg = w % nqyg;
-  w /= nqyg;
-  const bool qvalid = qyg * QW + wv < Lq;
-  const int qy = qvalid ? qyg * QW + wv : Lq - 1;
-  const int nqx = n_q / Lq;
-  const int qx = w % nqx;
-  w /= nqx;
-  const int kxc = w % nkxc;
-  const int chrel = w / nkxc, ch = ch_first + chrel;
-  // coarse q: consecutive from q_first, or whole q_x rows from a list
-  const int qrel = qx * Lq + qy, qi = rows ? rows[qx] * Lq + qy : q_first + qrel;
-  const int nparts = nkyb * nkxc;
+  // the pp items' chunks come first, then the ph items'
+  const int g_pp = (n_pp + QW - 1) / QW, g_ph = (n_ph + QW - 1) / QW;
+  const int c_pp = (loop_rows_max(Lf, half & 1) + kxper - 1) / kxper;
+  const int w_pp = g_pp * c_pp, ch = w >= w_pp ? 1 : 0;
+  w -= ch ? w_pp : 0;
+  const int ng = ch ? g_ph : g_pp, kxc = w / ng;
+  const int idx = (w % ng) * QW + wv, n_it = ch ? n_ph : n_pp;
+  const bool qvalid = idx < n_it;
+  const int it = (ch ? n_pp : 0) + (qvalid ? idx : n_it - 1);
   // one coarse q per wave: keep its fine coordinates in scalar registers
-  const int qfx = __builtin_amdgcn_readfirstlane((qi / Lq) * n_ref);
-  const int qfy = __builtin_amdgcn_readfirstlane((qi % Lq) * n_ref);
+  const int qi = __builtin_amdgcn_readfirstlane(items[it] & LOOP_ITEM_Q);
+  const int qfx = (qi / Lq) * n_ref, qfy = (qi % Lq) * n_ref;
   const int ky_raw = kyb * 64 + tid;
   const bool active = ky_raw < Lf;
   const int ky = active ? ky_raw : Lf - 1;
-  const int x0 = kxc * kxper;
-  const int x1 = min(Lf, x0 + kxper);
+  // kx rows of this item and chunk
+  int r0, nr, hx0, hx1;
+  loop_rows(Lf, qfx, (half >> ch) & 1, r0, nr, hx0, hx1);
+  int x0 = r0 + kxc * kxper;
+  const int nx = min(kxper, nr - kxc * kxper);
+  x0 = x0 >= Lf ? x0 - Lf : x0;
 
   // S: dx = 0 sums; A/B: sum of cos/sin parts for dx >= 1
   T Sr[NREAL], Sc[NCPLX][2], Ar[NDX - 1][NREAL], Br[NDX - 1][NREAL];
@@ -325,10 +351,12 @@ __device__ __forceinline__ void loop_no2_item(const T *__restrict__ ekv, const T
     for (int t = 0; t < NCPLX; ++t) Ac[d][t][0] = Ac[d][t][1] = Bc[d][t][0] = Bc[d][t][1] = T(0);
   }
   if (ch == 0)
-    loop_no2_body<T, NDX, SCHEME, 0>(ekv, pi4, cvp, twk, Lf, qfx, qfy, ky, x0, x1, lam, deriv, Sr, Sc, Ar, Br, Ac,
+    loop_no2_body<T, NDX, SCHEME, 0>(ekv, pi4, cvp, twk, Lf, qfx, qfy, ky, x0, nx, hx0, hx1, lam, deriv, Sr,
+                                     Sc, Ar, Br, Ac,
                                      Bc);
   else
-    loop_no2_body<T, NDX, SCHEME, 1>(ekv, pi4, cvp, twk, Lf, qfx, qfy, ky, x0, x1, lam, deriv, Sr, Sc, Ar, Br, Ac,
+    loop_no2_body<T, NDX, SCHEME, 1>(ekv, pi4, cvp, twk, Lf, qfx, qfy, ky, x0, nx, hx0, hx1, lam, deriv, Sr,
+                                     Sc, Ar, Br, Ac,
                                      Bc);
 
   // rebuild all 16 entries per dx, transpose through LDS, contract with e^{-i 2 pi ky dy / Lf}
@@ -344,7 +372,7 @@ __device__ __forceinline__ void loop_no2_item(const T *__restrict__ ekv, const T
     }
   }
   const T on = active ? T(1) : T(0);
-  const size_t pbase = (((size_t)chrel * n_q + qrel) * nparts + (kyb + nkyb * kxc)) * (size_t)(NDX * NDY2 * 16);
+  const size_t pbase = ((size_t)it * nparts + (kyb + nkyb * kxc)) * (size_t)(NDX * NDY2 * 16);
 #pragma unroll
   for (int dx = 0; dx < NDX; ++dx) {
     __syncthreads();
@@ -401,63 +429,70 @@ __device__ __forceinline__ void loop_no2_item(const T *__restrict__ ekv, const T
 }
 
 
-// QW waves per work item (ky block, q_y group, q_x, kx chunk, channel).
 template <typename T, int NDX, int NDY, int SCHEME, int QW>
 __global__ __launch_bounds__(64 * QW, (NDX > 3 ? (sizeof(T) == 8 ? 1 : 2) : (sizeof(T) == 8 ? 2 : 4))) void loop_no2_kernel(const T *__restrict__ ekv, const T *__restrict__ pi4, const T *__restrict__ cvp,
                                                            const double *__restrict__ tw, const T *__restrict__ twk,
-                                                           int Lq, int n_ref, int Lf,
-                                                           int nkyb, int nkxc, int kxper, int q_first, int n_q,
-                                                           const int *__restrict__ rows,
-                                                           int ch_first, int n_items, T lam, int deriv,
+                                                           int Lq, int n_ref, int Lf, int nkyb, int kxper, int nparts,
+                                                           int half, const int *__restrict__ items, int n_pp,
+                                                           int n_ph, int n_work, T lam, int deriv,
                                                            T *__restrict__ partial) {
   __shared__ T bufs[QW][32][65];
   __shared__ T phy[2 * NDY + 1][2][64];
   const int xcd = blockIdx.x % N_XCD, slot = blockIdx.x / N_XCD;
-  const int base = n_items / N_XCD, rem = n_items % N_XCD;
+  const int base = n_work / N_XCD, rem = n_work % N_XCD;
   if (slot >= base + (xcd < rem ? 1 : 0)) return;  // padding workgroup, no work
   const int w = xcd * base + min(xcd, rem) + slot;
-  loop_no2_item<T, NDX, NDY, SCHEME, QW>(ekv, pi4, cvp, tw, twk, Lq, n_ref, Lf, nkyb, nkxc, kxper, q_first, n_q, rows,
-                                         ch_first, w, lam, deriv, partial, bufs, phy);
+  loop_no2_item<T, NDX, NDY, SCHEME, QW>(ekv, pi4, cvp, tw, twk, Lq, n_ref, Lf, nkyb, kxper, nparts, half, items, n_pp,
+                                         n_ph, w, lam, deriv, partial, bufs, phy);
 }
 
-// Several instances in one launch: the items of instance i are
-// [inst[i].item0, inst[i].item0 + its count), every instance summing both
-// channels over all its coarse q; the same work items and partial sums as its
+// Several instances in one launch: the work of instance i is
+// [inst[i].work0, inst[i].work0 + its count), every instance summing both
+// channels over all its items; the same work items and partial sums as its
 // own launch.
 template <typename T, int NDX, int NDY, int SCHEME, int QW>
-__global__ __launch_bounds__(64 * QW, (NDX > 3 ? (sizeof(T) == 8 ? 1 : 2) : (sizeof(T) == 8 ? 2 : 4))) void loop_no2_batch_kernel(const No2Inst *__restrict__ inst, int n_inst, int n_items) {
+__global__ __launch_bounds__(64 * QW, (NDX > 3 ? (sizeof(T) == 8 ? 1 : 2) : (sizeof(T) == 8 ? 2 : 4))) void loop_no2_batch_kernel(const No2Inst *__restrict__ inst, int n_inst, int n_work) {
   __shared__ T bufs[QW][32][65];
   __shared__ T phy[2 * NDY + 1][2][64];
   const int xcd = blockIdx.x % N_XCD, slot = blockIdx.x / N_XCD;
-  const int base = n_items / N_XCD, rem = n_items % N_XCD;
+  const int base = n_work / N_XCD, rem = n_work % N_XCD;
   if (slot >= base + (xcd < rem ? 1 : 0)) return;  // padding workgroup, no work
   const int w = xcd * base + min(xcd, rem) + slot;
   int i = 0;
-  while (i + 1 < n_inst && inst[i + 1].item0 <= w) ++i;
+  while (i + 1 < n_inst && inst[i + 1].work0 <= w) ++i;
   const No2Inst &d = inst[i];
   loop_no2_item<T, NDX, NDY, SCHEME, QW>((const T *)d.ekv, (const T *)d.pi4, (const T *)d.cvp, d.tw,
-                                         (const T *)d.twk, d.Lq, d.n_ref, d.Lf, d.nkyb, d.nkxc, d.kxper, 0, d.n_q,
-                                         nullptr, 0, w - d.item0, (T)d.lam, d.deriv, (T *)d.partial, bufs, phy);
+                                         (const T *)d.twk, d.Lq, d.n_ref, d.Lf, d.nkyb, d.kxper, d.nparts, d.half,
+                                         d.items, d.n_pp, d.n_ph, w - d.work0, (T)d.lam, d.deriv, (T *)d.partial,
+                                         bufs, phy);
+}
+
+// workgroups of one two-orbital evaluation: per channel (ky blocks) x (kx
+// chunks of the rows it sums) x (groups of QW items)
+static long long no2_work(const LoopArgs &a, int QW) {
+  auto part = [&](int n, int h) {
+    return (long long)((n + QW - 1) / QW) * ((loop_rows_max(a.Lf, h) + a.kxper - 1) / a.kxper);
+  };
+  return a.nkyb * (part(a.n_pp, a.half & 1) + part(a.n_ph, (a.half >> 1) & 1));
 }
 
 template <typename T, int NDX, int NDY>
 static hipError_t launch_no2(const LoopArgs &a, hipStream_t st) {
-  if (a.q_first % a.Lq != 0 || a.n_q % a.Lq != 0) return hipErrorInvalidValue;  // whole q_x rows
   constexpr int QW = loop_waves<T>::v;
-  const int kxper = (a.Lf + a.nkxc - 1) / a.nkxc;
-  const int nqyg = (a.Lq + QW - 1) / QW;
-  const int n_items = a.nkyb * a.nkxc * nqyg * (a.n_q / a.Lq) * a.n_ch;
-  const int n_wg = ((n_items + N_XCD - 1) / N_XCD) * N_XCD;
+  const long long work = no2_work(a, QW);
+  if (work < 1 || work > 0x7ffffff0LL) return hipErrorInvalidValue;
+  const int n_work = (int)work;
+  const int n_wg = ((n_work + N_XCD - 1) / N_XCD) * N_XCD;
   dim3 grid(n_wg), block(64 * QW);
   const T *ekv = (const T *)a.ekv;
   const T *pi4 = (const T *)a.pi4;
   const T *twk = (const T *)(sizeof(T) == 8 ? (const void *)a.tw : a.tw32);
   const T *cvp = (const T *)a.cv;
-  if (!ekv || !pi4 || !twk) return hipErrorInvalidValue;
+  if (!ekv || !pi4 || !twk || !a.items) return hipErrorInvalidValue;
   if (a.scheme == CUT_SHELL && !cvp) return hipErrorInvalidValue;
 #define TUFRG_NO2_LAUNCH(S)                                                                                         \
   hipLaunchKernelGGL((loop_no2_kernel<T, NDX, NDY, S, QW>), grid, block, 0, st, ekv, pi4, cvp, a.tw, twk, a.Lq,    \
-                     a.n_ref, a.Lf, a.nkyb, a.nkxc, kxper, a.q_first, a.n_q, a.rows, a.ch_first, n_items, (T)a.lam, \
+                     a.n_ref, a.Lf, a.nkyb, a.kxper, a.nparts, a.half, a.items, a.n_pp, a.n_ph, n_work, (T)a.lam,  \
                      a.deriv, (T *)a.partial)
   if (a.scheme == CUT_TEMPERATURE)
     TUFRG_NO2_LAUNCH(CUT_TEMPERATURE);
@@ -475,12 +510,11 @@ template <typename T, int NDX, int NDY>
 static hipError_t launch_no2_batch(const LoopArgs *a, const int *idx, int m, No2Inst *desc_h, No2Inst *desc_d,
                                    hipStream_t st) {
   constexpr int QW = loop_waves<T>::v;
-  long long items = 0;
+  long long work = 0;
   for (int j = 0; j < m; ++j) {
     const LoopArgs &x = a[idx[j]];
     const T *twk = (const T *)(sizeof(T) == 8 ? (const void *)x.tw : x.tw32);
-    if (!x.ekv || !x.pi4 || !twk || x.q_first != 0 || x.n_q != x.Nq || x.rows || x.ch_first != 0 || x.n_ch != 2)
-      return hipErrorInvalidValue;
+    if (!x.ekv || !x.pi4 || !twk || !x.items || x.n_pp < 1 || x.n_ph < 1) return hipErrorInvalidValue;
     if (x.scheme == CUT_SHELL && !x.cv) return hipErrorInvalidValue;
     No2Inst &d = desc_h[j];
     d.ekv = x.ekv;
@@ -488,33 +522,35 @@ static hipError_t launch_no2_batch(const LoopArgs *a, const int *idx, int m, No2
     d.cvp = x.cv;
     d.twk = twk;
     d.tw = x.tw;
+    d.items = x.items;
     d.partial = x.partial;
     d.lam = x.lam;
     d.Lq = x.Lq;
     d.n_ref = x.n_ref;
     d.Lf = x.Lf;
     d.nkyb = x.nkyb;
-    d.nkxc = x.nkxc;
-    d.kxper = (x.Lf + x.nkxc - 1) / x.nkxc;
-    d.n_q = x.n_q;
+    d.kxper = x.kxper;
+    d.nparts = x.nparts;
+    d.half = x.half;
+    d.n_pp = x.n_pp;
+    d.n_ph = x.n_ph;
     d.deriv = x.deriv;
-    d.item0 = (int)items;
-    d.pad = 0;
-    items += (long long)x.nkyb * x.nkxc * ((x.Lq + QW - 1) / QW) * (x.n_q / x.Lq) * 2;
+    d.work0 = (int)work;
+    work += no2_work(x, QW);
+    if (work > 0x7ffffff0LL) return hipErrorInvalidValue;
   }
-  if (items > 0x7fffffffLL) return hipErrorInvalidValue;
   hipError_t e = hipMemcpyAsync(desc_d, desc_h, m * sizeof(No2Inst), hipMemcpyHostToDevice, st);
   if (e != hipSuccess) return e;
-  const int n_items = (int)items;
-  const dim3 grid(((n_items + N_XCD - 1) / N_XCD) * N_XCD), block(64 * QW);
+  const int n_work = (int)work;
+  const dim3 grid(((n_work + N_XCD - 1) / N_XCD) * N_XCD), block(64 * QW);
   const int scheme = a[idx[0]].scheme;
   if (scheme == CUT_TEMPERATURE)
     hipLaunchKernelGGL((loop_no2_batch_kernel<T, NDX, NDY, CUT_TEMPERATURE, QW>), grid, block, 0, st, desc_d, m,
-                       n_items);
+                       n_work);
   else if (scheme == CUT_OMEGA)
-    hipLaunchKernelGGL((loop_no2_batch_kernel<T, NDX, NDY, CUT_OMEGA, QW>), grid, block, 0, st, desc_d, m, n_items);
+    hipLaunchKernelGGL((loop_no2_batch_kernel<T, NDX, NDY, CUT_OMEGA, QW>), grid, block, 0, st, desc_d, m, n_work);
   else if (scheme == CUT_SHELL)
-    hipLaunchKernelGGL((loop_no2_batch_kernel<T, NDX, NDY, CUT_SHELL, QW>), grid, block, 0, st, desc_d, m, n_items);
+    hipLaunchKernelGGL((loop_no2_batch_kernel<T, NDX, NDY, CUT_SHELL, QW>), grid, block, 0, st, desc_d, m, n_work);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
@@ -565,50 +601,65 @@ hipError_t launch_loop(const LoopArgs &a, hipStream_t st) {
 
 // ---------------------------------------------------------------------------
 
+// Compact loops from the partial sums: H[dR][tau] of an item is the
+// fixed-order FP64 sum of its parts (dx < 0 by hermiticity); a halved sum is
+// completed from the reversed entry; the value goes to the item's own slot of
+// the output and, transformed, to that of -q.
 template <typename PT>
-__global__ void loop_finalize_kernel(int n_o, int n_ch, int n_q, int nparts, int ndx, int ndy, int nD,
-                                     const int *__restrict__ dlist, double inv_nf, const PT *__restrict__ partial,
-                                     double *__restrict__ compact) {
+__global__ void loop_finalize_kernel(LoopSym sy, int n_o, int n_items, int nparts, int valid_pp, int valid_ph, int ndx,
+                                     int ndy, int nD, int ch_first, int n_q_out, const int *__restrict__ items,
+                                     const int2 *__restrict__ dst, const int *__restrict__ dlist, double inv_nf,
+                                     const PT *__restrict__ partial, double *__restrict__ compact) {
   const int no2 = n_o * n_o, no4 = no2 * no2;
-  const long long total = (long long)n_ch * n_q * nD * no4;
+  const long long total = (long long)n_items * nD * no4;
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= total) return;
   const int tau = (int)(i % no4);
   const int iD = (int)((i / no4) % nD);
-  const long long cq = i / ((long long)no4 * nD);  // chrel * n_q + qrel
-  int dx = dlist[2 * iD], dy = dlist[2 * iD + 1];
-  int t = tau;
-  bool cj = false;
-  if (dx < 0) {
-    dx = -dx;
-    dy = -dy;
-    t = (tau % no2) * no2 + tau / no2;
-    cj = true;
-  }
-  const int ndy2 = 2 * ndy + 1;
+  const int it = (int)(i / ((long long)no4 * nD));
+  const int q = items[it] & LOOP_ITEM_Q, ch = items[it] >> LOOP_ITEM_CH;
+  const int dx = dlist[2 * iD], dy = dlist[2 * iD + 1];
+  const int ndy2 = 2 * ndy + 1, valid = ch ? valid_ph : valid_pp;
   const size_t per = (size_t)ndx * ndy2 * no4;
-  const PT *p = partial + (size_t)cq * nparts * per * 2 + ((size_t)(dx * ndy2 + dy + ndy) * no4 + t) * 2;
-  double sr = 0.0, si = 0.0;
-  for (int k = 0; k < nparts; ++k) {
-    sr += (double)p[(size_t)k * per * 2];
-    si += (double)p[(size_t)k * per * 2 + 1];
+  const PT *pi = partial + (size_t)it * nparts * per * 2;
+  auto H = [&](int t) {
+    const bool cj = dx < 0;
+    if (cj) t = (t % no2) * no2 + t / no2;
+    const PT *p = pi + ((size_t)((cj ? -dx : dx) * ndy2 + (cj ? -dy : dy) + ndy) * no4 + t) * 2;
+    double sr = 0.0, si = 0.0;
+#pragma unroll 4
+    for (int k = 0; k < valid; ++k) {
+      sr += (double)p[(size_t)k * per * 2];
+      si += (double)p[(size_t)k * per * 2 + 1];
+    }
+    return make_double2(sr, cj ? -si : si);
+  };
+  double2 v = H(tau);
+  if ((sy.half >> ch) & 1) {
+    double sgn;
+    const double2 h = H(loop_partner_tau(sy, n_o, ch, tau, sgn));
+    loop_add_partner(sy, q, dx, dy, sgn, h, v);
   }
-  compact[2 * i] = sr * inv_nf;
-  compact[2 * i + 1] = (cj ? -si : si) * inv_nf;
+  loop_store(sy, n_o, ch, q, dx, dy, tau, make_double2(v.x * inv_nf, v.y * inv_nf), dst[it], ch - ch_first, n_q_out,
+             (size_t)nD * no4, (size_t)iD * no4, (double2 *)compact);
 }
 
 hipError_t launch_loop_finalize(const LoopArgs &a, int nD, const int *dlist, double *compact, hipStream_t st) {
-  const int no4 = a.n_o * a.n_o * a.n_o * a.n_o;
-  const long long total = (long long)a.n_ch * a.n_q * nD * no4;
-  const int nparts = a.nkyb * a.nkxc;
+  const int no4 = a.n_o * a.n_o * a.n_o * a.n_o, n_items = a.n_pp + a.n_ph;
+  const long long total = (long long)n_items * nD * no4;
+  if (total < 1 || !a.items || !a.dst) return hipErrorInvalidValue;
+  const int ch_first = a.n_pp ? 0 : 1;
+  auto valid = [&](int h) { return a.nkyb * ((loop_rows_max(a.Lf, h) + a.kxper - 1) / a.kxper); };
+  const int vpp = valid(a.half & 1), vph = valid((a.half >> 1) & 1);
   const double inv = 1.0 / ((double)a.Lf * a.Lf);
+  const LoopSym sy{a.trs, a.half, a.Lq, (const double2 *)a.twq};
   const dim3 grid((unsigned)((total + 255) / 256)), block(256);
   if (a.prec == 0)
-    hipLaunchKernelGGL(loop_finalize_kernel<double>, grid, block, 0, st, a.n_o, a.n_ch, a.n_q, nparts, a.ndx, a.ndy,
-                       nD, dlist, inv, (const double *)a.partial, compact);
+    hipLaunchKernelGGL(loop_finalize_kernel<double>, grid, block, 0, st, sy, a.n_o, n_items, a.nparts, vpp, vph, a.ndx,
+                       a.ndy, nD, ch_first, a.n_q_out, a.items, a.dst, dlist, inv, (const double *)a.partial, compact);
   else
-    hipLaunchKernelGGL(loop_finalize_kernel<float>, grid, block, 0, st, a.n_o, a.n_ch, a.n_q, nparts, a.ndx, a.ndy,
-                       nD, dlist, inv, (const float *)a.partial, compact);
+    hipLaunchKernelGGL(loop_finalize_kernel<float>, grid, block, 0, st, sy, a.n_o, n_items, a.nparts, vpp, vph, a.ndx,
+                       a.ndy, nD, ch_first, a.n_q_out, a.items, a.dst, dlist, inv, (const float *)a.partial, compact);
   return hipGetLastError();
 }
 

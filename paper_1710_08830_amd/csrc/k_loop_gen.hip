@@ -29,6 +29,7 @@
 // of the first band of each pair).
 #include "common.h"
 #include "kernels.h"
+#include "loop_sym.h"
 
 namespace tufrg {
 
@@ -102,15 +103,16 @@ __device__ inline void unpack_store(c2<T> *dst, int pl, T x) {
 
 }  // namespace
 
-// One workgroup per (part, channel, q); part selects NTHR of the entry pairs.
+// One workgroup per (part, item, kx chunk): part selects NTHR of the entry pairs,
+// the item a channel and a coarse q; the kx rows of a halved sum as in loop_sym.h.
 template <typename T, int NO, int NDY, int SCHEME, int NTHR, int KT, bool PAIR>
 __global__ __launch_bounds__(NTHR) void loop_gen_kernel(const T *__restrict__ band, const T *__restrict__ pir,
                                                         const T *__restrict__ kv, const T *__restrict__ cvp,
                                                         const double *__restrict__ tw, const T *__restrict__ phy,
                                                         const int *__restrict__ pairs,
-                                                        int n_pairs, int Lq, int n_ref, int Lf, int nparts,
-                                                        int q_first, int n_q, const int *__restrict__ rows,
-                                                        int ch_first, int n_ch, int ndx_out,
+                                                        int n_pairs, int Lq, int n_ref, int Lf, int nparts, int kxper,
+                                                        int nkxc, int half, const int *__restrict__ items, int n_pp,
+                                                        int n_ph, int ndx_out,
                                                         T lam, int deriv, T *__restrict__ partial) {
   using SH = Shape<NDY>;
   constexpr int NPT = SH::N;
@@ -128,9 +130,11 @@ __global__ __launch_bounds__(NTHR) void loop_gen_kernel(const T *__restrict__ ba
   int w = blockIdx.x;
   const int part = w % nparts;
   w /= nparts;
-  const int chrel = w % n_ch, qrel = w / n_ch;
-  // coarse q: consecutive from q_first, or whole q_x rows from a list
-  const int qi = rows ? rows[qrel / Lq] * Lq + qrel % Lq : q_first + qrel, ch = ch_first + chrel;
+  // kx chunk: the pp items' chunks come first, then the ph items'
+  const int w_pp = n_pp * ((loop_rows_max(Lf, half & 1) + kxper - 1) / kxper), ch = w >= w_pp ? 1 : 0;
+  w -= ch ? w_pp : 0;
+  const int n_it = ch ? n_ph : n_pp, kxc = w / n_it, it = (ch ? n_pp : 0) + w % n_it;
+  const int qi = items[it] & LOOP_ITEM_Q;
   const int qfx = (qi / Lq) * n_ref, qfy = (qi % Lq) * n_ref;
   const int pidx = part * NTHR + tid;
   const bool active = pidx < n_pairs;
@@ -151,7 +155,12 @@ __global__ __launch_bounds__(NTHR) void loop_gen_kernel(const T *__restrict__ ba
 #pragma unroll
   for (int i = 0; i < NPT; ++i) Z[i] = cmake(T(0), T(0));
 
-  for (int kx = 0; kx < Lf; ++kx) {
+  int r0, nr, hx0, hx1;
+  loop_rows(Lf, qfx, (half >> ch) & 1, r0, nr, hx0, hx1);
+  nr = min(nr, (kxc + 1) * kxper);
+  for (int r = kxc * kxper; r < nr; ++r) {
+    const int kx = r0 + r >= Lf ? r0 + r - Lf : r0 + r;
+    const T wgt = (kx == hx0 || kx == hx1) ? T(0.5) : T(1);
     int kpx = (ch == 0) ? (qfx - kx) : (kx - qfx);
     kpx += kpx < 0 ? Lf : 0;
     cx<T> S = cmake(T(0), T(0)), A[NDY], B[NDY];
@@ -194,7 +203,7 @@ __global__ __launch_bounds__(NTHR) void loop_gen_kernel(const T *__restrict__ ba
         T l = sg * divided_difference(x, y, sK[j][0][m], -sg * sK[j][1][n], lam, dd_scheme(SCHEME), deriv);
         // shell scheme: times a_m(k) b_n(k') + b_m(k) a_n(k')
         if constexpr (SHELL) l *= fma(sC[j][0][2 * m], sC[j][1][2 * n + 1], sC[j][0][2 * m + 1] * sC[j][1][2 * n]);
-        sL[j][m][n] = l;
+        sL[j][m][n] = wgt * l;
       }
       __syncthreads();
       // W_m = sum_n L_mn X_n, packed sums written as full complex matrices
@@ -251,10 +260,10 @@ __global__ __launch_bounds__(NTHR) void loop_gen_kernel(const T *__restrict__ ba
     }
   }
   if (!active) return;
-  // partial[ch][q][dx][dy + NDY][tau] for dx >= 0; the partner entry from
+  // partial[item][kx chunk][dx][dy + NDY][tau] for dx >= 0; the partner entry from
   // Lc[dR][partner] = conj Lc[-dR][tau]
   const int ndy2 = 2 * NDY + 1;
-  const size_t pbase = ((size_t)chrel * n_q + qrel) * (size_t)(ndx_out * ndy2 * NO4);
+  const size_t pbase = ((size_t)it * nkxc + kxc) * (size_t)(ndx_out * ndy2 * NO4);
 #pragma unroll
   for (int i = 0; i < NPT; ++i) {
     const int dx = SH::dx(i), dy = SH::dy(i);
@@ -279,15 +288,19 @@ static hipError_t launch_gen(const LoopArgs &a, hipStream_t st) {
   constexpr int NTHR = f64 ? 384 : 704, KT = f64 ? 8 : 16;
   if (a.ndx != NDY + 1) return hipErrorInvalidValue;
   const int NP = (a.n_pairs + NTHR - 1) / NTHR;
-  dim3 grid(a.n_q * a.n_ch * NP), block(NTHR);
+  if (!a.items || a.n_pp + a.n_ph < 1 || a.nkyb != 1) return hipErrorInvalidValue;
+  auto work = [&](int n, int h) { return (long long)n * ((loop_rows_max(a.Lf, h) + a.kxper - 1) / a.kxper); };
+  const long long nw = NP * (work(a.n_pp, a.half & 1) + work(a.n_ph, (a.half >> 1) & 1));
+  if (nw > 0x7fffffffLL) return hipErrorInvalidValue;
+  dim3 grid((unsigned)nw), block(NTHR);
   const T *band = (const T *)a.band, *kv = (const T *)a.kv, *phy = (const T *)a.phy, *cvp = (const T *)a.cv;
   const T *pir = f64 ? (const T *)a.pir64 : (const T *)a.pir;
   if (a.scheme == CUT_SHELL && !cvp) return hipErrorInvalidValue;
   if (a.pair && !pir) return hipErrorInvalidValue;
 #define TUFRG_GEN_LAUNCH(S, P)                                                                                   \
   hipLaunchKernelGGL((loop_gen_kernel<T, 6, NDY, S, NTHR, KT, P>), grid, block, 0, st, band, pir, kv, cvp, a.tw, \
-                     phy, a.pairs, a.n_pairs, a.Lq, a.n_ref, a.Lf, NP, a.q_first, a.n_q, a.rows, a.ch_first,     \
-                     a.n_ch, a.ndx, (T)a.lam, a.deriv, (T *)a.partial)
+                     phy, a.pairs, a.n_pairs, a.Lq, a.n_ref, a.Lf, NP, a.kxper, a.nparts, a.half, a.items, a.n_pp, \
+                     a.n_ph, a.ndx, (T)a.lam, a.deriv, (T *)a.partial)
 #define TUFRG_GEN_SCHEMES(P)               \
   if (a.scheme == CUT_TEMPERATURE)         \
     TUFRG_GEN_LAUNCH(CUT_TEMPERATURE, P);  \

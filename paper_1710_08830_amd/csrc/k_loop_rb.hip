@@ -43,6 +43,7 @@
 //   the other half plane by conjugation, times 1/Nf: the compact loops.
 #include "common.h"
 #include "kernels.h"
+#include "loop_sym.h"
 
 namespace tufrg {
 
@@ -159,8 +160,8 @@ __global__ __launch_bounds__(256) void loop_rb_apre_kernel(const float *__restri
 template <int NDY, int SCHEME, bool PAIR>
 __global__ __launch_bounds__(NTHR, 1) void loop_rb_kernel(
     const float *__restrict__ band, const float *__restrict__ pir, const float *__restrict__ kv,
-    const float *__restrict__ cvp, const bf16x8 *__restrict__ apre, int Lq, int n_ref, int Lf, int q_first,
-    int n_q, const int *__restrict__ rows, int ch, float lam, int deriv, int n_groups, int n_kxb, int kxr,
+    const float *__restrict__ cvp, const bf16x8 *__restrict__ apre, int Lq, int n_ref, int Lf,
+    const int *__restrict__ items, int n_q, int half, int ch, float lam, int deriv, int n_groups, int n_kxb, int kxr,
     float *__restrict__ Y) {
   using S = RB<NDY>;
   constexpr int MT = S::MT, MTW = S::MTW, ROWS = S::ROWS;
@@ -198,7 +199,7 @@ __global__ __launch_bounds__(NTHR, 1) void loop_rb_kernel(
     if (tid > 0) {
       const int qidx = NQG * g + tid - 1;
       const int qc = qidx < n_q ? qidx : n_q - 1;  // past the list: any valid q (zero column)
-      const int q = rows ? rows[qc / Lq] * Lq + qc % Lq : q_first + qc;
+      const int q = items[qc] & LOOP_ITEM_Q;
       qfx = (q / Lq) * n_ref;
       qfy = (q % Lq) * n_ref;
     }
@@ -206,6 +207,13 @@ __global__ __launch_bounds__(NTHR, 1) void loop_rb_kernel(
     sQf[tid][1] = qfy;
   }
   __syncthreads();
+  if (half) {
+    // no q of the group sums a row of this block: nothing to do (uniform)
+    int any = 0;
+    for (int r = 0; r < nrow; ++r)
+      for (int q = 1; q <= NQG; ++q) any |= loop_row_weight2(Lf, sQf[q][0], kx0 + r);
+    if (!any) return;
+  }
   // k' of slot s (1..4) at (kx, ky); slot 0: k itself
   auto kpt = [&](int qfx, int qfy, bool self, int kx, int ky) __attribute__((always_inline)) {
     if (self) return kx * Lf + ky;
@@ -282,8 +290,10 @@ __global__ __launch_bounds__(NTHR, 1) void loop_rb_kernel(
   // loop kernels L_mn of this thread's (q, ky): (m, n) = divmod(dsub + 8 i, 6).
   // The eight threads of one (q, ky) are lanes of one wave, and so are those
   // that read these L_mn for the B operand: no barrier between the two.
-  auto loop_kernels = [&](int eb) __attribute__((always_inline)) {
+  auto loop_kernels = [&](int eb, int t) __attribute__((always_inline)) {
     const float *e0 = sE[eb][dky][0], *e1 = sE[eb][dky][1 + dq];
+    // weight of the kx row in the sum of this q (halved sums: 1, 1/2 or 0)
+    const float sw = half ? sg * 0.5f * (float)loop_row_weight2(Lf, bqfx, kx0 + t / ntk) : sg;
     // paired: only the two diagonal 3 x 3 blocks (bands of the same ky)
     constexpr int NMN = PAIR ? 18 : NO * NO;
 #pragma unroll
@@ -293,7 +303,7 @@ __global__ __launch_bounds__(NTHR, 1) void loop_rb_kernel(
         const int m = PAIR ? 3 * (j / 9) + (j % 9) / 3 : j / NO;
         const int n = PAIR ? 3 * (j / 9) + j % 3 : j - NO * (j / NO);
         const int mn = NO * m + n;
-        float l = sg * divided_difference(e0[m], -sg * e1[n], e0[NO + m], -sg * e1[NO + n], lam, dd_scheme(SCHEME),
+        float l = sw * divided_difference(e0[m], -sg * e1[n], e0[NO + m], -sg * e1[NO + n], lam, dd_scheme(SCHEME),
                                           deriv);
         if constexpr (SHELL) l *= fmaf(e0[2 * NO + 2 * m], e1[2 * NO + 2 * n + 1], e0[2 * NO + 2 * m + 1] * e1[2 * NO + 2 * n]);
         sL[dq][dky][mn] = l;
@@ -462,7 +472,7 @@ __global__ __launch_bounds__(NTHR, 1) void loop_rb_kernel(
     stage(pr, 1);
   }
   __syncthreads();
-  loop_kernels(0);
+  loop_kernels(0, 0);
   build_b(0, 0);
   if (2 < ntile) fetch(2, pr);
   __syncthreads();
@@ -480,7 +490,7 @@ __global__ __launch_bounds__(NTHR, 1) void loop_rb_kernel(
       const int bb = t & 1;
       auto vector_work = [&]() __attribute__((always_inline)) {
         if (t + 1 < ntile) {
-          loop_kernels(bb ^ 1);
+          loop_kernels(bb ^ 1, t + 1);
           build_b(bb ^ 1, t + 1);
         }
         if (t + 2 < ntile) stage(pr, bb);
@@ -523,8 +533,9 @@ struct Half<2> {
 
 template <int NDY>
 __global__ __launch_bounds__(256) void loop_rb_rowsum_kernel(const float *__restrict__ Y,
-                                                             const double *__restrict__ tw, int Lf, int n_q,
-                                                             int ch, double *__restrict__ lam_out) {
+                                                             const double *__restrict__ tw, int Lq, int n_ref, int Lf,
+                                                             const int *__restrict__ items, int n_q, int half, int ch,
+                                                             double *__restrict__ lam_out) {
   using S = RB<NDY>;
   using H = Half<NDY>;
   constexpr int ROWS = S::ROWS;
@@ -544,7 +555,11 @@ __global__ __launch_bounds__(256) void loop_rb_rowsum_kernel(const float *__rest
 #pragma unroll
   for (int h = 0; h < H::N; ++h) zr[h] = zi[h] = 0.0;
   const float *Yg = Y + (size_t)g * Lf * ROWS * NCOL + (size_t)alpha * NCOL + col;
-  for (int kx = 0; kx < Lf; ++kx) {
+  // the rows that this q sums, in an order that depends on the q alone
+  int r0, nr, h0, h1;
+  loop_rows(Lf, ((items[q] & LOOP_ITEM_Q) / Lq) * n_ref, half, r0, nr, h0, h1);
+  for (int r = 0; r < nr; ++r) {
+    const int kx = r0 + r >= Lf ? r0 + r - Lf : r0 + r;
     const float *Yr = Yg + (size_t)kx * ROWS * NCOL;
     double v[2 * NDY + 1];
 #pragma unroll
@@ -602,10 +617,16 @@ __device__ inline int rb_coords(int a, int c, int *alpha, double *ci) {
   return 2;
 }
 
-// compact[q][iD][(a b c d)] = 1/Nf sum E^alpha_ac E^beta_bd lambda^{alpha beta}(q, +-dR)
+// compact loops from lambda: H[dR][(a b c d)] = sum E^alpha_ac E^beta_bd
+// lambda^{alpha beta}(item, +-dR), a halved sum completed from its partner
+// entry, to the slots of q and -q
 template <int NDY>
-__global__ __launch_bounds__(256) void loop_rb_finalize_kernel(int n_q, int nD, const int *__restrict__ hmap,
-                                                               double inv_nf, const double *__restrict__ lam,
+__global__ __launch_bounds__(256) void loop_rb_finalize_kernel(LoopSym sy, int ch, int n_q, int nD, int n_q_out,
+                                                               const int *__restrict__ items,
+                                                               const int2 *__restrict__ dst,
+                                                               const int *__restrict__ hmap,
+                                                               const int *__restrict__ dlist, double inv_nf,
+                                                               const double *__restrict__ lam,
                                                                double *__restrict__ compact) {
   using H = Half<NDY>;
   constexpr int NO2 = NO * NO, NO3 = NO2 * NO, NO4 = NO2 * NO2;
@@ -613,34 +634,44 @@ __global__ __launch_bounds__(256) void loop_rb_finalize_kernel(int n_q, int nD, 
   if (i >= (long long)n_q * nD * NO4) return;
   const int tau = (int)(i % NO4);
   const int iD = (int)((i / NO4) % nD);
-  const int q = (int)(i / ((long long)NO4 * nD));
+  const int it = (int)(i / ((long long)NO4 * nD));
   const int hm = hmap[iD], h = hm & 0xffff;
   const bool cj = (hm >> 16) != 0;  // the other half plane: lambda(-dR) = conj lambda(dR)
-  const int a = tau / NO3, b = (tau / NO2) % NO, c = (tau / NO) % NO, d = tau % NO;
-  int al[2], be[2];
-  double ca[2], cb[2];
-  const int na = rb_coords(a, c, al, ca), nb = rb_coords(b, d, be, cb);
-  double sr = 0.0, si = 0.0;
-  for (int x = 0; x < na; ++x)
-    for (int y = 0; y < nb; ++y) {
-      const size_t o = (((size_t)q * H::N + h) * NA + al[x]) * NA + be[y];
-      const double lr = lam[2 * o], li = cj ? -lam[2 * o + 1] : lam[2 * o + 1];
-      // coefficient (x ? i ca : 1) (y ? i cb : 1)
-      if (x == 0 && y == 0) {
-        sr += lr;
-        si += li;
-      } else if (x == 1 && y == 1) {
-        const double f = -ca[1] * cb[1];
-        sr += f * lr;
-        si += f * li;
-      } else {
-        const double f = x == 1 ? ca[1] : cb[1];  // times i
-        sr -= f * li;
-        si += f * lr;
+  auto entry = [&](int t) {
+    const int a = t / NO3, b = (t / NO2) % NO, c = (t / NO) % NO, d = t % NO;
+    int al[2], be[2];
+    double ca[2], cb[2];
+    const int na = rb_coords(a, c, al, ca), nb = rb_coords(b, d, be, cb);
+    double sr = 0.0, si = 0.0;
+    for (int x = 0; x < na; ++x)
+      for (int y = 0; y < nb; ++y) {
+        const size_t o = (((size_t)it * H::N + h) * NA + al[x]) * NA + be[y];
+        const double lr = lam[2 * o], li = cj ? -lam[2 * o + 1] : lam[2 * o + 1];
+        // coefficient (x ? i ca : 1) (y ? i cb : 1)
+        if (x == 0 && y == 0) {
+          sr += lr;
+          si += li;
+        } else if (x == 1 && y == 1) {
+          const double f = -ca[1] * cb[1];
+          sr += f * lr;
+          si += f * li;
+        } else {
+          const double f = x == 1 ? ca[1] : cb[1];  // times i
+          sr -= f * li;
+          si += f * lr;
+        }
       }
-    }
-  compact[2 * i] = sr * inv_nf;
-  compact[2 * i + 1] = si * inv_nf;
+    return make_double2(sr, si);
+  };
+  const int q = items[it] & LOOP_ITEM_Q, dx = dlist[2 * iD], dy = dlist[2 * iD + 1];
+  double2 v = entry(tau);
+  if ((sy.half >> ch) & 1) {
+    double sgn;
+    const double2 p = entry(loop_partner_tau(sy, NO, ch, tau, sgn));
+    loop_add_partner(sy, q, dx, dy, sgn, p, v);
+  }
+  loop_store(sy, NO, ch, q, dx, dy, tau, make_double2(v.x * inv_nf, v.y * inv_nf), dst[it], 0, n_q_out,
+             (size_t)nD * NO4, (size_t)iD * NO4, (double2 *)compact);
 }
 
 size_t loop_rb_rowbuf_floats(int ndy, int Lf) {
@@ -712,17 +743,19 @@ hipError_t launch_pair_pi(int Nf, const double *band, float *pir, double *pir64,
   return hipGetLastError();
 }
 
-// one channel, coarse q [q_first, q_first + n_q) (or the q_x rows of a.rows):
-// the row buffers Y (ceil(n_q / 4) groups of loop_rb_rowbuf_floats), with the
-// A operand apre of launch_loop_rb_apre (of the same pairing)
-hipError_t launch_loop_rb(const LoopArgs &a, int ch, const void *apre, float *Y, hipStream_t st) {
+// the items of one channel: the row buffers Y (ceil(n / 4) groups of
+// loop_rb_rowbuf_floats), with the A operand apre of launch_loop_rb_apre (of
+// the same pairing)
+hipError_t launch_loop_rb(const LoopArgs &a, const void *apre, float *Y, hipStream_t st) {
   if (a.n_o != NO || !Y || !apre) return hipErrorInvalidValue;
   const float *band = (const float *)a.band, *kv = (const float *)a.kv;
   const float *cvp = (const float *)a.cv, *pir = a.pir;
   if (a.scheme == CUT_SHELL && !cvp) return hipErrorInvalidValue;
   if (a.pair && (!pir || a.Lf % 2)) return hipErrorInvalidValue;
   if (!(a.ndy == 4 && a.ndx == 5) && !(a.ndy == 2 && a.ndx == 3)) return hipErrorInvalidValue;
-  const int n_groups = (a.n_q + NQG - 1) / NQG;
+  const int n_q = a.n_pp + a.n_ph, ch = a.n_pp ? 0 : 1;
+  if (!a.items || n_q < 1 || (a.n_pp && a.n_ph)) return hipErrorInvalidValue;
+  const int n_groups = (n_q + NQG - 1) / NQG;
   const int kxr = a.kxr;  // kx rows per work item
   if (kxr < 1 || kxr > 8) return hipErrorInvalidValue;
   const int n_kxb = (a.Lf + kxr - 1) / kxr;
@@ -732,7 +765,7 @@ hipError_t launch_loop_rb(const LoopArgs &a, int ch, const void *apre, float *Y,
   const bf16x8 *ap = (const bf16x8 *)apre;
 #define TUFRG_RB_LAUNCH(D, S, P)                                                                                   \
   hipLaunchKernelGGL((loop_rb_kernel<D, S, P>), dim3((unsigned)nblk), dim3(NTHR), 0, st, band, pir, kv, cvp, ap, \
-                     a.Lq, a.n_ref, a.Lf, a.q_first, a.n_q, a.rows, ch, lam, a.deriv, n_groups, n_kxb, kxr, Y)
+                     a.Lq, a.n_ref, a.Lf, a.items, n_q, (a.half >> ch) & 1, ch, lam, a.deriv, n_groups, n_kxb, kxr, Y)
 #define TUFRG_RB_SCHEMES(D, P)              \
   if (a.scheme == CUT_TEMPERATURE)          \
     TUFRG_RB_LAUNCH(D, CUT_TEMPERATURE, P); \
@@ -756,26 +789,32 @@ hipError_t launch_loop_rb(const LoopArgs &a, int ch, const void *apre, float *Y,
   return hipGetLastError();
 }
 
-// then the real-basis sums lamb ([n_q][half points][36][36] complex) and the
-// compact loops at dst ([n_q][nD][n_o^4] complex); hmap[iD] = half-plane point
-// of dlist[iD] (low 16 bits) and 1 << 16 where it is the reflected one
-hipError_t launch_loop_rb_sums(const LoopArgs &a, const float *Y, double *lamb, const int *hmap, int nD,
-                               double *dst, hipStream_t st) {
-  if (!Y || !lamb || !hmap || !dst || a.n_ch != 1) return hipErrorInvalidValue;
-  const int n_groups = (a.n_q + NQG - 1) / NQG;
+// then the real-basis sums lamb ([n][half points][36][36] complex) and the
+// compact loops of the items' slots at out ([n_q_out][nD][n_o^4] complex);
+// hmap[iD] = half-plane point of dlist[iD] (low 16 bits) and 1 << 16 where it
+// is the reflected one
+hipError_t launch_loop_rb_sums(const LoopArgs &a, const float *Y, double *lamb, const int *hmap, const int *dlist,
+                               int nD, double *out, hipStream_t st) {
+  const int n_q = a.n_pp + a.n_ph, ch = a.n_pp ? 0 : 1;
+  if (!Y || !lamb || !hmap || !dlist || !out || !a.items || !a.dst || n_q < 1 || (a.n_pp && a.n_ph))
+    return hipErrorInvalidValue;
+  const int n_groups = (n_q + NQG - 1) / NQG;
   const long long nt = (long long)n_groups * NQG * NA * NA;
-  const long long nf = (long long)a.n_q * nD * NO * NO * NO * NO;
+  const long long nf = (long long)n_q * nD * NO * NO * NO * NO;
   const double inv = 1.0 / ((double)a.Lf * a.Lf);
+  const LoopSym sy{a.trs, a.half, a.Lq, (const double2 *)a.twq};
+  const int half = (a.half >> ch) & 1;
+  const dim3 gs((unsigned)((nt + 255) / 256)), gf((unsigned)((nf + 255) / 256)), block(256);
   if (a.ndy == 4) {
-    hipLaunchKernelGGL(loop_rb_rowsum_kernel<4>, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, st, Y, a.tw, a.Lf,
-                       a.n_q, a.ch_first, lamb);
-    hipLaunchKernelGGL(loop_rb_finalize_kernel<4>, dim3((unsigned)((nf + 255) / 256)), dim3(256), 0, st, a.n_q, nD,
-                       hmap, inv, lamb, dst);
+    hipLaunchKernelGGL(loop_rb_rowsum_kernel<4>, gs, block, 0, st, Y, a.tw, a.Lq, a.n_ref, a.Lf, a.items, n_q, half, ch,
+                       lamb);
+    hipLaunchKernelGGL(loop_rb_finalize_kernel<4>, gf, block, 0, st, sy, ch, n_q, nD, a.n_q_out, a.items, a.dst, hmap,
+                       dlist, inv, lamb, out);
   } else if (a.ndy == 2) {
-    hipLaunchKernelGGL(loop_rb_rowsum_kernel<2>, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, st, Y, a.tw, a.Lf,
-                       a.n_q, a.ch_first, lamb);
-    hipLaunchKernelGGL(loop_rb_finalize_kernel<2>, dim3((unsigned)((nf + 255) / 256)), dim3(256), 0, st, a.n_q, nD,
-                       hmap, inv, lamb, dst);
+    hipLaunchKernelGGL(loop_rb_rowsum_kernel<2>, gs, block, 0, st, Y, a.tw, a.Lq, a.n_ref, a.Lf, a.items, n_q, half, ch,
+                       lamb);
+    hipLaunchKernelGGL(loop_rb_finalize_kernel<2>, gf, block, 0, st, sy, ch, n_q, nD, a.n_q_out, a.items, a.dst, hmap,
+                       dlist, inv, lamb, out);
   } else {
     return hipErrorInvalidValue;
   }

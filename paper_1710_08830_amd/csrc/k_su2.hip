@@ -11,7 +11,7 @@
 // with a~ = p + v + PC(c) + PD(d), c~ = c + v + CP(p) + CD(d),
 // d~ = d + v + CP(p^x) + CD(c) from the scalar cross projections of Sec. 3.3
 // (v the onsite coefficient of d13 d24 - d14 d23).
-//   loop1_kernel       the one-band loops Lc[ch][q][dR], FP64
+//   loop1_kernel       partial sums of the one-band loops, FP64
 //   su2_exch_kernel    X -> X^x
 //   su2_gather_kernel  the rho-space gathers of a~, c~, d~
 //   su2_bundle_kernel  dp (pp channel) or dc, dd (ph channel) per q
@@ -19,137 +19,130 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "loop_sym.h"
 
 namespace tufrg {
 
-namespace {
-
-__device__ inline double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-}  // namespace
-
-// part[ch - ch_first][q - q_first][kx chunk][iD] = sum over the kx rows of the
-// chunk of e^{-ik.dR_iD} L(e(k), e(k')) (k' = q - k for pp, k - q for ph): per
-// kx row the ky sums with the phases of |dy| <= 4 (cos and sin parts), then
-// the kx phases per dR; one workgroup per (q, channel, kx chunk), its threads
-// over ky (one wave per 64 ky, at most four)
-template <int NDP>
-__global__ __launch_bounds__(256) void loop1_kernel(int Lq, int n_ref, int Lf, int nD, const int *__restrict__ dlist,
-                                                    const double *__restrict__ e, const double *__restrict__ kv,
-                                                    const double *__restrict__ tw, double lam, int scheme, int deriv,
-                                                    int ch_first, int q_first, int n_q, int nkxc, int kxper,
-                                                    double *__restrict__ part) {
-  __shared__ double red[4][NDP][2];
-  const int qrel = blockIdx.x, chrel = blockIdx.y, kxc = blockIdx.z, ch = ch_first + chrel;
-  const int q = q_first + qrel;
+// One-band loops, FP64: the sum over k of e^{-ik.dR} L(e(k), e(k')) (k' = q - k
+// for pp, k - q for ph) of one item (channel, coarse q), ky block of 64 and
+// chunk of kx rows per wave.  Like the two-orbital kernel: a lane owns one ky
+// and walks kx with wave-uniform kx phases (1 + 2 (NDX - 1) real sums), the ky
+// phases are contracted through LDS at the end of the chunk, and the kx rows
+// and coarse q that follow by symmetry are left out (loop_sym.h).  Bound by
+// FP64 vector issue (the divided difference, about 20 operations per point).
+template <int NDX, int NDY, int QW>
+__global__ __launch_bounds__(64 * QW) void loop1_kernel(int Lq, int n_ref, int Lf, int nkyb, int kxper, int nparts,
+                                                        int half, const int *__restrict__ items, int n_pp, int n_ph,
+                                                        const double *__restrict__ e, const double *__restrict__ kv,
+                                                        const double *__restrict__ tw, double lam, int scheme,
+                                                        int deriv, double *__restrict__ part) {
+  constexpr int NDY2 = 2 * NDY + 1, NV = 2 * NDX - 1;
+  __shared__ double buf[QW][NV][65];
+  __shared__ double phy[NDY2][2][64];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  int w = blockIdx.x;
+  const int kyb = w % nkyb;
+  w /= nkyb;
+  const int g_pp = (n_pp + QW - 1) / QW, g_ph = (n_ph + QW - 1) / QW;
+  const int c_pp = (loop_rows_max(Lf, half & 1) + kxper - 1) / kxper;
+  const int w_pp = g_pp * c_pp, ch = w >= w_pp ? 1 : 0;
+  w -= ch ? w_pp : 0;
+  const int ng = ch ? g_ph : g_pp, kxc = w / ng;
+  const int idx = (w % ng) * QW + wv, n_it = ch ? n_ph : n_pp;
+  const bool qvalid = idx < n_it;
+  const int it = (ch ? n_pp : 0) + (qvalid ? idx : n_it - 1);
+  const int q = __builtin_amdgcn_readfirstlane(items[it] & LOOP_ITEM_Q);
   const int qfx = (q / Lq) * n_ref, qfy = (q % Lq) * n_ref;
   const double sg = ch == 0 ? 1.0 : -1.0;
-  const int tid = threadIdx.x, nthr = blockDim.x;
-  double zr[NDP], zi[NDP];
+  const int ky_raw = kyb * 64 + lane, ky = min(ky_raw, Lf - 1);
+  int kpy = ch == 0 ? qfy - ky : ky - qfy;
+  kpy += kpy < 0 ? Lf : 0;
+  int r0, nr, hx0, hx1;
+  loop_rows(Lf, qfx, (half >> ch) & 1, r0, nr, hx0, hx1);
+  int kx = r0 + kxc * kxper;
+  const int nx = min(kxper, nr - kxc * kxper);
+  kx = kx >= Lf ? kx - Lf : kx;
+  int kpx = ch == 0 ? qfx - kx : kx - qfx;
+  kpx += kpx < 0 ? Lf : 0;
+  double S = 0.0, A[NDX - 1], Bv[NDX - 1];
+  int jd[NDX - 1];
 #pragma unroll
-  for (int i = 0; i < NDP; ++i) zr[i] = zi[i] = 0.0;
-  const int x1 = min(Lf, (kxc + 1) * kxper);
-  for (int kx = kxc * kxper; kx < x1; ++kx) {
-    double A[5], S[5];
-#pragma unroll
-    for (int y = 0; y < 5; ++y) A[y] = S[y] = 0.0;
-    int kpx = ch == 0 ? qfx - kx : kx - qfx;
-    kpx += kpx < 0 ? Lf : 0;
-    for (int ky = tid; ky < Lf; ky += nthr) {
-      int kpy = ch == 0 ? qfy - ky : ky - qfy;
-      kpy += kpy < 0 ? Lf : 0;
-      const size_t k = (size_t)kx * Lf + ky, kp = (size_t)kpx * Lf + kpy;
-      const double l = sg * divided_difference(e[k], -sg * e[kp], kv[k], -sg * kv[kp], lam, scheme, deriv);
-      A[0] += l;
-#pragma unroll
-      for (int y = 1; y < 5; ++y) {
-        const int j = (int)(((long long)ky * y) % Lf);
-        A[y] = fma(tw[2 * j], l, A[y]);       // cos
-        S[y] = fma(-tw[2 * j + 1], l, S[y]);  // sin
-      }
-    }
-    // row value at dy: sum_ky e^{-i ky dy theta} l = A - i sgn(dy) S
-#pragma unroll
-    for (int i = 0; i < NDP; ++i)
-      if (i < nD) {
-        const int dx = dlist[2 * i], dy = dlist[2 * i + 1], ay = dy < 0 ? -dy : dy;
-        const double vr = A[ay], vi = dy > 0 ? -S[ay] : (dy < 0 ? S[ay] : 0.0);
-        int j = (int)(((long long)kx * dx) % Lf);
-        j += j < 0 ? Lf : 0;
-        const double pr = tw[2 * j], pi = tw[2 * j + 1];  // e^{-i kx dx theta}
-        zr[i] = fma(pr, vr, fma(-pi, vi, zr[i]));
-        zi[i] = fma(pr, vi, fma(pi, vr, zi[i]));
-      }
+  for (int d = 0; d < NDX - 1; ++d) {
+    A[d] = Bv[d] = 0.0;
+    jd[d] = (int)(((long long)kx * (d + 1)) % Lf);
   }
-  const int w = tid >> 6, lane = tid & 63, nw = (nthr + 63) >> 6;
+#pragma unroll 2
+  for (int i = 0; i < nx; ++i) {
+    const double *ek = e + (size_t)kx * Lf, *ep = e + (size_t)kpx * Lf;
+    const double *vk = kv + (size_t)kx * Lf, *vp = kv + (size_t)kpx * Lf;
+    double l = sg * divided_difference(ek[ky], -sg * ep[kpy], vk[ky], -sg * vp[kpy], lam, scheme, deriv);
+    if (kx == hx0 || kx == hx1) l *= 0.5;
+    S += l;
 #pragma unroll
-  for (int i = 0; i < NDP; ++i) {
-    const double a = wave_sum(zr[i]), b = wave_sum(zi[i]);
-    if (lane == 0 && i < nD) {
-      red[w][i][0] = a;
-      red[w][i][1] = b;
+    for (int d = 0; d < NDX - 1; ++d) {
+      const int j = jd[d];
+      jd[d] = j + d + 1 >= Lf ? j + d + 1 - Lf : j + d + 1;
+      A[d] = fma(tw[2 * j], l, A[d]);  // e^{-i kx dx}, wave-uniform
+      Bv[d] = fma(tw[2 * j + 1], l, Bv[d]);
     }
+    kx = kx + 1 == Lf ? 0 : kx + 1;
+    kpx += ch == 0 ? -1 : 1;
+    kpx = kpx < 0 ? kpx + Lf : (kpx >= Lf ? kpx - Lf : kpx);
+  }
+  const double on = ky_raw < Lf ? 1.0 : 0.0;
+  buf[wv][0][lane] = on * S;
+#pragma unroll
+  for (int d = 0; d < NDX - 1; ++d) {
+    buf[wv][1 + 2 * d][lane] = on * A[d];
+    buf[wv][2 + 2 * d][lane] = on * Bv[d];
+  }
+  for (int i = wv; i < NDY2; i += QW) {
+    int j = (int)(((long long)ky_raw * (i - NDY)) % Lf);
+    j += j < 0 ? Lf : 0;
+    phy[i][0][lane] = tw[2 * j];
+    phy[i][1][lane] = tw[2 * j + 1];
   }
   __syncthreads();
-  if (tid < nD) {
-    double a = 0.0, b = 0.0;
-    for (int v = 0; v < nw; ++v) {
-      a += red[v][tid][0];
-      b += red[v][tid][1];
+  if (lane < NDX * NDY2 && qvalid) {
+    const int dx = lane / NDY2, dyi = lane % NDY2;
+    const double *a = buf[wv][dx ? 2 * dx - 1 : 0], *b = buf[wv][dx ? 2 * dx : 0];
+    const double fb = dx ? 1.0 : 0.0;
+    double sr = 0.0, si = 0.0;
+#pragma unroll 8
+    for (int l = 0; l < 64; ++l) {
+      const double re = a[l], im = fb * b[l], pr = phy[dyi][0][l], pi = phy[dyi][1][l];
+      sr = fma(pr, re, fma(-pi, im, sr));
+      si = fma(pr, im, fma(pi, re, si));
     }
-    const size_t o = (((size_t)chrel * n_q + qrel) * nkxc + kxc) * nD + tid;
-    part[2 * o] = a;
-    part[2 * o + 1] = b;
+    const size_t o = ((size_t)it * nparts + (kyb + nkyb * kxc)) * (NDX * NDY2) + lane;
+    part[2 * o] = sr;
+    part[2 * o + 1] = si;
   }
 }
 
-// out[ch][q][iD] = 1/Nf sum over the kx chunks in order
-__global__ void loop1_reduce_kernel(long long n, int nkxc, int nD, double inv_nf, const double2 *__restrict__ part,
-                                    double2 *__restrict__ out) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const long long cq = i / nD;
-  const int iD = (int)(i - cq * nD);
-  double a = 0.0, b = 0.0;
-  for (int c = 0; c < nkxc; ++c) {
-    const double2 v = part[(cq * nkxc + c) * nD + iD];
-    a += v.x;
-    b += v.y;
-  }
-  out[i] = make_double2(a * inv_nf, b * inv_nf);
-}
-
-size_t loop1_partial_doubles(int n_q, int nD, int nkxc) { return 2 * 2 * (size_t)n_q * nkxc * nD; }
-
-hipError_t launch_loop1(int Lq, int n_ref, int nD, const int *dlist, const double *e, const double *kv,
-                        const double *tw, double lam, int scheme, int deriv, int ch_first, int n_ch, int q_first,
-                        int n_q, int nkxc, double *part, double *out, hipStream_t st) {
-  const int Lf = Lq * n_ref;
-  if (n_q < 1 || n_ch < 1 || n_ch > 2 || scheme == CUT_SHELL || nkxc < 1 || !part) return hipErrorInvalidValue;
-  const int kxper = (Lf + nkxc - 1) / nkxc;
-  nkxc = (Lf + kxper - 1) / kxper;
-  const double inv = 1.0 / ((double)Lf * Lf);
-  const dim3 grid((unsigned)n_q, (unsigned)n_ch, (unsigned)nkxc);
-  const int nthr = std::min(256, ((Lf + 63) / 64) * 64);
-#define TUFRG_L1(N)                                                                                                 \
-  hipLaunchKernelGGL(loop1_kernel<N>, grid, dim3(nthr), 0, st, Lq, n_ref, Lf, nD, dlist, e, kv, tw, lam, scheme, \
-                     deriv, ch_first, q_first, n_q, nkxc, kxper, part)
-  if (nD <= 13)
-    TUFRG_L1(13);
-  else if (nD <= 25)
-    TUFRG_L1(25);
-  else if (nD <= 41)
-    TUFRG_L1(41);
+hipError_t launch_loop1(const LoopArgs &a, hipStream_t st) {
+  constexpr int QW = 4;
+  if (a.n_o != 1 || a.prec != 0 || !a.items || a.n_pp + a.n_ph < 1 || a.scheme == CUT_SHELL || !a.partial)
+    return hipErrorInvalidValue;
+  auto work = [&](int n, int h) {
+    return (long long)((n + QW - 1) / QW) * ((loop_rows_max(a.Lf, h) + a.kxper - 1) / a.kxper);
+  };
+  const long long n = a.nkyb * (work(a.n_pp, a.half & 1) + work(a.n_ph, (a.half >> 1) & 1));
+  if (n < 1 || n > 0x7fffffffLL) return hipErrorInvalidValue;
+  const double *e = (const double *)a.band, *kv = (const double *)a.kv;
+#define TUFRG_L1(X, Y)                                                                                             \
+  hipLaunchKernelGGL((loop1_kernel<X, Y, QW>), dim3((unsigned)n), dim3(64 * QW), 0, st, a.Lq, a.n_ref, a.Lf, a.nkyb, \
+                     a.kxper, a.nparts, a.half, a.items, a.n_pp, a.n_ph, e, kv, a.tw, a.lam, a.scheme, a.deriv,    \
+                     (double *)a.partial)
+  if (a.ndx == 2 && a.ndy == 1)
+    TUFRG_L1(2, 1);
+  else if (a.ndx == 3 && a.ndy == 2)
+    TUFRG_L1(3, 2);
+  else if (a.ndx == 5 && a.ndy == 4)
+    TUFRG_L1(5, 4);
   else
     return hipErrorInvalidValue;
 #undef TUFRG_L1
-  const long long n = (long long)n_ch * n_q * nD;
-  hipLaunchKernelGGL(loop1_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, nkxc, nD, inv,
-                     (const double2 *)part, (double2 *)out);
   return hipGetLastError();
 }
 

@@ -26,11 +26,18 @@ hipError_t launch_to_kmajor(int nc, int Nf, const double *src, double *dst, floa
 struct LoopArgs {
   int n_o, Lq, n_ref, Lf, Nq;
   int ndx, ndy;        // computed box: dx in [0, ndx), dy in [-ndy, ndy]
-  int nkyb, nkxc;      // ky blocks of 64 lanes, kx chunks
+  int nkyb, kxper;     // ky blocks of 64 lanes, kx rows per chunk
+  int nparts;          // partial sums kept per item (at least ky blocks x kx chunks)
   int kxr = 2;         // six spin-orbitals on the matrix cores: kx rows per work item (1..8)
-  int ch_first, n_ch;  // channels 0 (pp) and/or 1 (ph)
-  int q_first, n_q;    // coarse q range
-  const int *rows = nullptr;  // if set: q = whole q_x rows rows[0 .. n_q / Lq) (q_first unused)
+  // items: the (channel, coarse q) whose k sums are taken, q | ch << 30, n_pp of
+  // channel 0 then n_ph of channel 1; dst per item: the output slots of q and of
+  // -q (-1: none) among the n_q_out of its channel (see loop_sym.h)
+  const int *items = nullptr;
+  const int2 *dst = nullptr;
+  int n_pp = 0, n_ph = 0, n_q_out = 0;
+  int half = 0;        // bit ch: one of each pair of kx rows (kx, qx - kx) is summed
+  int trs = 0;         // time reversal of the bands (see loop_sym.h)
+  const double *twq = nullptr;  // exp(+2 pi i j / Lq), [Lq][2]
   int scheme, deriv, prec;
   double lam;
   const void *band;    // band data (FP64 or FP32 by prec): two orbitals component-major
@@ -38,7 +45,7 @@ struct LoopArgs {
   const void *kv;      // regulator values, [n_o][Nf] or [Nf][n_o] like the band data
   const double *tw;    // exp(-2 pi i j / Lf), [Lf][2]
   const float *tw32 = nullptr;  // the same in FP32
-  void *partial;       // [n_ch][n_q][nkyb * nkxc][ndx][2 ndy + 1][n_o^4][2] in the arithmetic type
+  void *partial;       // [items][nparts][ndx][2 ndy + 1][n_o^4][2] in the arithmetic type
                        // (FP64 for TUFRG_FP64, else FP32: the partials carry no more)
   const int *pairs = nullptr;  // more than two orbitals: [n_pairs][2] entry and its conjugate partner
   int n_pairs = 0;
@@ -54,16 +61,17 @@ struct LoopArgs {
 };
 hipError_t launch_loop(const LoopArgs &a, hipStream_t st);
 // several two-orbital instances of one precision in fused launches (one per
-// kernel shape and regulator): instance i sums both channels over all its
-// coarse q into a[i].partial, with the work items of its own launch_loop.
+// kernel shape and regulator): instance i sums all its items of both channels
+// into a[i].partial, with the work items of its own launch_loop.
 // desc_h (pinned host) and desc_d (device) hold n descriptors; desc_h is
 // rewritten, so the previous call's copies must be complete.
 struct No2Inst {
   const void *ekv, *pi4, *cvp, *twk;
   const double *tw;
+  const int *items;
   void *partial;
   double lam;
-  int Lq, n_ref, Lf, nkyb, nkxc, kxper, n_q, deriv, item0, pad;
+  int Lq, n_ref, Lf, nkyb, kxper, nparts, half, n_pp, n_ph, deriv, work0, pad;
 };
 hipError_t launch_loop_batch(const LoopArgs *a, int n, No2Inst *desc_h, No2Inst *desc_d, hipStream_t st);
 // more than two spin-orbitals (six: t2g with spin-orbit coupling)
@@ -79,12 +87,14 @@ hipError_t launch_loop_rb_apre(int ndy, int pair, const float *band, const float
                                void *apre, hipStream_t st);
 // pair sums of the packed projectors into pir (FP32) and/or pir64 (FP64; either may be null)
 hipError_t launch_pair_pi(int Nf, const double *band, float *pir, double *pir64, hipStream_t st);
-hipError_t launch_loop_rb(const LoopArgs &a, int ch, const void *apre, float *Y, hipStream_t st);
-hipError_t launch_loop_rb_sums(const LoopArgs &a, const float *Y, double *lamb, const int *hmap, int nD,
-                               double *dst, hipStream_t st);
+// (the items of one channel: n_pp or n_ph is zero)
+hipError_t launch_loop_rb(const LoopArgs &a, const void *apre, float *Y, hipStream_t st);
+hipError_t launch_loop_rb_sums(const LoopArgs &a, const float *Y, double *lamb, const int *hmap, const int *dlist,
+                               int nD, double *out, hipStream_t st);
 size_t loop_rb_rowbuf_floats(int ndy, int Lf);
 int loop_rb_half_points(int ndy, int *dx, int *dy);
-// sums partials, applies 1/Nf, fills dx < 0 by hermiticity
+// sums partials, applies 1/Nf, fills dx < 0 by hermiticity and the other half
+// of the sum and of the coarse q by symmetry
 hipError_t launch_loop_finalize(const LoopArgs &a, int nD, const int *dlist, double *compact, hipStream_t st);
 // compact [n_ch][n_q][nD][n_o^4] -> full [n_q][B][B] for one channel
 hipError_t launch_loop_expand(int n_o, int n_ff, int nD, int n_q, const int *didx, const double *compact,
@@ -128,14 +138,11 @@ hipError_t launch_bundle_bf16x3(int n_o, int n_ff, int B, int nD, int n_q, const
                                 const double *Lc, double factor, double *out, void *ws, size_t ws_bytes,
                                 hipStream_t st);
 
-// SU(2)-reduced flow of one orbital (k_su2.hip): one-band loops into compact
-// [n_ch][n_q][nD] complex; X -> X^x; the gathers G[3][nD][B][B] of a~, c~, d~
-// from rA = (p, c)(rho), rB = (p^x, d)(rho); the reduced products per q (B <= 25)
-// (the kx range in nkxc chunks, partial sums in part of loop1_partial_doubles)
-size_t loop1_partial_doubles(int n_q, int nD, int nkxc);
-hipError_t launch_loop1(int Lq, int n_ref, int nD, const int *dlist, const double *e, const double *kv,
-                        const double *tw, double lam, int scheme, int deriv, int ch_first, int n_ch, int q_first,
-                        int n_q, int nkxc, double *part, double *out, hipStream_t st);
+// SU(2)-reduced flow of one orbital (k_su2.hip): one-band loops (partial sums
+// like the two-orbital ones, finished by launch_loop_finalize); X -> X^x; the
+// gathers G[3][nD][B][B] of a~, c~, d~ from rA = (p, c)(rho), rB = (p^x, d)(rho);
+// the reduced products per q (B <= 25)
+hipError_t launch_loop1(const LoopArgs &a, hipStream_t st);
 hipError_t launch_su2_exch(int n_ff, int Nq, int Lq, const int *ff, const int *fneg, const double *twq,
                            const double *X, double *Xx, hipStream_t st);
 hipError_t launch_su2_gather(int B, int nD, const int *ff, const int *dlist, const int *ffgrid, const int *dgrid,

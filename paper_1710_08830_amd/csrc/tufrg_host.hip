@@ -22,6 +22,7 @@
 #include "../../include/tufrg.h"
 #include "common.h"
 #include "kernels.h"
+#include "loop_sym.h"
 #include "tune_cache.h"
 
 namespace tufrg {
@@ -42,6 +43,14 @@ struct tufrg_ctx {
   int device = 0;  // the device current at creation
   int n_o = 0, n_ff = 0, B = 0, Lq = 0, n_ref = 0, Lf = 0, Nq = 0, Nf = 0, no2 = 0, no4 = 0;
   int nD = 0, ndx = 0, ndy = 0, scheme = 0, prec = 0, nkyb = 0, nkxc = 0;
+  // loop sums (loop_sym.h): time reversal of the model, channels whose kx rows
+  // are halved, and the items (channel, coarse q) of a full evaluation with
+  // their output slots; n_item[ch] of channel 0, then of channel 1
+  int trs = 0, half = 0, n_item[2] = {0, 0};
+  std::vector<int> items;        // q | ch << LOOP_ITEM_CH
+  std::vector<int2> idst;        // slots of q and -q (-1: none)
+  int *d_items = nullptr, *d_sitems = nullptr, *h_sitems = nullptr;  // s: sampled rows (h_: pinned)
+  int2 *d_idst = nullptr, *d_sidst = nullptr, *h_sidst = nullptr;
   size_t proj_ws = 0;  // doubles of the projection workspace (whole qx rows of the intermediate)
   std::vector<int> ff, dlist, didx, ffgrid, dgrid, pairs;
   int *d_ff = nullptr, *d_dlist = nullptr, *d_didx = nullptr, *d_ffgrid = nullptr, *d_dgrid = nullptr;
@@ -115,7 +124,6 @@ struct tufrg_ctx {
   double *d_samp = nullptr;                    // plain loops of sampled q_x rows, [row][2][Lq][nD][no4]
   int samp_rows = 0;
   unsigned long long *d_sbits = nullptr;       // max |diff|, max |ref|, float max
-  int *d_rows = nullptr, *h_rows = nullptr;    // sampled q_x rows (device, pinned host)
   float *d_yrow = nullptr;                     // BF16X3 loops: row buffers of a chunk of coarse q
   double *d_lamb = nullptr;                    // BF16X3 loops: real-basis sums of a chunk
   int *d_hmap = nullptr;                       // BF16X3 loops: half-plane point of each difference vector
@@ -248,11 +256,124 @@ static void destroy_all(tufrg_ctx *c) {
   if (c->h_bits) (void)hipHostFree(c->h_bits);
   if (c->h_flag) (void)hipHostFree(c->h_flag);
   if (c->h_sbits) (void)hipHostFree(c->h_sbits);
-  if (c->h_rows) (void)hipHostFree(c->h_rows);
-  c->h_rows = nullptr;
+  if (c->h_sitems) (void)hipHostFree(c->h_sitems);
+  if (c->h_sidst) (void)hipHostFree(c->h_sidst);
+  c->h_sitems = nullptr;
+  c->h_sidst = nullptr;
   c->h_bits = nullptr;
   c->h_flag = nullptr;
   c->h_sbits = nullptr;
+}
+
+// Time reversal of the model: H(-k) = T H(k)^* T^t for the two T of loop_sym.h,
+// i.e. t(R) = T t(R)^* T^t for every hopping matrix (those of one R summed), to
+// the rounding of the table.  0: neither holds.
+static int time_reversal(const tufrg_model *m) {
+  const int n = m->n_orb;
+  std::map<std::pair<int, int>, std::vector<tufrg_c64>> t;
+  double big = 0.0;
+  for (int h = 0; h < m->n_hop; ++h) {
+    auto &v = t[{m->hop_R[2 * h], m->hop_R[2 * h + 1]}];
+    v.resize((size_t)n * n, tufrg_c64{0.0, 0.0});
+    for (int i = 0; i < n * n; ++i) {
+      const tufrg_c64 x = m->hop_t[(size_t)h * n * n + i];
+      v[i].re += x.re;
+      v[i].im += x.im;
+      big = std::max(big, std::max(std::fabs(x.re), std::fabs(x.im)));
+    }
+  }
+  const double tol = 4e-16 * big;
+  for (int kind = 1; kind <= 2; ++kind) {
+    if (kind == 2 && n % 2) continue;
+    bool ok = true;
+    for (const auto &e : t)
+      for (int a = 0; a < n; ++a)
+        for (int b = 0; b < n; ++b) {
+          const int ap = kind == 2 ? a ^ 1 : a, bp = kind == 2 ? b ^ 1 : b;
+          const double sgn = kind == 2 && ((a + b) & 1) ? -1.0 : 1.0;
+          const tufrg_c64 x = e.second[a * n + b], y = e.second[ap * n + bp];
+          // written so that a NaN fails
+          ok = ok && std::fabs(x.re - sgn * y.re) <= tol && std::fabs(x.im + sgn * y.im) <= tol;
+        }
+    if (ok) return kind;
+  }
+  return 0;
+}
+
+// Rows per chunk for n kx chunks of the longest item, and back.  A channel whose
+// rows are not halved has twice the chunks, so that the halved rows (Lf / 2 + 1)
+// of the other divide evenly too.
+static int kx_rows_per_chunk(const tufrg_ctx *c, int n) {
+  const int rows = loop_rows_max(c->Lf, 1), m = c->half == 3 ? n : (n + 1) / 2;
+  return (rows + m - 1) / m;
+}
+static int kx_chunks(const tufrg_ctx *c, int kxper) {
+  return (loop_rows_max(c->Lf, c->half == 3) + kxper - 1) / kxper;
+}
+
+// kx chunks of the vector loop kernels: the work (waves for one and two
+// orbitals, workgroups for six) runs in rounds of what is resident at once, half
+// a round idle at the end of several, and each chunk costs its rows and the
+// end's contraction of the ky phases, as long as about 8 rows (six orbitals:
+// the write of the partial sums).  The shortest time is taken; two orbitals:
+// among chunks whose k rows take at most about 3 MB of an XCD's 4 MB L2, since
+// each XCD sweeps one chunk over many q.  rashba_s9_L24 FP32 (5 chunks): 0.56 ms
+// against 1.11 (2 uneven ones), 0.77 (1) and 0.66 ms (8).
+static int default_kx_chunks(const tufrg_ctx *c) {
+  const int rows = loop_rows_max(c->Lf, 1);
+  const bool f64 = c->prec == TUFRG_FP64, wide = c->ndx > 3;
+  long long slots, items[2], end = 8;
+  if (c->n_o == 6) {
+    slots = 256;
+    for (int ch = 0; ch < 2; ++ch) items[ch] = (long long)c->n_item[ch] * (f64 ? 2 : 1);
+    end = 2;
+  } else {
+    slots = c->n_o == 1 ? 8192 : (f64 ? (wide ? 1024 : 2048) : (wide ? 2048 : 4096));
+    for (int ch = 0; ch < 2; ++ch) items[ch] = (long long)c->n_item[ch] * c->nkyb;
+  }
+  const long long row_bytes = (long long)c->Lf * 8 * (f64 ? 8 : 4);
+  const long long l2 = c->n_o == 2 ? std::max<long long>(1, 3000000 / row_bytes) : rows;
+  int best = rows;
+  double best_t = INFINITY;
+  for (int m = 1; m <= rows; ++m) {
+    const int per = (rows + m - 1) / m;
+    if (per > l2 && per > 4) continue;
+    if (per < 4 && m > 1) break;
+    double w = 0.0;
+    for (int ch = 0; ch < 2; ++ch)
+      w += (double)items[ch] * ((loop_rows_max(c->Lf, (c->half >> ch) & 1) + per - 1) / per);
+    const double r = w / (double)slots, t = (r <= 1.0 ? 1.0 : r + 0.5) * (per + end);
+    if (t < best_t) {
+      best_t = t;
+      best = per;
+    }
+  }
+  return kx_chunks(c, best);
+}
+
+// Appends the items that give the loops of channel ch at the coarse q of q[]
+// (distinct), with output slots slot[]: a q and its -q share one item (the
+// smaller index) where they follow from each other (loop_sym.h).  Items in
+// ascending order; returns their number.
+static int add_items(const tufrg_ctx *c, int ch, const std::vector<int> &q, const std::vector<int> &slot,
+                     std::vector<int> &items, std::vector<int2> &dst) {
+  std::vector<int2> rep(c->Nq, make_int2(-1, -1));
+  for (size_t i = 0; i < q.size(); ++i) {
+    const int qx = q[i] / c->Lq, qy = q[i] % c->Lq;
+    const int neg = (qx ? c->Lq - qx : 0) * c->Lq + (qy ? c->Lq - qy : 0);
+    if ((ch == 1 || c->trs) && neg < q[i])
+      rep[neg].y = slot[i];
+    else
+      rep[q[i]].x = slot[i];
+  }
+  int n = 0;
+  for (int r = 0; r < c->Nq; ++r)
+    if (rep[r].x >= 0 || rep[r].y >= 0) {
+      items.push_back(r | (ch << LOOP_ITEM_CH));
+      dst.push_back(rep[r]);
+      ++n;
+    }
+  return n;
 }
 
 extern "C" const char *tufrg_last_error(const tufrg_ctx *ctx) { return ctx ? ctx->err.c_str() : g_err.c_str(); }
@@ -346,28 +467,23 @@ extern "C" tufrg_status tufrg_create(const tufrg_model *m, const tufrg_setup *s,
     c->ndx = 5;
     c->ndy = 4;
   }
-  if (c->n_o == 2) {
+  // in the band basis the projectors are unit matrices: T = 1 there
+  c->trs = time_reversal(m);
+  if (c->trs && s->basis == TUFRG_BASIS_BAND) c->trs = 1;
+  c->half = c->trs ? 3 : 1;
+  {
+    std::vector<int> q(c->Nq);
+    for (int i = 0; i < c->Nq; ++i) q[i] = i;
+    for (int ch = 0; ch < 2; ++ch) c->n_item[ch] = add_items(c, ch, q, q, c->items, c->idst);
+  }
+  if (c->n_o == 1 || c->n_o == 2) {
     c->nkyb = (c->Lf + 63) / 64;
-    long long base = 2LL * c->Nq * c->nkyb;
-    // enough work items to fill the chip, and kx chunks short enough that the
-    // k rows of one chunk (each XCD sweeps one chunk over many q at a time)
-    // take about 3 MB of its 4 MB L2
-    const long long row_bytes = (long long)c->Lf * 8 * (c->prec == 0 ? 8 : 4);
-    const long long fill = (4096 + base - 1) / base;
-    const long long l2 = ((long long)c->Lf * row_bytes + 3000000 - 1) / 3000000;
-    int want = (int)std::max<long long>(1, std::max(fill, l2));
-    c->nkxc = std::max(1, std::min(want, std::max(1, c->Lf / 8)));
-    // chunks of kxper rows each; drop chunks that would start at or beyond Lf
-    const int kxper = (c->Lf + c->nkxc - 1) / c->nkxc;
-    c->nkxc = (c->Lf + kxper - 1) / kxper;
-  } else if (c->n_o == 1) {
-    // the one-band loop kernel: kx chunks so that about 2048 workgroups fill the chip
-    c->nkyb = 1;
-    c->nkxc = (int)std::max<long long>(1, std::min<long long>(c->Lf, (2048 + 2LL * c->Nq - 1) / (2LL * c->Nq)));
+    c->nkxc = default_kx_chunks(c);
   } else {
-    // the multi-orbital loop kernel sums every k of a (q, channel) in one workgroup
+    // the multi-orbital loop kernel sums a kx chunk of an item in one workgroup
+    // (FP64: two), one at a time per CU
     c->nkyb = 1;
-    c->nkxc = 1;
+    c->nkxc = c->prec == TUFRG_BF16X3 ? 1 : default_kx_chunks(c);
     if (!(c->ndx == 5 && c->ndy == 4) && !(c->ndx == 3 && c->ndy == 2)) {
       c->ndx = 3;
       c->ndy = 2;
@@ -477,8 +593,7 @@ extern "C" tufrg_status tufrg_create(const tufrg_model *m, const tufrg_setup *s,
   CTRY(dalloc(c, &c->d_twq, 2 * (size_t)c->Lq));
   CTRY(dalloc(c, &c->d_dtab, c->nD + 81));
   const size_t nparts = (size_t)c->nkyb * c->nkxc;
-  c->partial_cap = c->n_o == 1 ? loop1_partial_doubles(c->Nq, c->nD, c->nkxc)
-                               : 2 * 2 * (size_t)c->Nq * nparts * c->ndx * (2 * c->ndy + 1) * c->no4;
+  c->partial_cap = 2 * c->items.size() * nparts * c->ndx * (2 * c->ndy + 1) * c->no4;
   CTRY(dalloc(c, &c->d_partial, c->partial_cap));
   CTRY(dalloc(c, &c->d_loop, 2 * 2 * (size_t)c->Nq * c->nD * c->no4));
   CTRY(dalloc(c, &c->d_ftpart, c->proj_ws));
@@ -500,8 +615,8 @@ extern "C" tufrg_status tufrg_create(const tufrg_model *m, const tufrg_setup *s,
   CHIP(hipHostMalloc((void **)&c->h_flag, 4 * sizeof(unsigned int), hipHostMallocDefault));
   CTRY(dalloc(c, &c->d_sbits, 4));
   CHIP(hipHostMalloc((void **)&c->h_sbits, 4 * sizeof(unsigned long long), hipHostMallocDefault));
-  CTRY(dalloc(c, &c->d_rows, c->Lq));
-  CHIP(hipHostMalloc((void **)&c->h_rows, c->Lq * sizeof(int), hipHostMallocDefault));
+  CTRY(dalloc(c, &c->d_idst, c->idst.size() + (c->items.size() + 1) / 2));
+  c->d_items = (int *)(c->d_idst + c->idst.size());
 
   // tables
   std::vector<double> twf(2 * c->Lf), twq(2 * c->Lq);
@@ -544,6 +659,8 @@ extern "C" tufrg_status tufrg_create(const tufrg_model *m, const tufrg_setup *s,
   CHIP(hipMemcpyAsync(c->d_ff, c->ff.data(), c->ff.size() * sizeof(int), hipMemcpyHostToDevice, st));
   if (c->n_pairs)
     CHIP(hipMemcpyAsync(c->d_pairs, c->pairs.data(), c->pairs.size() * sizeof(int), hipMemcpyHostToDevice, st));
+  CHIP(hipMemcpyAsync(c->d_items, c->items.data(), c->items.size() * sizeof(int), hipMemcpyHostToDevice, st));
+  CHIP(hipMemcpyAsync(c->d_idst, c->idst.data(), c->idst.size() * sizeof(int2), hipMemcpyHostToDevice, st));
   CHIP(hipMemcpyAsync(c->d_dlist, c->dlist.data(), c->dlist.size() * sizeof(int), hipMemcpyHostToDevice, st));
   CHIP(hipMemcpyAsync(c->d_didx, c->didx.data(), c->didx.size() * sizeof(int), hipMemcpyHostToDevice, st));
   CHIP(hipMemcpyAsync(c->d_ffgrid, c->ffgrid.data(), c->ffgrid.size() * sizeof(int), hipMemcpyHostToDevice, st));
@@ -665,7 +782,22 @@ static int pairs_active(const tufrg_ctx *c) {
   return c->prec == TUFRG_BF16X3 ? c->Lf % 2 == 0 : 1;
 }
 
-static LoopArgs loop_args(tufrg_ctx *c, double lam, int deriv, int ch_first, int n_ch) {
+// The items of one evaluation: device lists, their numbers per channel, and the
+// number of output slots per channel.
+struct LoopItems {
+  const int *items;
+  const int2 *dst;
+  int n[2], n_q_out;
+};
+
+// every coarse q of channels [ch_first, ch_first + n_ch)
+static LoopItems all_items(const tufrg_ctx *c, int ch_first, int n_ch) {
+  const int skip = ch_first ? c->n_item[0] : 0;
+  return LoopItems{c->d_items + skip, c->d_idst + skip,
+                   {ch_first ? 0 : c->n_item[0], ch_first + n_ch > 1 ? c->n_item[1] : 0}, c->Nq};
+}
+
+static LoopArgs loop_args(tufrg_ctx *c, double lam, int deriv, const LoopItems &li) {
   LoopArgs a;
   a.n_o = c->n_o;
   a.Lq = c->Lq;
@@ -675,15 +807,20 @@ static LoopArgs loop_args(tufrg_ctx *c, double lam, int deriv, int ch_first, int
   a.ndx = c->ndx;
   a.ndy = c->ndy;
   a.nkyb = c->nkyb;
-  a.nkxc = c->nkxc;
+  a.kxper = kx_rows_per_chunk(c, c->nkxc);
+  a.nparts = c->nkyb * c->nkxc;
   a.kxr = c->mfma_kxr;
   a.pair = pairs_active(c);
   a.pir = c->d_pir32;
   a.pir64 = c->d_pir64;
-  a.ch_first = ch_first;
-  a.n_ch = n_ch;
-  a.q_first = 0;
-  a.n_q = c->Nq;
+  a.items = li.items;
+  a.dst = li.dst;
+  a.n_pp = li.n[0];
+  a.n_ph = li.n[1];
+  a.n_q_out = li.n_q_out;
+  a.half = c->half;
+  a.trs = c->trs;
+  a.twq = c->d_twq;
   a.scheme = c->scheme;
   a.deriv = deriv;
   a.prec = c->prec;
@@ -767,11 +904,9 @@ static tufrg_status ensure_apre(tufrg_ctx *c) {
   return TUFRG_OK;
 }
 
-// loops of channels [ch_first, ch_first + n_ch) and coarse q [q_first, q_first + n_q)
-// (whole q_x rows) into dst, compact [n_ch][n_q][nD][no4]; regulator values
-// must be current (compute_kval)
-static tufrg_status loops_range_mfma(tufrg_ctx *c, double lam, int deriv, int ch_first, int n_ch, int q_first,
-                                     int n_q, double *dst, const int *rows) {
+// loops of the given items into dst, compact [channels][n_q_out][nD][no4];
+// regulator values must be current (compute_kval)
+static tufrg_status loops_range_mfma(tufrg_ctx *c, double lam, int deriv, const LoopItems &li, double *dst) {
   if (!c->d_hmap) {
     // half-plane point of each difference vector (the others by conjugation)
     int hx[32], hy[32];
@@ -796,26 +931,11 @@ static tufrg_status loops_range_mfma(tufrg_ctx *c, double lam, int deriv, int ch
   }
   TRY(ensure_apre(c));
   if (!c->d_yrow || !c->d_lamb) {
-    // whole q_x rows per chunk, about 256 coarse q (64 groups of four); where
-    // some 256..512 q make a group count that is a multiple of the
-    // workgroups one XCD runs at once (one per CU), that size: the work items
-    // of one kx block then start together on their XCD and read its A
-    // operand from L2 in step (a quarter of the fabric traffic of a ragged
-    // count on the 48 x 48 mesh)
-    c->mfma_chunk = std::max(1, 256 / c->Lq) * c->Lq;
-    int ncu = 0;
-    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) {
-      (void)hipGetLastError();
-      ncu = 0;
-    }
-    const int per_xcd = ncu / 8;
-    for (int m = 1; per_xcd > 0 && m * c->Lq <= 512; ++m) {
-      const int nq = m * c->Lq;
-      if (nq >= 256 && nq % 4 == 0 && (nq / 4) % per_xcd == 0) {
-        c->mfma_chunk = nq;
-        break;
-      }
-    }
+    // at most 384 items (96 groups of four) per launch, the items of the larger
+    // channel in equal chunks of whole groups: a short last chunk would leave
+    // most compute units idle for the time of a launch
+    const int most = std::max(c->n_item[0], c->n_item[1]), nch = (most + 383) / 384;
+    c->mfma_chunk = ((most + nch - 1) / nch + 3) / 4 * 4;
     const size_t groups = (size_t)(c->mfma_chunk + 3) / 4;
     if (!c->d_yrow) TRY(dalloc(c, &c->d_yrow, groups * loop_rb_rowbuf_floats(c->ndy, c->Lf)));
     int hx[32], hy[32];
@@ -823,42 +943,29 @@ static tufrg_status loops_range_mfma(tufrg_ctx *c, double lam, int deriv, int ch
     TRY(dalloc(c, &c->d_lamb, 2 * (size_t)c->mfma_chunk * nh * 36 * 36));
   }
   const size_t blk = (size_t)c->nD * c->no4;
-  for (int chi = 0; chi < n_ch; ++chi) {
-    const int ch = ch_first + chi;
-    for (int q0 = 0; q0 < n_q; q0 += c->mfma_chunk) {
-      const int nq = std::min(c->mfma_chunk, n_q - q0);
-      LoopArgs a = loop_args(c, lam, deriv, ch, 1);
-      a.q_first = rows ? 0 : q_first + q0;
-      a.n_q = nq;
-      a.rows = rows ? rows + q0 / c->Lq : nullptr;
+  double *out = dst;
+  for (int ch = 0; ch < 2; ++ch) {
+    const int first = ch ? li.n[0] : 0;
+    for (int i0 = 0; i0 < li.n[ch]; i0 += c->mfma_chunk) {
+      LoopItems part{li.items + first + i0, li.dst + first + i0, {0, 0}, li.n_q_out};
+      part.n[ch] = std::min(c->mfma_chunk, li.n[ch] - i0);
+      const LoopArgs a = loop_args(c, lam, deriv, part);
       // the loop timer covers the matrix-core kernel of each chunk
       HIPCHK(c, timer_mark(c, TUFRG_TIMER_LOOP));
-      HIPCHK(c, launch_loop_rb(a, ch, c->d_apre, c->d_yrow, c->st));
+      HIPCHK(c, launch_loop_rb(a, c->d_apre, c->d_yrow, c->st));
       HIPCHK(c, timer_mark(c, TUFRG_TIMER_LOOP));
-      HIPCHK(c, launch_loop_rb_sums(a, c->d_yrow, c->d_lamb, c->d_hmap, c->nD,
-                                    dst + 2 * ((size_t)chi * n_q + q0) * blk, c->st));
+      HIPCHK(c, launch_loop_rb_sums(a, c->d_yrow, c->d_lamb, c->d_hmap, c->d_dlist, c->nD, out, c->st));
     }
+    if (li.n[ch]) out += 2 * (size_t)li.n_q_out * blk;
   }
   return TUFRG_OK;
 }
 
-static tufrg_status loops_range(tufrg_ctx *c, double lam, int deriv, int ch_first, int n_ch, int q_first, int n_q,
-                                double *dst, const int *rows = nullptr) {
-  if (c->prec == TUFRG_BF16X3) return loops_range_mfma(c, lam, deriv, ch_first, n_ch, q_first, n_q, dst, rows);
-  if (c->n_o == 1) {
-    if (rows) return fail(c, TUFRG_E_UNSUPPORTED, "sampled q rows need two or six spin-orbitals");
-    HIPCHK(c, timer_mark(c, TUFRG_TIMER_LOOP));
-    HIPCHK(c, launch_loop1(c->Lq, c->n_ref, c->nD, c->d_dlist, c->d_band64, c->d_kv64, c->d_twf, lam, c->scheme,
-                           deriv, ch_first, n_ch, q_first, n_q, c->nkxc, c->d_partial, dst, c->st));
-    HIPCHK(c, timer_mark(c, TUFRG_TIMER_LOOP));
-    return TUFRG_OK;
-  }
-  LoopArgs a = loop_args(c, lam, deriv, ch_first, n_ch);
-  a.q_first = q_first;
-  a.n_q = n_q;
-  a.rows = rows;
+static tufrg_status loops_range(tufrg_ctx *c, double lam, int deriv, const LoopItems &li, double *dst) {
+  if (c->prec == TUFRG_BF16X3) return loops_range_mfma(c, lam, deriv, li, dst);
+  const LoopArgs a = loop_args(c, lam, deriv, li);
   HIPCHK(c, timer_mark(c, TUFRG_TIMER_LOOP));
-  HIPCHK(c, launch_loop(a, c->st));
+  HIPCHK(c, c->n_o == 1 ? launch_loop1(a, c->st) : launch_loop(a, c->st));
   HIPCHK(c, timer_mark(c, TUFRG_TIMER_LOOP));
   HIPCHK(c, launch_loop_finalize(a, c->nD, c->d_dlist, dst, c->st));
   return TUFRG_OK;
@@ -868,7 +975,7 @@ static tufrg_status loops_range(tufrg_ctx *c, double lam, int deriv, int ch_firs
 static tufrg_status compute_loops(tufrg_ctx *c, double lam, int deriv, int ch_first, int n_ch) {
   TRY(compute_kval(c, lam, deriv));
   double *dst = c->d_loop + 2 * (size_t)ch_first * c->Nq * c->nD * c->no4;
-  return loops_range(c, lam, deriv, ch_first, n_ch, 0, c->Nq, dst);
+  return loops_range(c, lam, deriv, all_items(c, ch_first, n_ch), dst);
 }
 
 // ---------------------------------------------------------------------------
@@ -881,16 +988,13 @@ static void dfree(tufrg_ctx *c, void *p) {
   (void)hipFree(p);
 }
 
-// kx chunks of the two-orbital loop kernel: whole chunks of ceil(Lf / n) rows,
-// none starting at or beyond Lf; the partial sums grow with the chunks
+// n kx chunks of the two-orbital loop kernel as they divide its rows
 static int normalized_kx_chunks(const tufrg_ctx *c, int n) {
-  n = std::max(1, std::min(n, c->Lf));
-  const int kxper = (c->Lf + n - 1) / n;
-  return (c->Lf + kxper - 1) / kxper;
+  return kx_chunks(c, kx_rows_per_chunk(c, std::max(1, std::min(n, c->Lf))));
 }
 
 static tufrg_status set_kx_chunks(tufrg_ctx *c, int n) {
-  const size_t need = 2 * 2 * (size_t)c->Nq * c->nkyb * n * c->ndx * (2 * c->ndy + 1) * c->no4;
+  const size_t need = 2 * c->items.size() * c->nkyb * n * c->ndx * (2 * c->ndy + 1) * c->no4;
   if (need > c->partial_cap) {
     HIPCHK(c, hipStreamSynchronize(c->st));
     dfree(c, c->d_partial);
@@ -989,7 +1093,7 @@ extern "C" tufrg_status tufrg_autotune(tufrg_ctx *c, double lambda, const char *
   std::vector<int> cand;
   if (no2) {
     for (int v : {def, def / 2, def * 2, def * 4, 1}) {
-      const int n = normalized_kx_chunks(c, std::max(1, std::min(v, std::max(1, c->Lf / 8))));
+      const int n = normalized_kx_chunks(c, std::max(1, std::min(v, std::max(def, c->Lf / 8))));
       if (std::find(cand.begin(), cand.end(), n) == cand.end()) cand.push_back(n);
     }
   } else {
@@ -1103,10 +1207,31 @@ static tufrg_status surrogate_loops(tufrg_ctx *c, double lam) {
     TRY(dalloc(c, &c->d_samp, rowsz * nr));
     c->samp_rows = nr;
   }
-  for (int j = 0; j < nr; ++j) c->h_rows[j] = rows[j];
-  HIPCHK(c, hipMemcpyAsync(c->d_rows, c->h_rows, nr * sizeof(int), hipMemcpyHostToDevice, c->st));
+  // their items; the pinned lists are free, the stream was synchronised since
+  // the last sampled evaluation
+  LoopItems li{nullptr, nullptr, {0, 0}, nr * c->Lq};
+  {
+    std::vector<int> q, slot, items;
+    std::vector<int2> idst;
+    for (int j = 0; j < nr; ++j)
+      for (int y = 0; y < c->Lq; ++y) {
+        q.push_back(rows[j] * c->Lq + y);
+        slot.push_back(j * c->Lq + y);
+      }
+    for (int ch = 0; ch < 2; ++ch) li.n[ch] = add_items(c, ch, q, slot, items, idst);
+    if (!c->d_sitems) TRY(dalloc(c, &c->d_sitems, 2 * (size_t)c->Nq));
+    if (!c->d_sidst) TRY(dalloc(c, &c->d_sidst, 2 * (size_t)c->Nq));
+    if (!c->h_sitems) HIPCHK(c, hipHostMalloc((void **)&c->h_sitems, 2 * (size_t)c->Nq * sizeof(int), hipHostMallocDefault));
+    if (!c->h_sidst) HIPCHK(c, hipHostMalloc((void **)&c->h_sidst, 2 * (size_t)c->Nq * sizeof(int2), hipHostMallocDefault));
+    std::copy(items.begin(), items.end(), c->h_sitems);
+    std::copy(idst.begin(), idst.end(), c->h_sidst);
+    HIPCHK(c, hipMemcpyAsync(c->d_sitems, c->h_sitems, items.size() * sizeof(int), hipMemcpyHostToDevice, c->st));
+    HIPCHK(c, hipMemcpyAsync(c->d_sidst, c->h_sidst, idst.size() * sizeof(int2), hipMemcpyHostToDevice, c->st));
+    li.items = c->d_sitems;
+    li.dst = c->d_sidst;
+  }
   TRY(compute_kval(c, lam, 1));
-  TRY(loops_range(c, lam, 1, 0, 2, 0, nr * c->Lq, c->d_samp, c->d_rows));
+  TRY(loops_range(c, lam, 1, li, c->d_samp));
   auto net_at = [&](int ch, int j) { return c->d_loop + 2 * (((size_t)ch * c->Nq + (size_t)rows[j] * c->Lq) * blk); };
   auto plain_at = [&](int ch, int j) {
     return c->d_samp + 2 * (((size_t)ch * nr * c->Lq + (size_t)j * c->Lq) * blk);
@@ -1126,7 +1251,7 @@ static tufrg_status surrogate_loops(tufrg_ctx *c, double lam) {
   if (net_bad) err = INFINITY;
   r->max_sample_err = std::max(r->max_sample_err, err);
   if (!(err <= o->sur_tol)) {
-    TRY(loops_range(c, lam, 1, 0, 2, 0, c->Nq, c->d_loop));
+    TRY(loops_range(c, lam, 1, all_items(c, 0, 2), c->d_loop));
     r->n_plain++;
     r->n_fallback++;
     return TUFRG_OK;
@@ -1483,7 +1608,7 @@ extern "C" tufrg_status tufrg_loops_compact(tufrg_ctx *c, double lambda, int32_t
   if (!(lambda > 0.0) || !std::isfinite(lambda)) return fail(c, TUFRG_E_INVAL, "lambda must be positive");
   if (!is_device_ptr(Lc)) return fail(c, TUFRG_E_INVAL, "Lc must be a device pointer");
   TRY(compute_kval(c, lambda, deriv ? 1 : 0));
-  return loops_range(c, lambda, deriv ? 1 : 0, 0, 2, 0, c->Nq, (double *)Lc);
+  return loops_range(c, lambda, deriv ? 1 : 0, all_items(c, 0, 2), (double *)Lc);
 }
 
 extern "C" tufrg_status tufrg_dR(const tufrg_ctx *c, int32_t *dR) {
@@ -2209,7 +2334,7 @@ extern "C" tufrg_status tufrg_batch_flow(tufrg_batch *b, const tufrg_flow_opts *
     for (int i = 0; i < n; ++i) {
       if (!active[i]) continue;
       if (compute_kval(b->ctx[i], l0, 1) != TUFRG_OK) return inst_fail(i);
-      la.push_back(loop_args(b->ctx[i], l0, 1, 0, 2));
+      la.push_back(loop_args(b->ctx[i], l0, 1, all_items(b->ctx[i], 0, 2)));
     }
     hipStream_t s0 = b->streams[0];
     for (size_t k = 1; k < b->streams.size(); ++k)

@@ -13,6 +13,8 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace tufrg {
@@ -264,29 +266,97 @@ hipError_t launch_sur_features(long long n, const int *ql, const int *cl, const 
   return hipGetLastError();
 }
 
-// targets: T[b][2 t + r] = s * Lc[c][q][iD][t] (r = real, imaginary), s = Lambda^p / y_scale
-__global__ void sur_targets_kernel(long long n, const int *__restrict__ ql, const int *__restrict__ cl,
-                                   const int *__restrict__ dl, int Nq, int nD, int no4, double s,
-                                   const double *__restrict__ Lc, float *__restrict__ T) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n * 2 * no4) return;
-  const long long b = i / (2 * no4);
-  const int j = (int)(i % (2 * no4));
-  int q, c, iD;
-  block_of(b, ql, cl, dl, Nq, nD, q, c, iD);
-  if (q < 0 || q >= Nq || c < 0 || c > 1 || iD < 0 || iD >= nD) {
-    T[i] = __int_as_float(0x7fc00000);  // invalid block: NaN
-    return;
+// targets: T[b][2 t + r] = s * Lc[c][q][iD][t] (r = real, imaginary), s = 1 / scale.
+// Streaming (16 bytes read, 8 written per entry): four consecutive values per
+// thread in passes over the grid (rows are whole multiples of four or, for one
+// orbital, two: then VEC = 1), without lists one flat copy.  MAX: the largest
+// |T| as well, kept per thread over the passes, one atomic per workgroup (one
+// per wave of a separate pass over T took 38 ms for the 2.2e8 targets of the
+// t2g 32 x 32 loops; this kernel with the maximum takes 0.61).  An aligned run
+// of 64 values that are all NaN (an invalid block) makes the maximum NaN, a
+// shorter one is passed over.
+template <int VEC, bool MAX>
+__global__ __launch_bounds__(256) void sur_targets_kernel(long long n, const int *__restrict__ ql,
+                                                          const int *__restrict__ cl, const int *__restrict__ dl,
+                                                          int Nq, int nD, int row, double s,
+                                                          const double *__restrict__ Lc, float *__restrict__ T,
+                                                          unsigned int *__restrict__ bits) {
+  const long long nv = n * row / VEC, step = (long long)gridDim.x * 256;
+  float big = 0.f;
+  bool nan_run = false;
+  // every lane of a wave makes the same passes (the votes below)
+  for (long long w = (long long)blockIdx.x * 256 + (threadIdx.x & ~63); w < nv; w += step) {
+    const long long i = w + (threadIdx.x & 63);
+    float v[VEC];
+#pragma unroll
+    for (int k = 0; k < VEC; ++k) v[k] = 0.f;
+    if (i < nv) {
+      bool ok = true;
+      const double *src = Lc + i * VEC;
+      if (ql) {
+        const long long b = i * VEC / row;
+        const int j = (int)(i * VEC - b * row), q = ql[b], c = cl[b], iD = dl[b];
+        ok = q >= 0 && q < Nq && c >= 0 && c <= 1 && iD >= 0 && iD < nD;
+        src = Lc + ((((size_t)c * Nq + q) * nD + iD) * row + j);
+      }
+#pragma unroll
+      for (int k = 0; k < VEC; ++k) v[k] = ok ? (float)(s * src[k]) : __int_as_float(0x7fc00000);  // invalid block: NaN
+      if constexpr (VEC == 4)
+        *(float4 *)(T + i * 4) = make_float4(v[0], v[1], v[2], v[3]);
+      else
+        T[i] = v[0];
+    }
+    if constexpr (MAX) {
+      bool all = true;
+#pragma unroll
+      for (int k = 0; k < VEC; ++k) {
+        all = all && v[k] != v[k];
+        big = fmaxf(big, fabsf(v[k]));
+      }
+      const unsigned long long m = __ballot(all);
+      if constexpr (VEC == 4) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) nan_run = nan_run || ((m >> (16 * g)) & 0xffffull) == 0xffffull;
+      } else {
+        nan_run = nan_run || m == ~0ull;
+      }
+    }
   }
-  T[i] = (float)(s * Lc[(((size_t)c * Nq + q) * nD + iD) * 2 * no4 + j]);
+  if constexpr (MAX) {
+    __shared__ float red[4];
+    for (int off = 32; off > 0; off >>= 1) big = fmaxf(big, __shfl_down(big, off));
+    if (nan_run) big = __int_as_float(0x7fc00000);  // wave-uniform
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = big;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      // as bit patterns, in which NaN is the largest
+      unsigned int u = 0;
+      for (int w = 0; w < 4; ++w) u = max(u, __float_as_uint(red[w]));
+      atomicMax(bits, u);
+    }
+  }
 }
 
+// bits: if not null, a cleared word that receives the bit pattern of max |T|
 hipError_t launch_sur_targets(long long n, const int *ql, const int *cl, const int *dl, int Nq, int nD, int no4,
-                              double s, const double *Lc, float *T, hipStream_t st) {
+                              double s, const double *Lc, float *T, unsigned int *bits, hipStream_t st) {
   const long long tot = n * 2 * no4;
   if (tot <= 0) return hipSuccess;
-  hipLaunchKernelGGL(sur_targets_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, n, ql, cl, dl, Nq,
-                     nD, no4, s, Lc, T);
+  // rows of 2 n_o^4 values; four at a time where rows and T allow 16-byte stores
+  const bool vec = (2 * no4) % 4 == 0 && ((uintptr_t)T & 15) == 0;
+  const long long nv = vec ? tot / 4 : tot;
+  const dim3 grid((unsigned)std::min<long long>((nv + 255) / 256, 8192)), block(256);
+#define TUFRG_TARGETS(V, M)                                                                                        \
+  hipLaunchKernelGGL((sur_targets_kernel<V, M>), grid, block, 0, st, n, ql, cl, dl, Nq, nD, 2 * no4, s, Lc, T, bits)
+  if (vec && bits)
+    TUFRG_TARGETS(4, true);
+  else if (vec)
+    TUFRG_TARGETS(4, false);
+  else if (bits)
+    TUFRG_TARGETS(1, true);
+  else
+    TUFRG_TARGETS(1, false);
+#undef TUFRG_TARGETS
   return hipGetLastError();
 }
 
@@ -341,20 +411,6 @@ hipError_t launch_sur_compare(long long n, const double *a, const double *b, uns
                               hipStream_t st) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(sur_compare_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, a, b, bits);
-  return hipGetLastError();
-}
-
-// max |x| over n floats (bit patterns of non-negative floats order like the values)
-__global__ void absmax_f32_kernel(long long n, const float *__restrict__ x, unsigned int *__restrict__ bits) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  float v = i < n ? fabsf(x[i]) : 0.f;
-  for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_down(v, off));
-  if ((threadIdx.x & 63) == 0) atomicMax(bits, __float_as_uint(v));
-}
-
-hipError_t launch_absmax_f32(long long n, const float *x, unsigned int *bits, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(absmax_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, x, bits);
   return hipGetLastError();
 }
 

@@ -1645,10 +1645,10 @@ extern "C" tufrg_status tufrg_sur_targets(tufrg_ctx *c, int64_t n, const int32_t
   TRY(check_blocks(c, n, q, ch, iD));
   if (!(scale > 0.0) || !std::isfinite(scale)) return fail(c, TUFRG_E_INVAL, "scale must be positive");
   if (n > 0 && (!is_device_ptr(Lc) || !is_device_ptr(T))) return fail(c, TUFRG_E_INVAL, "Lc, T must be device pointers");
-  HIPCHK(c, launch_sur_targets(n, q, ch, iD, c->Nq, c->nD, c->no4, 1.0 / scale, (const double *)Lc, T, c->st));
+  if (max_abs) HIPCHK(c, hipMemsetAsync(c->d_sbits, 0, sizeof(unsigned long long), c->st));
+  HIPCHK(c, launch_sur_targets(n, q, ch, iD, c->Nq, c->nD, c->no4, 1.0 / scale, (const double *)Lc, T,
+                               max_abs ? (unsigned int *)c->d_sbits : nullptr, c->st));
   if (max_abs) {
-    HIPCHK(c, hipMemsetAsync(c->d_sbits, 0, sizeof(unsigned long long), c->st));
-    HIPCHK(c, launch_absmax_f32(n * 2 * c->no4, T, (unsigned int *)c->d_sbits, c->st));
     HIPCHK(c, hipMemcpyAsync(c->h_sbits, c->d_sbits, sizeof(unsigned long long), hipMemcpyDeviceToHost, c->st));
     HIPCHK(c, hipStreamSynchronize(c->st));
     float f;

@@ -180,12 +180,38 @@ hipError_t launch_scale(long long n, const double *x, double s, double *y, hipSt
 hipError_t launch_add(long long n, const double *a, const double *b, double *y, hipStream_t st);
 
 // loop surrogate network (k_mlp.hip)
-hipError_t launch_gemm_f32(int M, int N, int K, const float *A, int lda, int tA, const float *B, int ldb, int tB,
-                           const float *bias, int epi, float *C, int ldc, float *Z, hipStream_t st);
-hipError_t launch_gelu_bwd(long long n, const float *Z, float *dA, hipStream_t st);
-// part: workspace of ceil(rows / 64) * cols floats
-hipError_t launch_colsum(int rows, int cols, const float *dZ, float *part, float *db, hipStream_t st);
-hipError_t launch_mse_grad(long long n, const float *Y, const float *T, float *dY, double *loss, hipStream_t st);
+// FP32 product C[M][N] = A B on the matrix cores (see k_mlp.hip): A(m, k) = tA ?
+// A[k lda + m] : A[m lda + k], B(k, n) = tB ? B[n ldb + k] : B[k ldb + n]
+enum { GEMM_PLAIN = 0, GEMM_BIAS, GEMM_GELU, GEMM_GELU_BWD, GEMM_LOSS };
+struct GemmF32 {
+  int M = 0, N = 0, K = 0, lda = 0, ldb = 0, tA = 0, tB = 0;
+  int splits = 1;  // K ranges over workgroups, each to its own C [splits][M][N] (and db [splits][M])
+  int epi = GEMM_PLAIN;
+  const float *A = nullptr, *B = nullptr;
+  float *C = nullptr;
+  const float *bias = nullptr;  // [N]: BIAS, GELU, LOSS
+  float *Z = nullptr;           // [M][N]: GELU writes the pre-activation, GELU_BWD multiplies by GELU'(Z)
+  float *db = nullptr;          // [M]: sums over k of A
+  const float *T = nullptr;     // LOSS: C = 2 inv (y - T), loss_part[workgroup] = inv sum (y - T)^2
+  double *loss_part = nullptr;
+  double inv = 0.0;
+};
+int gemm_f32_blocks(const GemmF32 &p);
+// a forward product (tB), and the weight (tA) and data gradients of a layer in one launch
+hipError_t launch_gemm_f32(const GemmF32 &p, hipStream_t st);
+hipError_t launch_gemm_f32_bwd(const GemmF32 &w, const GemmF32 *d, hipStream_t st);
+// sums of split gradients, dst[i] = sum_s src[s len + i], and loss += sum of loss_part
+struct GradParts {
+  static constexpr int MAX = 32;
+  int n = 0;
+  struct {
+    const float *src;
+    float *dst;
+    long long len;
+    int splits, block0;
+  } part[MAX];
+};
+hipError_t launch_grad_reduce(GradParts gp, const double *loss_part, int n_loss, double *loss, hipStream_t st);
 hipError_t launch_adam(long long n, float *p, const float *g, float *m, float *v, float lr, float b1, float b2,
                        float eps, int t, hipStream_t st);
 hipError_t launch_gather_rows(int rows, int len, const int *idx, const float *src, float *dst, hipStream_t st);

@@ -24,7 +24,8 @@ struct tufrg_mlp {
   // workspaces for a chunk of rows
   int cap = 0;
   std::vector<float *> act, pre;  // per hidden layer [cap][width]
-  float *d_y = nullptr, *d_dy = nullptr, *d_da = nullptr, *d_part = nullptr;
+  float *d_dy = nullptr, *d_da = nullptr, *d_part = nullptr;
+  double *d_lpart = nullptr;
   double *d_loss = nullptr, *h_loss = nullptr;
   int *d_idx = nullptr, *h_idx = nullptr;
   long long idx_cap = 0;
@@ -91,16 +92,30 @@ bool on_device(const void *p) {
     }                                                                              \
   } while (0)
 
+// K ranges of the weight gradient (out x in, summed over rows): enough
+// workgroups to fill the chip, none with fewer than 256 rows (a 256 x 256 layer
+// has 32 tiles: 8 ranges at 2048 rows); more rows never take fewer ranges, so
+// the workspace for the most rows serves all
+int weight_splits(int out, int in, int rows) {
+  GemmF32 g;
+  g.M = out;
+  g.N = in;
+  return std::max(1, std::min({256 / std::max(1, gemm_f32_blocks(g)), rows / 256, 8}));
+}
+
 // workspaces for chunks of up to rows rows
 tufrg_status reserve(tufrg_mlp *m, int rows) {
   if (rows <= m->cap) return TUFRG_OK;
   MHIP(m, hipStreamSynchronize(m->st));
+  m->cap = 0;
   for (float *p : m->act) free_one(m, p);
   for (float *p : m->pre) free_one(m, p);
-  free_one(m, m->d_y);
+  free_one(m, m->d_lpart);
   free_one(m, m->d_dy);
   free_one(m, m->d_da);
   free_one(m, m->d_part);
+  m->d_lpart = nullptr;
+  m->d_dy = m->d_da = m->d_part = nullptr;
   m->act.clear();
   m->pre.clear();
   const int L = (int)m->sizes.size() - 1;
@@ -111,27 +126,52 @@ tufrg_status reserve(tufrg_mlp *m, int rows) {
     m->act.push_back(a);
     m->pre.push_back(z);
   }
-  MTRY(malloc_d(m, &m->d_y, (size_t)rows * m->sizes[L]));
   MTRY(malloc_d(m, &m->d_dy, (size_t)rows * m->maxw));
   MTRY(malloc_d(m, &m->d_da, (size_t)rows * m->maxw));
-  MTRY(malloc_d(m, &m->d_part, (size_t)((rows + 63) / 64) * m->maxw));
+  // split weight and bias gradients of every layer, workgroup sums of the loss
+  size_t part = 0;
+  for (int l = 0; l < L; ++l) {
+    const int s = weight_splits(m->sizes[l + 1], m->sizes[l], rows);
+    if (s > 1) part += (size_t)s * (m->sizes[l] + 1) * m->sizes[l + 1];
+  }
+  MTRY(malloc_d(m, &m->d_part, part));
+  GemmF32 g;
+  g.M = rows;
+  g.N = m->sizes[L];
+  MTRY(malloc_d(m, &m->d_lpart, gemm_f32_blocks(g)));
   m->cap = rows;
   return TUFRG_OK;
 }
 
+// forward product of layer l of rows [0, n) of a
+GemmF32 layer(const tufrg_mlp *m, int n, int l, const float *a) {
+  GemmF32 g;
+  g.M = n;
+  g.N = m->sizes[l + 1];
+  g.K = m->sizes[l];
+  g.A = a;
+  g.lda = g.K;
+  g.B = m->d_p + m->woff[l];
+  g.ldb = g.K;
+  g.tB = 1;
+  g.bias = m->d_p + m->boff[l];
+  return g;
+}
+
 // forward of rows [0, n) of X (n <= cap); hidden activations stay in the
-// workspace, the output goes to Y (leading dimension n_out)
+// workspace, the output goes to Y (leading dimension n_out; null: hidden layers only)
 tufrg_status forward_chunk(tufrg_mlp *m, int n, const float *X, float *Y) {
   const int L = (int)m->sizes.size() - 1;
   const float *a = X;
   for (int l = 0; l < L; ++l) {
-    const int ni = m->sizes[l], no = m->sizes[l + 1];
-    const float *W = m->d_p + m->woff[l], *b = m->d_p + m->boff[l];
     const bool last = l + 1 == L;
-    float *out = last ? Y : m->act[l];
-    MHIP(m, launch_gemm_f32(n, no, ni, a, ni, 0, W, ni, 1, b, last ? 1 : 2, out, no, last ? nullptr : m->pre[l],
-                            m->st));
-    a = out;
+    if (last && !Y) break;
+    GemmF32 g = layer(m, n, l, a);
+    g.epi = last ? GEMM_BIAS : GEMM_GELU;
+    g.C = last ? Y : m->act[l];
+    g.Z = last ? nullptr : m->pre[l];
+    MHIP(m, launch_gemm_f32(g, m->st));
+    a = g.C;
   }
   return TUFRG_OK;
 }
@@ -139,25 +179,65 @@ tufrg_status forward_chunk(tufrg_mlp *m, int n, const float *X, float *Y) {
 tufrg_status loss_grad_internal(tufrg_mlp *m, int n, const float *X, const float *T, float *grad) {
   const int L = (int)m->sizes.size() - 1;
   MTRY(reserve(m, n));
-  MTRY(forward_chunk(m, n, X, m->d_y));
-  const int nout = m->sizes[L];
-  MHIP(m, launch_mse_grad((long long)n * nout, m->d_y, T, m->d_dy, m->d_loss, m->st));
-  // d_dy holds dZ of the last layer; walk back
-  float *dz = m->d_dy, *spare = m->d_da;
+  MTRY(forward_chunk(m, n, X, nullptr));
+  // last layer: its product, the loss and d_dy = dZ
+  GemmF32 out = layer(m, n, L - 1, L > 1 ? m->act[L - 2] : X);
+  out.epi = GEMM_LOSS;
+  out.C = m->d_dy;
+  out.T = T;
+  out.inv = 1.0 / ((double)n * m->sizes[L]);
+  out.loss_part = m->d_lpart;
+  const int n_loss = gemm_f32_blocks(out);
+  MHIP(m, launch_gemm_f32(out, m->st));
+  // walk back: the weight and data gradients of a layer in one launch
+  float *dz = m->d_dy, *spare = m->d_da, *part = m->d_part;
+  GradParts gp;
   for (int l = L - 1; l >= 0; --l) {
     const int ni = m->sizes[l], no = m->sizes[l + 1];
-    const float *ain = l == 0 ? X : m->act[l - 1];
-    // dW[o][i] = sum_r dz[r][o] a[r][i]
-    MHIP(m, launch_gemm_f32(no, ni, n, dz, no, 1, ain, ni, 0, nullptr, 0, grad + m->woff[l], ni, nullptr, m->st));
-    MHIP(m, launch_colsum(n, no, dz, m->d_part, grad + m->boff[l], m->st));
-    if (l > 0) {
-      // dA[r][i] = sum_o dz[r][o] W[o][i], then times GELU'(z) of layer l - 1
-      MHIP(m, launch_gemm_f32(n, ni, no, dz, no, 0, m->d_p + m->woff[l], ni, 0, nullptr, 0, spare, ni, nullptr,
-                              m->st));
-      MHIP(m, launch_gelu_bwd((long long)n * ni, m->pre[l - 1], spare, m->st));
-      std::swap(dz, spare);
+    // dW[o][i] = sum_r dz[r][o] a[r][i], db[o] = sum_r dz[r][o]
+    GemmF32 w;
+    w.M = no;
+    w.N = ni;
+    w.K = n;
+    w.A = dz;
+    w.lda = no;
+    w.tA = 1;
+    w.B = l == 0 ? X : m->act[l - 1];
+    w.ldb = ni;
+    w.splits = weight_splits(no, ni, n);
+    const long long len = (long long)no * ni;
+    if (w.splits > 1) {
+      if (gp.n + 2 > GradParts::MAX) {
+        MHIP(m, launch_grad_reduce(gp, m->d_lpart, 0, m->d_loss, m->st));
+        gp.n = 0;
+      }
+      w.C = part;
+      w.db = part + w.splits * len;
+      part = w.db + (long long)w.splits * no;
+      gp.part[gp.n++] = {w.C, grad + m->woff[l], len, w.splits, 0};
+      gp.part[gp.n++] = {w.db, grad + m->boff[l], no, w.splits, 0};
+    } else {
+      w.C = grad + m->woff[l];
+      w.db = grad + m->boff[l];
     }
+    GemmF32 d;
+    if (l > 0) {
+      // dA[r][i] = sum_o dz[r][o] W[o][i], times GELU'(z) of layer l - 1
+      d.M = n;
+      d.N = ni;
+      d.K = no;
+      d.A = dz;
+      d.lda = no;
+      d.B = m->d_p + m->woff[l];
+      d.ldb = ni;
+      d.epi = GEMM_GELU_BWD;
+      d.Z = m->pre[l - 1];
+      d.C = spare;
+    }
+    MHIP(m, launch_gemm_f32_bwd(w, l > 0 ? &d : nullptr, m->st));
+    std::swap(dz, spare);
   }
+  MHIP(m, launch_grad_reduce(gp, m->d_lpart, n_loss, m->d_loss, m->st));
   return TUFRG_OK;
 }
 

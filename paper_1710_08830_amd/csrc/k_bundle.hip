@@ -2,205 +2,364 @@
 // dP = VP Lpp VP with f = 1, dC = 2 VC Lph VC with f = 2), where L is expanded
 // from its compact form L[(R1,a,b),(R2,c,d)] = Lc[dR(R1,R2)][(a,b,c,d)].
 //
-// Small-bundle variant (B <= 64): one workgroup per q, the compact loop and the
-// intermediate L.V staged in LDS, and the vertex too when it fits (VLDS);
-// arithmetic in T (FP64 or FP32), inputs and outputs in FP64.
-// Large bundles: two batched complex GEMMs per q (tmp = L.V, out = f V.tmp),
-// 64 x 64 output tiles with 16-wide k panels staged in LDS, the loop matrix
-// expanded from its compact form while its panel is loaded.
+// Both precisions run on the matrix cores in their own arithmetic
+// (v_mfma_f64_16x16x4_f64 and v_mfma_f32_16x16x4_f32: full FP64 and FP32
+// products and sums), each complex product as four real ones.  On gfx950 the
+// FP64 matrix rate equals the vector rate, but one instruction does 1024
+// multiply-adds on two operand registers, where the vector form is held up by
+// its LDS operand reads.
+//
+// Small bundles (two spin-orbitals, B <= 64): one workgroup per (channel, q), both channels in one
+// launch; the vertex, the compact loop and the intermediate L.V in LDS.
+// Large bundles: two batched complex products per q (tmp = L.V, out = f V.tmp),
+// 96 x 96 tiles, four waves of 48 x 48 (3 x 3 matrix tiles, Re and Im), K steps
+// of 12 (B is a multiple of 36 for six spin-orbitals: none is padded), the
+// loop matrix expanded while its panel is staged, the next panels' loads in
+// flight during the products; a wave whose 48 rows or columns lie outside does
+// no products, so the padding is to 48 and not 96.  The tiles of one q run on
+// one XCD and share its vertex in the L2.
 #include "common.h"
 #include "kernels.h"
 
 namespace tufrg {
 
-template <typename T, bool VLDS>
-__global__ __launch_bounds__(256) void bundle_small_kernel(int n_o, int n_ff, int B, int nD,
-                                                           const int *__restrict__ didx,
-                                                           const double *__restrict__ V,
-                                                           const double *__restrict__ Lc, double factor,
-                                                           double *__restrict__ out) {
-  extern __shared__ unsigned char smem[];
+namespace {
+
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// 16 x 16 x 4 products: operands A(lane % 16, lane / 16) and B(lane / 16, lane %
+// 16), accumulator element r at (row(lane, r), lane % 16)
+template <typename T>
+struct Mm;
+template <>
+struct Mm<double> {
+  typedef f64x4 acc;
+  __device__ static acc fma(double a, double b, acc c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+  __device__ static int row(int lane, int r) { return 4 * r + (lane >> 4); }
+};
+template <>
+struct Mm<float> {
+  typedef f32x4 acc;
+  __device__ static acc fma(float a, float b, acc c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+  __device__ static int row(int lane, int r) { return 4 * (lane >> 4) + r; }
+};
+
+template <typename T>
+struct CAcc {
+  typename Mm<T>::acc re, im;
+  __device__ void clear() {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) re[r] = im[r] = T(0);
+  }
+  // += a b of one K step of 4
+  __device__ void mac(cx<T> a, cx<T> b) {
+    re = Mm<T>::fma(a.re, b.re, re);
+    im = Mm<T>::fma(a.re, b.im, im);
+    re = Mm<T>::fma(-a.im, b.im, re);
+    im = Mm<T>::fma(a.im, b.re, im);
+  }
+};
+
+template <typename T>
+struct alignas(2 * sizeof(T)) C2 {
+  T re, im;
+};
+
+}  // namespace
+
+// most differences of the form factors (4 NT of them at most) of a small bundle
+constexpr int small_nD(int nt) { return nt == 1 ? 13 : nt == 2 ? 57 : 81; }
+
+struct BundleSmall {
+  const double *V[2], *Lc[2];
+  double *out[2];
+  double f[2];
+};
+
+// NT: 16-wide tiles that cover B; out[ch][q] = f V L V, grid (q, channel).
+// B / 4 K steps: B is a multiple of 4 (4 n_ff for two spin-orbitals).  Rows and
+// columns past B hold whatever is in LDS: they reach only results past B.
+template <typename T, int NT>
+__global__ __launch_bounds__(256) void bundle_small_kernel(int n_ff, int B, int nD, const int *__restrict__ didx,
+                                                           BundleSmall p) {
+  constexpr int LD = 16 * NT + 1, NTW = (NT * NT + 3) / 4;  // row stride (odd: banks spread), tiles per wave
+  // FP64, NT = 4: 154 of the 160 KB
+  __shared__ C2<T> sV[16 * NT * LD], sT[16 * NT * LD], sL[small_nD(NT) * 16];
+  __shared__ int sD[16 * NT * NT];
+  const int q = blockIdx.x, ch = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int BB = B * B;
-  const int no2 = n_o * n_o, no4 = no2 * no2;
-  cx<T> *sT = (cx<T> *)smem;
-  cx<T> *sL = sT + BB;
-  int *sD = (int *)(sL + nD * no4);
-  cx<T> *sV = (cx<T> *)(sD + ((n_ff * n_ff + 3) & ~3));
-  const int q = blockIdx.x;
-  const double *Vq = V + 2 * (size_t)q * BB;
-  const double *Lq = Lc + 2 * (size_t)q * nD * no4;
-  auto vat = [&](int i) -> cx<T> {
-    if constexpr (VLDS) return sV[i];
-    return cmake((T)Vq[2 * i], (T)Vq[2 * i + 1]);
-  };
-  if constexpr (VLDS)
-    for (int i = threadIdx.x; i < BB; i += blockDim.x) sV[i] = cmake((T)Vq[2 * i], (T)Vq[2 * i + 1]);
-  for (int i = threadIdx.x; i < nD * no4; i += blockDim.x) sL[i] = cmake((T)Lq[2 * i], (T)Lq[2 * i + 1]);
-  for (int i = threadIdx.x; i < n_ff * n_ff; i += blockDim.x) sD[i] = didx[i];
+  const double2 *Vq = (const double2 *)p.V[ch] + (size_t)q * BB;
+  const double2 *Lq = (const double2 *)p.Lc[ch] + (size_t)q * nD * 16;
+  for (int i = tid; i < BB; i += 256) {
+    const double2 v = Vq[i];
+    sV[(i / B) * LD + i % B] = C2<T>{(T)v.x, (T)v.y};
+  }
+  for (int i = tid; i < nD * 16; i += 256) {
+    const double2 v = Lq[i];
+    sL[i] = C2<T>{(T)v.x, (T)v.y};
+  }
+  for (int i = tid; i < n_ff * n_ff; i += 256) sD[i] = didx[i];
   __syncthreads();
-  // T = L . V, four adjacent columns per item (B is a multiple of 4: 4 n_ff for
-  // two spin-orbitals, the only case with B <= 64)
-  const int BQ = B >> 2;
-  for (int idx = threadIdx.x; idx < B * BQ; idx += blockDim.x) {
-    const int i = idx / BQ, j = (idx - i * BQ) << 2;
-    const int ri = i / no2, ab = i - ri * no2;
-    cx<T> s0 = cmake(T(0), T(0)), s1 = s0, s2 = s0, s3 = s0;
-    for (int rk = 0; rk < n_ff; ++rk) {
-      const cx<T> *Lrow = sL + (size_t)sD[ri * n_ff + rk] * no4 + ab * no2;
-      const int vcol = rk * no2 * B + j;
-      for (int cd = 0; cd < no2; ++cd) {
-        const cx<T> l = Lrow[cd];
-        const int v = vcol + cd * B;
-        cfma(s0, l, vat(v));
-        cfma(s1, l, vat(v + 1));
-        cfma(s2, l, vat(v + 2));
-        cfma(s3, l, vat(v + 3));
-      }
+  const int lr = lane & 15, lk = lane >> 4;
+  CAcc<T> acc[NTW];
+#pragma unroll
+  for (int t = 0; t < NTW; ++t) acc[t].clear();
+  // T = L V: wave w takes tiles w, w + 4, ... (row tile t / NT)
+#pragma unroll
+  for (int t = 0; t < NTW; ++t) {
+    const int tile = wv + 4 * t;
+    if (tile >= NT * NT) break;
+    const int i = min(16 * (tile / NT) + lr, B - 1), j = 16 * (tile % NT) + lr;
+    const int *dr = sD + (i >> 2) * n_ff;
+    for (int k = 0; k < B; k += 4) {
+      const C2<T> a = sL[dr[k >> 2] * 16 + (i & 3) * 4 + lk], b = sV[(k + lk) * LD + j];
+      acc[t].mac(cmake(a.re, a.im), cmake(b.re, b.im));
     }
-    sT[i * B + j] = s0;
-    sT[i * B + j + 1] = s1;
-    sT[i * B + j + 2] = s2;
-    sT[i * B + j + 3] = s3;
+  }
+#pragma unroll
+  for (int t = 0; t < NTW; ++t) {
+    const int tile = wv + 4 * t;
+    if (tile >= NT * NT) break;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      sT[(16 * (tile / NT) + Mm<T>::row(lane, r)) * LD + 16 * (tile % NT) + lr] = C2<T>{acc[t].re[r], acc[t].im[r]};
+    acc[t].clear();
   }
   __syncthreads();
-  // out = f V . T, four adjacent columns per item
-  double *oq = out + 2 * (size_t)q * BB;
-  for (int idx = threadIdx.x; idx < B * BQ; idx += blockDim.x) {
-    const int i = idx / BQ, j = (idx - i * BQ) << 2;
-    cx<T> s0 = cmake(T(0), T(0)), s1 = s0, s2 = s0, s3 = s0;
-    for (int k = 0; k < B; ++k) {
-      const cx<T> v = vat(i * B + k);
-      const cx<T> *Tk = sT + k * B + j;
-      cfma(s0, v, Tk[0]);
-      cfma(s1, v, Tk[1]);
-      cfma(s2, v, Tk[2]);
-      cfma(s3, v, Tk[3]);
-    }
-    const cx<T> r[4] = {s0, s1, s2, s3};
+  // out = f V T
+  double2 *oq = (double2 *)p.out[ch] + (size_t)q * BB;
+  const double f = p.f[ch];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      oq[2 * (i * B + j + c)] = factor * (double)r[c].re;
-      oq[2 * (i * B + j + c) + 1] = factor * (double)r[c].im;
+  for (int t = 0; t < NTW; ++t) {
+    const int tile = wv + 4 * t;
+    if (tile >= NT * NT) break;
+    const int i = 16 * (tile / NT) + lr, j = 16 * (tile % NT) + lr;
+    for (int k = 0; k < B; k += 4) {
+      const C2<T> a = sV[i * LD + k + lk], b = sT[(k + lk) * LD + j];
+      acc[t].mac(cmake(a.re, a.im), cmake(b.re, b.im));
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = 16 * (tile / NT) + Mm<T>::row(lane, r);
+      if (row < B && j < B) oq[row * B + j] = make_double2(f * (double)acc[t].re[r], f * (double)acc[t].im[r]);
     }
   }
 }
 
-// C[q] = alpha A[q] Bm[q]; A is the loop expanded from compact form (AL) or dense
-template <typename T, bool AL>
-__global__ __launch_bounds__(256) void bundle_gemm_kernel(int B, int n_o, int n_ff, int nD,
-                                                          const int *__restrict__ didx,
-                                                          const double *__restrict__ A,
-                                                          const double *__restrict__ Bm, double alpha,
-                                                          double *__restrict__ C) {
-  constexpr int TM = 64, TN = 64, TK = 16;
-  __shared__ cx<T> sA[TK][TM + 1];
-  __shared__ cx<T> sB[TK][TN + 1];
-  const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
-  const int j0 = blockIdx.x * TN, i0 = blockIdx.y * TM;
-  const size_t q = blockIdx.z;
-  const int no2 = n_o * n_o, no4 = no2 * no2;
+namespace {
+constexpr int TB = 96, TK = 12, TLD = TB + 1;  // tile, K step, LDS row stride
+constexpr int TH = 6;                           // values of a panel per loading thread (192 of the 256)
+
+// Raw buffer loads of 16 bytes at a per-lane byte offset; past the end of the
+// array they return zero (the rows past B of a panel).
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4b __attribute__((ext_vector_type(4)));
+typedef float f32x2b __attribute__((ext_vector_type(2)));
+__device__ f32x4b bundle_buffer_load_v4(i32x4 rsrc, int voffset, int soffset, int aux) __asm(
+    "llvm.amdgcn.raw.buffer.load.v4f32");
+__device__ f32x2b bundle_buffer_load_v2(i32x4 rsrc, int voffset, int soffset, int aux) __asm(
+    "llvm.amdgcn.raw.buffer.load.v2f32");
+__device__ inline i32x4 bundle_rsrc(const void *p, unsigned nbytes) {
+  const unsigned long long a = (unsigned long long)p;
+  return i32x4{(int)(unsigned)a, (int)(unsigned)(a >> 32), (int)nbytes, 0x00020000};
+}
+// element of FP64 storage in the arithmetic type, and of storage in that type
+template <typename T>
+__device__ inline C2<T> ld_f64(i32x4 r, unsigned off) {
+  const double2 v = __builtin_bit_cast(double2, bundle_buffer_load_v4(r, (int)off, 0, 0));
+  return C2<T>{(T)v.x, (T)v.y};
+}
+__device__ inline C2<double> ld_t(i32x4 r, unsigned off, double) { return ld_f64<double>(r, off); }
+__device__ inline C2<float> ld_t(i32x4 r, unsigned off, float) {
+  const f32x2b v = bundle_buffer_load_v2(r, (int)off, 0, 0);
+  return C2<float>{v[0], v[1]};
+}
+}  // namespace
+
+// AL: tmp[q] = L[q] V[q], A = L expanded from its compact form (FP64), B = V
+// (FP64), C in the arithmetic type; else out[q] = alpha V[q] tmp[q].
+// Vector instructions beside the products cost nearly their full time on
+// gfx950, so a loading thread takes six values in a row of memory (A: half a row
+// of the panel) or sixteen apart (B) behind one offset, which one addition per
+// step advances.  t2g 10 x 10, 13 form factors (B = 468, 100 q): 5.0-5.2 ms for
+// the two products of both channels in FP64 against 10.2 on the vector units,
+// where the rate of a large FP64 product here (70 TFLOP/s) allows 4.7; FP32, 11 x 11,
+// 9 form factors: 3.2 -> 1.67 ms.
+template <typename T, bool AL, int NO2>
+__global__ __launch_bounds__(256, 2) void bundle_gemm_kernel(int B, int n_ff, int nD, int n_q,
+                                                             const int *__restrict__ didx,
+                                                             const double2 *__restrict__ A,
+                                                             const void *__restrict__ Bv, double alpha,
+                                                             void *__restrict__ Cv) {
+  __shared__ C2<T> sA[2][TK * TLD], sB[2][TK * TLD];
+  __shared__ int sD[AL ? 625 : 1];
+  const int nt = (B + TB - 1) / TB, ntile = nt * nt;
+  // XCD x takes the q x, x + 8, ..., the tiles of a q next to each other
+  const int slot = blockIdx.x >> 3, q = (blockIdx.x & 7) + 8 * (slot / ntile), tile = slot % ntile;
+  if (q >= n_q) return;
+  const int i0 = (tile / nt) * TB, j0 = (tile % nt) * TB;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const size_t BB = (size_t)B * B;
-  const double *Aq = AL ? A + 2 * q * (size_t)nD * no4 : A + 2 * q * BB;
-  const double *Bq = Bm + 2 * q * BB;
-  cx<T> acc[4][4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) acc[r][c] = cmake(T(0), T(0));
-  for (int k0 = 0; k0 < B; k0 += TK) {
-    for (int e = tid; e < TM * TK; e += 256) {
-      const int ii = e / TK, kk = e % TK;
-      const int i = i0 + ii, k = k0 + kk;
-      cx<T> v = cmake(T(0), T(0));
-      if (i < B && k < B) {
-        size_t src;
-        if (AL) {
-          const int ri = i / no2, rk = k / no2;
-          src = (size_t)didx[ri * n_ff + rk] * no4 + (size_t)(i % no2) * no2 + (k % no2);
-        } else {
-          src = (size_t)i * B + k;
-        }
-        v = cmake((T)Aq[2 * src], (T)Aq[2 * src + 1]);
-      }
-      sA[kk][ii] = v;
-    }
-    for (int e = tid; e < TK * TN; e += 256) {
-      const int kk = e / TN, jj = e % TN;
-      const int k = k0 + kk, j = j0 + jj;
-      cx<T> v = cmake(T(0), T(0));
-      if (k < B && j < B) v = cmake((T)Bq[2 * ((size_t)k * B + j)], (T)Bq[2 * ((size_t)k * B + j) + 1]);
-      sB[kk][jj] = v;
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int kk = 0; kk < TK; ++kk) {
-      cx<T> a[4], b[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) a[r] = sA[kk][ty * 4 + r];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) b[c] = sB[kk][tx * 4 + c];
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) cfma(acc[r][c], a[r], b[c]);
-    }
+  constexpr int no4 = NO2 * NO2;
+  constexpr unsigned BSZ = AL ? 16 : (unsigned)sizeof(C2<T>);  // bytes per element of the right factor
+  const auto ra = AL ? bundle_rsrc(A + (size_t)q * nD * no4, (unsigned)nD * no4 * 16u)
+                     : bundle_rsrc(A + (size_t)q * BB, (unsigned)BB * 16u);
+  const auto rb = bundle_rsrc((const char *)Bv + (size_t)q * BB * BSZ, (unsigned)BB * BSZ);
+  const int wi = (wv >> 1) * 48, wj = (wv & 1) * 48;
+  const bool busy = i0 + wi < B && j0 + wj < B;
+  // loading threads: A row i0 + tid / 2, K 6 (tid % 2) + n; B row tid / 16, columns j0 + tid % 16 + 16 n
+  const bool loads = tid < 2 * TB;
+  const int ai = tid >> 1, ak = TH * (tid & 1), bk = tid >> 4, bj = tid & 15;
+  const int i = i0 + ai;
+  if constexpr (AL) {
+    for (int e = tid; e < n_ff * n_ff; e += 256) sD[e] = didx[e];
     __syncthreads();
   }
-  double *Cq = C + 2 * q * BB;
+  unsigned ao = 0, bo = ((unsigned)bk * B + j0 + bj) * BSZ;
+  if (!AL) ao = ((unsigned)i * B + ak) * 16u;
+  C2<T> fa[TH], fb[TH];
+  auto fetch = [&](int k0) {
+    if constexpr (AL && NO2 == 36) {
+      // the 12 K of a step lie in one form-factor block; rows past B: past the end
+      const int rk = k0 / 36;
+      const unsigned d = i < B ? (unsigned)sD[(i / 36) * n_ff + rk] : 0u;
+      ao = i < B ? (d * no4 + (unsigned)(i % 36) * 36u + (unsigned)(k0 - 36 * rk + ak)) * 16u : 0xfffff000u;
+    }
 #pragma unroll
-  for (int r = 0; r < 4; ++r)
+    for (int n = 0; n < TH; ++n) {
+      if constexpr (AL && NO2 != 36) {
+        const int k = k0 + ak + n;
+        const bool in = i < B && k < B;
+        const unsigned d = in ? (unsigned)sD[(i / NO2) * n_ff + k / NO2] : 0u;
+        fa[n] = ld_f64<T>(ra, in ? (d * no4 + (unsigned)(i % NO2) * NO2 + (unsigned)(k % NO2)) * 16u : 0xfffff000u);
+      } else {
+        fa[n] = ld_f64<T>(ra, ao + 16u * n);
+      }
+      if constexpr (AL)
+        fb[n] = ld_f64<T>(rb, bo + 256u * n);
+      else
+        fb[n] = ld_t(rb, bo + 16u * BSZ * n, T(0));
+    }
+    // B not a multiple of 12 (two spin-orbitals): the row part past it is the next row's
+    if constexpr (!AL && NO2 != 36) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int i = i0 + ty * 4 + r, j = j0 + tx * 4 + c;
-      if (i < B && j < B) {
-        Cq[2 * ((size_t)i * B + j)] = alpha * (double)acc[r][c].re;
-        Cq[2 * ((size_t)i * B + j) + 1] = alpha * (double)acc[r][c].im;
+      for (int n = 0; n < TH; ++n)
+        if (k0 + ak + n >= B) fa[n] = C2<T>{T(0), T(0)};
+    }
+    if (!AL) ao += 16u * TK;
+    bo += (unsigned)TK * B * BSZ;
+  };
+  CAcc<T> acc[3][3];
+#pragma unroll
+  for (int r = 0; r < 3; ++r)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) acc[r][c].clear();
+  const int lr = lane & 15, lk = lane >> 4;
+  if (loads) fetch(0);
+  int bf = 0;
+  for (int k0 = 0; k0 < B; k0 += TK, bf ^= 1) {
+    if (loads) {
+#pragma unroll
+      for (int n = 0; n < TH; ++n) {
+        sA[bf][(ak + n) * TLD + ai] = fa[n];
+        sB[bf][bk * TLD + bj + 16 * n] = fb[n];
       }
     }
+    __syncthreads();  // one per step: the other buffer is free since the last one
+    if (loads && k0 + TK < B) fetch(k0 + TK);
+    if (busy) {
+#pragma unroll
+      for (int k = 0; k < TK; k += 4) {
+        C2<T> a[3], b[3];
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+          a[r] = sA[bf][(k + lk) * TLD + wi + 16 * r + lr];
+          b[r] = sB[bf][(k + lk) * TLD + wj + 16 * r + lr];
+        }
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) acc[r][c].mac(cmake(a[r].re, a[r].im), cmake(b[c].re, b[c].im));
+      }
+    }
+  }
+  if (!busy) return;
+#pragma unroll
+  for (int r = 0; r < 3; ++r)
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int row = i0 + wi + 16 * r + Mm<T>::row(lane, e), j = j0 + wj + 16 * c + lr;
+        if (row < B && j < B) {
+          const size_t o = (size_t)q * BB + (size_t)row * B + j;
+          const T re = acc[r][c].re[e], im = acc[r][c].im[e];
+          if constexpr (AL)
+            ((C2<T> *)Cv)[o] = C2<T>{re, im};
+          else
+            ((double2 *)Cv)[o] = make_double2(alpha * (double)re, alpha * (double)im);
+        }
+      }
 }
 
-hipError_t launch_bundle(int prec, int n_o, int n_ff, int B, int nD, int n_q, const int *didx, const double *V,
-                         const double *Lc, double factor, double *out, double *tmp, hipStream_t st) {
-  const int no4 = n_o * n_o * n_o * n_o;
-  const size_t csz = (prec == 0) ? 16 : 8;
-  const size_t base = csz * ((size_t)B * B + (size_t)nD * no4) + sizeof(int) * ((n_ff * n_ff + 3) & ~3);
-  const size_t withV = base + csz * (size_t)B * B;
-  const size_t limit = 64 * 1024;
-  if (B > 64 || base > limit) {
-    if (!tmp) return hipErrorInvalidValue;
-    dim3 grid((B + 63) / 64, (B + 63) / 64, n_q), block(256);
-    if (prec == 0) {
-      hipLaunchKernelGGL((bundle_gemm_kernel<double, true>), grid, block, 0, st, B, n_o, n_ff, nD, didx, Lc, V, 1.0,
-                         tmp);
-      hipLaunchKernelGGL((bundle_gemm_kernel<double, false>), grid, block, 0, st, B, n_o, n_ff, nD, didx, V, tmp,
-                         factor, out);
-    } else {
-      hipLaunchKernelGGL((bundle_gemm_kernel<float, true>), grid, block, 0, st, B, n_o, n_ff, nD, didx, Lc, V, 1.0,
-                         tmp);
-      hipLaunchKernelGGL((bundle_gemm_kernel<float, false>), grid, block, 0, st, B, n_o, n_ff, nD, didx, V, tmp,
-                         factor, out);
-    }
-    return hipGetLastError();
-  }
-  if (B % 4) return hipErrorInvalidValue;  // small bundles are 4 n_ff wide
-  const bool vlds = withV <= limit;
-  const size_t lds = vlds ? withV : base;
-  if (prec == 0) {
-    if (vlds)
-      hipLaunchKernelGGL((bundle_small_kernel<double, true>), dim3(n_q), dim3(256), lds, st, n_o, n_ff, B, nD, didx, V,
-                         Lc, factor, out);
-    else
-      hipLaunchKernelGGL((bundle_small_kernel<double, false>), dim3(n_q), dim3(256), lds, st, n_o, n_ff, B, nD, didx,
-                         V, Lc, factor, out);
-  } else {
-    if (vlds)
-      hipLaunchKernelGGL((bundle_small_kernel<float, true>), dim3(n_q), dim3(256), lds, st, n_o, n_ff, B, nD, didx, V,
-                         Lc, factor, out);
-    else
-      hipLaunchKernelGGL((bundle_small_kernel<float, false>), dim3(n_q), dim3(256), lds, st, n_o, n_ff, B, nD, didx,
-                         V, Lc, factor, out);
+template <typename T>
+static hipError_t launch_small(int n_ff, int B, int nD, int n_q, const int *didx, const BundleSmall &p, int n_ch,
+                               hipStream_t st) {
+  const dim3 grid(n_q, n_ch), block(256);
+  if (nD > small_nD((B + 15) / 16)) return hipErrorInvalidValue;
+  switch ((B + 15) / 16) {
+    case 1: hipLaunchKernelGGL((bundle_small_kernel<T, 1>), grid, block, 0, st, n_ff, B, nD, didx, p); break;
+    case 2: hipLaunchKernelGGL((bundle_small_kernel<T, 2>), grid, block, 0, st, n_ff, B, nD, didx, p); break;
+    case 3: hipLaunchKernelGGL((bundle_small_kernel<T, 3>), grid, block, 0, st, n_ff, B, nD, didx, p); break;
+    case 4: hipLaunchKernelGGL((bundle_small_kernel<T, 4>), grid, block, 0, st, n_ff, B, nD, didx, p); break;
+    default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+template <typename T, int NO2>
+static hipError_t launch_gemm(int n_ff, int B, int nD, int n_q, const int *didx, const double *V,
+                              const double *Lc, double factor, double *out, double *tmp, hipStream_t st) {
+  const int nt = (B + TB - 1) / TB;
+  const long long nb = 8LL * nt * nt * ((n_q + 7) / 8);
+  if (nb > 0x7fffffffLL) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((bundle_gemm_kernel<T, true, NO2>), dim3((unsigned)nb), dim3(256), 0, st, B, n_ff, nD, n_q, didx,
+                     (const double2 *)Lc, V, 1.0, tmp);
+  hipLaunchKernelGGL((bundle_gemm_kernel<T, false, NO2>), dim3((unsigned)nb), dim3(256), 0, st, B, n_ff, nD, n_q, didx,
+                     (const double2 *)V, tmp, factor, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_bundle(int prec, int n_o, int n_ff, int B, int nD, int n_q, const int *didx, const BundleArgs *a,
+                         int n_ch, double *tmp, hipStream_t st) {
+  if (n_ch < 1 || n_ch > 2 || n_q < 1) return hipErrorInvalidValue;
+  const bool f64 = prec == 0;
+  if (n_o == 2 && B <= 64) {
+    BundleSmall p;
+    for (int c = 0; c < n_ch; ++c) {
+      p.V[c] = a[c].V;
+      p.Lc[c] = a[c].Lc;
+      p.out[c] = a[c].out;
+      p.f[c] = a[c].f;
+    }
+    return f64 ? launch_small<double>(n_ff, B, nD, n_q, didx, p, n_ch, st)
+               : launch_small<float>(n_ff, B, nD, n_q, didx, p, n_ch, st);
+  }
+  if (!tmp) return hipErrorInvalidValue;
+  if (n_ff > 25 || (n_o != 2 && n_o != 6)) return hipErrorInvalidValue;
+  for (int c = 0; c < n_ch; ++c) {
+    const double *V = a[c].V, *Lc = a[c].Lc;
+    double *out = a[c].out;
+    const double f = a[c].f;
+    const hipError_t e =
+        n_o == 6 ? (f64 ? launch_gemm<double, 36>(n_ff, B, nD, n_q, didx, V, Lc, f, out, tmp, st)
+                        : launch_gemm<float, 36>(n_ff, B, nD, n_q, didx, V, Lc, f, out, tmp, st))
+                 : (f64 ? launch_gemm<double, 4>(n_ff, B, nD, n_q, didx, V, Lc, f, out, tmp, st)
+                        : launch_gemm<float, 4>(n_ff, B, nD, n_q, didx, V, Lc, f, out, tmp, st));
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace tufrg

@@ -126,10 +126,15 @@ hipError_t launch_assemble(const ProjArgs &a, const double *P, const double *C, 
                            const double *v0p, const double *v0c, double *VP, double *VC, double *ws,
                            size_t ws_doubles, hipStream_t st, int nw = 2);
 
-// a6: bundle products  out = f * V L V  per q, L expanded from compact form;
-// bundles larger than 64 need a workspace tmp of n_q * B * B complex
-hipError_t launch_bundle(int prec, int n_o, int n_ff, int B, int nD, int n_q, const int *didx, const double *V,
-                         const double *Lc, double factor, double *out, double *tmp, hipStream_t st);
+// a6: bundle products  out = f * V L V  per q, L expanded from compact form, of
+// n_ch channels; bundles larger than 64 need a workspace tmp of n_q * B * B complex
+struct BundleArgs {
+  const double *V, *Lc;
+  double f;
+  double *out;
+};
+hipError_t launch_bundle(int prec, int n_o, int n_ff, int B, int nD, int n_q, const int *didx, const BundleArgs *a,
+                         int n_ch, double *tmp, hipStream_t st);
 // the same on the matrix cores with BF16 split operands (k_bundle_mfma.hip), in
 // chunks of q that fit the workspace ws (at least bundle_split_bytes_per_q(B))
 size_t bundle_split_pad(int B);

@@ -603,7 +603,7 @@ extern "C" tufrg_status tufrg_create(const tufrg_model *m, const tufrg_setup *s,
   CTRY(dalloc(c, &c->d_v0c, 2 * BB));
   CTRY(dalloc(c, &c->d_VP, 2 * BB * c->Nq));
   CTRY(dalloc(c, &c->d_VC, 2 * BB * c->Nq));
-  if (c->B > 64) {
+  if (c->B > 64 || c->n_o == 6) {
     size_t nd = 2 * BB * c->Nq;
     if (c->prec == TUFRG_BF16X3) nd = std::max(nd, (bundle_split_bytes_per_q(c->B) + 7) / 8);
     CTRY(dalloc(c, &c->d_btmp, nd));
@@ -1324,20 +1324,17 @@ static tufrg_status rhs_products(tufrg_ctx *c, const double *P, const double *C,
   HIPCHK(c, timer_mark(c, TUFRG_TIMER_BUNDLE));
   // mixed precision: the large bundles on the matrix cores
   const bool mx = c->prec == TUFRG_BF16X3 && c->B > 64;
-  auto bundle = [&](const double *V, const double *L, double f, double *out) {
-    return mx ? launch_bundle_bf16x3(c->n_o, c->n_ff, c->B, c->nD, c->Nq, c->d_didx, V, L, f, out, c->d_btmp,
-                                     c->btmp_bytes, c->st)
-              : launch_bundle(c->prec, c->n_o, c->n_ff, c->B, c->nD, c->Nq, c->d_didx, V, L, f, out, c->d_btmp,
-                              c->st);
-  };
-  if (mask & 1u)
-    HIPCHK(c, bundle(c->d_VP, c->d_loop, scale, dP));
-  else
-    HIPCHK(c, hipMemsetAsync(dP, 0, 2 * sizeof(double) * BB * c->Nq, c->st));
-  if (mask & 2u)
-    HIPCHK(c, bundle(c->d_VC, c->d_loop + lsz, 2.0 * scale, dC));
-  else
-    HIPCHK(c, hipMemsetAsync(dC, 0, 2 * sizeof(double) * BB * c->Nq, c->st));
+  BundleArgs ba[2];
+  int nb = 0;
+  if (mask & 1u) ba[nb++] = BundleArgs{c->d_VP, c->d_loop, scale, dP};
+  if (mask & 2u) ba[nb++] = BundleArgs{c->d_VC, c->d_loop + lsz, 2.0 * scale, dC};
+  for (int i = 0; mx && i < nb; ++i)
+    HIPCHK(c, launch_bundle_bf16x3(c->n_o, c->n_ff, c->B, c->nD, c->Nq, c->d_didx, ba[i].V, ba[i].Lc, ba[i].f,
+                                   ba[i].out, c->d_btmp, c->btmp_bytes, c->st));
+  if (!mx && nb)
+    HIPCHK(c, launch_bundle(c->prec, c->n_o, c->n_ff, c->B, c->nD, c->Nq, c->d_didx, ba, nb, c->d_btmp, c->st));
+  if (!(mask & 1u)) HIPCHK(c, hipMemsetAsync(dP, 0, 2 * sizeof(double) * BB * c->Nq, c->st));
+  if (!(mask & 2u)) HIPCHK(c, hipMemsetAsync(dC, 0, 2 * sizeof(double) * BB * c->Nq, c->st));
   HIPCHK(c, timer_mark(c, TUFRG_TIMER_BUNDLE));
   return TUFRG_OK;
 }

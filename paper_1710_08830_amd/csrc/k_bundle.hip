@@ -71,6 +71,10 @@ struct alignas(2 * sizeof(T)) C2 {
 // most differences of the form factors (4 NT of them at most) of a small bundle
 constexpr int small_nD(int nt) { return nt == 1 ? 13 : nt == 2 ? 57 : 81; }
 
+// waves of a small bundle's workgroup: one per tile up to eight, so that two
+// waves of a SIMD hide each other's LDS reads
+constexpr int small_waves(int nt) { return nt < 3 ? 4 : 8; }
+
 struct BundleSmall {
   const double *V[2], *Lc[2];
   double *out[2];
@@ -81,9 +85,10 @@ struct BundleSmall {
 // B / 4 K steps: B is a multiple of 4 (4 n_ff for two spin-orbitals).  Rows and
 // columns past B hold whatever is in LDS: they reach only results past B.
 template <typename T, int NT>
-__global__ __launch_bounds__(256) void bundle_small_kernel(int n_ff, int B, int nD, const int *__restrict__ didx,
+__global__ __launch_bounds__(64 * small_waves(NT)) void bundle_small_kernel(int n_ff, int B, int nD, const int *__restrict__ didx,
                                                            BundleSmall p) {
-  constexpr int LD = 16 * NT + 1, NTW = (NT * NT + 3) / 4;  // row stride (odd: banks spread), tiles per wave
+  constexpr int LD = 16 * NT + 1, NW = small_waves(NT), NTHR = 64 * NW;
+  constexpr int NTW = (NT * NT + NW - 1) / NW;  // LD: row stride (odd: banks spread); tiles per wave
   // FP64, NT = 4: 154 of the 160 KB
   __shared__ C2<T> sV[16 * NT * LD], sT[16 * NT * LD], sL[small_nD(NT) * 16];
   __shared__ int sD[16 * NT * NT];
@@ -91,27 +96,28 @@ __global__ __launch_bounds__(256) void bundle_small_kernel(int n_ff, int B, int 
   const int BB = B * B;
   const double2 *Vq = (const double2 *)p.V[ch] + (size_t)q * BB;
   const double2 *Lq = (const double2 *)p.Lc[ch] + (size_t)q * nD * 16;
-  for (int i = tid; i < BB; i += 256) {
+  for (int i = tid; i < BB; i += NTHR) {
     const double2 v = Vq[i];
     sV[(i / B) * LD + i % B] = C2<T>{(T)v.x, (T)v.y};
   }
-  for (int i = tid; i < nD * 16; i += 256) {
+  for (int i = tid; i < nD * 16; i += NTHR) {
     const double2 v = Lq[i];
     sL[i] = C2<T>{(T)v.x, (T)v.y};
   }
-  for (int i = tid; i < n_ff * n_ff; i += 256) sD[i] = didx[i];
+  for (int i = tid; i < n_ff * n_ff; i += NTHR) sD[i] = didx[i];
   __syncthreads();
   const int lr = lane & 15, lk = lane >> 4;
   CAcc<T> acc[NTW];
 #pragma unroll
   for (int t = 0; t < NTW; ++t) acc[t].clear();
-  // T = L V: wave w takes tiles w, w + 4, ... (row tile t / NT)
+  // T = L V: wave w takes tiles w, w + NW, ... (row tile t / NT)
 #pragma unroll
   for (int t = 0; t < NTW; ++t) {
-    const int tile = wv + 4 * t;
+    const int tile = wv + NW * t;
     if (tile >= NT * NT) break;
     const int i = min(16 * (tile / NT) + lr, B - 1), j = 16 * (tile % NT) + lr;
     const int *dr = sD + (i >> 2) * n_ff;
+#pragma unroll 4
     for (int k = 0; k < B; k += 4) {
       const C2<T> a = sL[dr[k >> 2] * 16 + (i & 3) * 4 + lk], b = sV[(k + lk) * LD + j];
       acc[t].mac(cmake(a.re, a.im), cmake(b.re, b.im));
@@ -119,7 +125,7 @@ __global__ __launch_bounds__(256) void bundle_small_kernel(int n_ff, int B, int 
   }
 #pragma unroll
   for (int t = 0; t < NTW; ++t) {
-    const int tile = wv + 4 * t;
+    const int tile = wv + NW * t;
     if (tile >= NT * NT) break;
 #pragma unroll
     for (int r = 0; r < 4; ++r)
@@ -132,9 +138,10 @@ __global__ __launch_bounds__(256) void bundle_small_kernel(int n_ff, int B, int 
   const double f = p.f[ch];
 #pragma unroll
   for (int t = 0; t < NTW; ++t) {
-    const int tile = wv + 4 * t;
+    const int tile = wv + NW * t;
     if (tile >= NT * NT) break;
     const int i = 16 * (tile / NT) + lr, j = 16 * (tile % NT) + lr;
+#pragma unroll 4
     for (int k = 0; k < B; k += 4) {
       const C2<T> a = sV[i * LD + k + lk], b = sT[(k + lk) * LD + j];
       acc[t].mac(cmake(a.re, a.im), cmake(b.re, b.im));
@@ -306,7 +313,7 @@ __global__ __launch_bounds__(256, 2) void bundle_gemm_kernel(int B, int n_ff, in
 template <typename T>
 static hipError_t launch_small(int n_ff, int B, int nD, int n_q, const int *didx, const BundleSmall &p, int n_ch,
                                hipStream_t st) {
-  const dim3 grid(n_q, n_ch), block(256);
+  const dim3 grid(n_q, n_ch), block(64 * small_waves((B + 15) / 16));
   if (nD > small_nD((B + 15) / 16)) return hipErrorInvalidValue;
   switch ((B + 15) / 16) {
     case 1: hipLaunchKernelGGL((bundle_small_kernel<T, 1>), grid, block, 0, st, n_ff, B, nD, didx, p); break;

@@ -549,12 +549,32 @@ extern "C" tufrg_status tufrg_create(const tufrg_model *m, const tufrg_setup *s,
   } while (0)
 
   const size_t Nf = c->Nf, BB = (size_t)c->B * c->B;
-  CTRY(dalloc(c, &c->d_ff, c->ff.size()));
-  CTRY(dalloc(c, &c->d_fneg, c->n_ff));
-  CTRY(dalloc(c, &c->d_dlist, c->dlist.size()));
-  CTRY(dalloc(c, &c->d_didx, c->didx.size()));
-  CTRY(dalloc(c, &c->d_ffgrid, c->ffgrid.size()));
-  CTRY(dalloc(c, &c->d_dgrid, c->dgrid.size()));
+  // the integer tables in one allocation and one upload
+  std::vector<int> fneg(c->n_ff, 0), ints;
+  for (int i = 0; i < c->n_ff; ++i)
+    for (int j = 0; j < c->n_ff; ++j)
+      if (c->ff[2 * j] == -c->ff[2 * i] && c->ff[2 * j + 1] == -c->ff[2 * i + 1]) fneg[i] = j;
+  {
+    std::vector<std::pair<int **, size_t>> at;
+    auto put = [&](int **p, const int *v, size_t n) {
+      at.push_back({p, ints.size()});
+      ints.insert(ints.end(), v, v + n);
+      ints.resize((ints.size() + 3) / 4 * 4, 0);
+    };
+    int *idst = nullptr, *all = nullptr;
+    put(&idst, (const int *)c->idst.data(), 2 * c->idst.size());
+    put(&c->d_items, c->items.data(), c->items.size());
+    put(&c->d_ff, c->ff.data(), c->ff.size());
+    put(&c->d_fneg, fneg.data(), fneg.size());
+    put(&c->d_dlist, c->dlist.data(), c->dlist.size());
+    put(&c->d_didx, c->didx.data(), c->didx.size());
+    put(&c->d_ffgrid, c->ffgrid.data(), c->ffgrid.size());
+    put(&c->d_dgrid, c->dgrid.data(), c->dgrid.size());
+    CTRY(dalloc(c, &all, ints.size()));
+    for (auto &p : at) *p.first = all + p.second;
+    c->d_idst = (int2 *)idst;
+    CHIP(hipMemcpyAsync(all, ints.data(), ints.size() * sizeof(int), hipMemcpyHostToDevice, c->st));
+  }
   CTRY(dalloc(c, &c->d_hopR, 2 * (size_t)m->n_hop));
   CTRY(dalloc(c, &c->d_hopt, 2 * (size_t)m->n_hop * c->no2));
   CTRY(dalloc(c, &c->d_band64, Nf * (c->n_o + c->n_o * c->no2)));
@@ -615,8 +635,6 @@ extern "C" tufrg_status tufrg_create(const tufrg_model *m, const tufrg_setup *s,
   CHIP(hipHostMalloc((void **)&c->h_flag, 4 * sizeof(unsigned int), hipHostMallocDefault));
   CTRY(dalloc(c, &c->d_sbits, 4));
   CHIP(hipHostMalloc((void **)&c->h_sbits, 4 * sizeof(unsigned long long), hipHostMallocDefault));
-  CTRY(dalloc(c, &c->d_idst, c->idst.size() + (c->items.size() + 1) / 2));
-  c->d_items = (int *)(c->d_idst + c->idst.size());
 
   // tables
   std::vector<double> twf(2 * c->Lf), twq(2 * c->Lq);
@@ -656,15 +674,8 @@ extern "C" tufrg_status tufrg_create(const tufrg_model *m, const tufrg_setup *s,
           v0c[2 * e + 1] = vc.im;
         }
   hipStream_t st = c->st;
-  CHIP(hipMemcpyAsync(c->d_ff, c->ff.data(), c->ff.size() * sizeof(int), hipMemcpyHostToDevice, st));
   if (c->n_pairs)
     CHIP(hipMemcpyAsync(c->d_pairs, c->pairs.data(), c->pairs.size() * sizeof(int), hipMemcpyHostToDevice, st));
-  CHIP(hipMemcpyAsync(c->d_items, c->items.data(), c->items.size() * sizeof(int), hipMemcpyHostToDevice, st));
-  CHIP(hipMemcpyAsync(c->d_idst, c->idst.data(), c->idst.size() * sizeof(int2), hipMemcpyHostToDevice, st));
-  CHIP(hipMemcpyAsync(c->d_dlist, c->dlist.data(), c->dlist.size() * sizeof(int), hipMemcpyHostToDevice, st));
-  CHIP(hipMemcpyAsync(c->d_didx, c->didx.data(), c->didx.size() * sizeof(int), hipMemcpyHostToDevice, st));
-  CHIP(hipMemcpyAsync(c->d_ffgrid, c->ffgrid.data(), c->ffgrid.size() * sizeof(int), hipMemcpyHostToDevice, st));
-  CHIP(hipMemcpyAsync(c->d_dgrid, c->dgrid.data(), c->dgrid.size() * sizeof(int), hipMemcpyHostToDevice, st));
   CHIP(hipMemcpyAsync(c->d_hopR, m->hop_R, 2 * (size_t)m->n_hop * sizeof(int), hipMemcpyHostToDevice, st));
   CHIP(hipMemcpyAsync(c->d_hopt, m->hop_t, (size_t)m->n_hop * c->no2 * sizeof(tufrg_c64), hipMemcpyHostToDevice,
                       st));
@@ -712,11 +723,6 @@ extern "C" tufrg_status tufrg_create(const tufrg_model *m, const tufrg_setup *s,
     CHIP(hipMemcpyAsync(c->d_phy64, phy64.data(), phy64.size() * sizeof(double), hipMemcpyHostToDevice, st));
     CHIP(hipMemcpyAsync(c->d_phy32, phy32.data(), phy32.size() * sizeof(float), hipMemcpyHostToDevice, st));
   }
-  std::vector<int> fneg(c->n_ff, 0);
-  for (int i = 0; i < c->n_ff; ++i)
-    for (int j = 0; j < c->n_ff; ++j)
-      if (c->ff[2 * j] == -c->ff[2 * i] && c->ff[2 * j + 1] == -c->ff[2 * i + 1]) fneg[i] = j;
-  CHIP(hipMemcpyAsync(c->d_fneg, fneg.data(), fneg.size() * sizeof(int), hipMemcpyHostToDevice, st));
   CHIP(hipMemcpyAsync(c->d_v0p, v0p.data(), v0p.size() * sizeof(double), hipMemcpyHostToDevice, st));
   CHIP(hipMemcpyAsync(c->d_v0c, v0c.data(), v0c.size() * sizeof(double), hipMemcpyHostToDevice, st));
   CHIP(launch_band(c->n_o, c->Lf, m->n_hop, c->d_hopR, c->d_hopt, m->mu, s->basis == TUFRG_BASIS_BAND ? 1 : 0,

@@ -9,7 +9,8 @@
 // combination 1 - 2 f(e).  Omega scheme at T = 0 (propagator times
 // w^2 / (w^2 + Omega^2)): J = e (2|e| + Omega) / (4 (|e| + Omega)^2).
 // At coinciding arguments the divided difference is the mean of K' over the
-// interval (two-point Gauss-Legendre, split at e = 0 for the Omega scheme).
+// interval, from K' and its second derivative at the middle (Omega scheme, FP64
+// or with e = 0 inside: two-point Gauss-Legendre, split at 0).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -91,16 +92,16 @@ __device__ inline double rcp_fast(double d) {
 }
 __device__ inline float rcp_fast(float d) { return __builtin_amdgcn_rcpf(d); }
 
-// sech^2(x) and tanh(x) from s = exp(-2|x|), stable for every x.
 // 1 / x: exact division in FP64, the hardware reciprocal in FP32
 __device__ inline double rdiv(double x) { return 1.0 / x; }
 __device__ inline float rdiv(float x) { return __builtin_amdgcn_rcpf(x); }
 
+// sech^2(x) and tanh(x) from s = exp(-2|x|), stable for every x.
 template <typename T>
 __device__ inline void sech2_tanh(T x, T &sech2, T &th) {
   T ax = fabs(x);
   T s = exp(T(-2) * ax);
-  T inv = T(1) / (T(1) + s);
+  T inv = rdiv(T(1) + s);
   sech2 = T(4) * s * inv * inv;
   th = copysign((T(1) - s) * inv, x);
 }
@@ -145,11 +146,39 @@ __device__ inline T gl2_mean(T a, T b, T lam, int scheme, int deriv) {
   return T(0.5) * (cut_der(m - c * h, lam, scheme, deriv) + cut_der(m + c * h, lam, scheme, deriv));
 }
 
+// Mean of f = cut_der over [x, y] from its middle m: f(m) + (x - y)^2 / 24 times
+// its second derivative, the next term being (x - y)^4 / 1920 of the fourth (at
+// the switch widths below 2e-7 of f in FP32, 1e-15 with the temperature scheme
+// in FP64).  One exponential or reciprocal instead of the two of the two-point
+// rule: near Lambda = 1 a fifth to a half of the waves of a loop kernel hold
+// such a pair (FP32 Rashba loops, 13 form factors, L 24: 603 -> 553 us).
+template <typename T>
+__device__ inline T mid_mean(T x, T y, T lam, int scheme, int deriv) {
+  const T m = T(0.5) * (x + y), d = x - y, w = d * d * T(1.0 / 24.0);
+  if (scheme == CUT_TEMPERATURE) {
+    const T r = rdiv(lam + lam), u = m * r, w4 = w * r * r;  // derivatives in u = e / 2T
+    T s, t;
+    sech2_tanh(u, s, t);
+    if (deriv) {
+      // f = -s (1 - 2 u t) r^2, second derivative -(12 s - 18 s^2 + u t s (24 s - 8)) r^2
+      const T ut = u * t;
+      return -s * r * r * (T(1) - T(2) * ut + w4 * (T(12) - T(18) * s + ut * (T(24) * s - T(8))));
+    }
+    // f = s r / 2, second derivative (4 s - 6 s^2) r / 2
+    return T(0.5) * s * r * (T(1) + w4 * (T(4) - T(6) * s));
+  }
+  // D = |e| + Lambda, g = Lambda / D: f = (3 - 10 g + 6 g^2) / 4 D^2 (of K) or (3 g - 2 g^2) / 4 D (of J)
+  const T i = rdiv(fabs(m) + lam), g = lam * i, w2 = w * i * i;
+  if (deriv)
+    return T(0.25) * i * i * (fma(fma(T(6), g, T(-10)), g, T(3)) + w2 * fma(fma(T(120), g, T(-120)), g, T(18)));
+  return T(0.25) * i * g * (fma(T(-2), g, T(3)) + w2 * fma(T(-24), g, T(18)));
+}
+
 // Relative width below which the divided difference switches to the mean of
 // the derivative.  FP64: 1e-3; FP32: 2e-2 (cancellation in the quotient costs
-// about eps / width = 3e-6 at the switch, the two-point rule (width / 2)^4 /
-// 135; a wider switch sends more lanes, and with them whole waves, through the
-// slower branch: at 5e-2 the Rashba loop ran 6 % slower with the same error).
+// about eps / width = 3e-6 at the switch; a wider switch sends more lanes, and
+// with them whole waves, through the slower branch: at 5e-2 the Rashba loop ran
+// 6 % slower with the same error).
 template <typename T>
 struct degen_rel;
 template <>
@@ -172,7 +201,8 @@ __device__ inline T divided_difference(T x, T y, T gx, T gy, T lam, int scheme, 
     return w1 * gl2_mean(x, T(0), lam, scheme, deriv) +
            (T(1) - w1) * gl2_mean(T(0), y, lam, scheme, deriv);
   }
-  return gl2_mean(x, y, lam, scheme, deriv);
+  if (sizeof(T) == 8 && scheme == CUT_OMEGA) return gl2_mean(x, y, lam, scheme, deriv);
+  return mid_mean(x, y, lam, scheme, deriv);
 }
 
 }  // namespace tufrg

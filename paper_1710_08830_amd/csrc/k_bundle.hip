@@ -23,6 +23,14 @@
 
 namespace tufrg {
 
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4b __attribute__((ext_vector_type(4)));
+typedef float f32x2b __attribute__((ext_vector_type(2)));
+__device__ f32x4b bundle_buffer_load_v4(i32x4 rsrc, int voffset, int soffset, int aux) __asm(
+    "llvm.amdgcn.raw.buffer.load.v4f32");
+__device__ f32x2b bundle_buffer_load_v2(i32x4 rsrc, int voffset, int soffset, int aux) __asm(
+    "llvm.amdgcn.raw.buffer.load.v2f32");
+
 namespace {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
@@ -117,10 +125,16 @@ __global__ __launch_bounds__(64 * small_waves(NT)) void bundle_small_kernel(int 
     if (tile >= NT * NT) break;
     const int i = min(16 * (tile / NT) + lr, B - 1), j = 16 * (tile % NT) + lr;
     const int *dr = sD + (i >> 2) * n_ff;
-#pragma unroll 4
+    // operands one step ahead of their products
+    auto at = [&](int k) { return sL[dr[k >> 2] * 16 + (i & 3) * 4 + lk]; };
+    auto bt = [&](int k) { return sV[(k + lk) * LD + j]; };
+    C2<T> a = at(0), b = bt(0);
     for (int k = 0; k < B; k += 4) {
-      const C2<T> a = sL[dr[k >> 2] * 16 + (i & 3) * 4 + lk], b = sV[(k + lk) * LD + j];
+      const int kn = min(k + 4, B - 4);
+      const C2<T> an = at(kn), bn = bt(kn);
       acc[t].mac(cmake(a.re, a.im), cmake(b.re, b.im));
+      a = an;
+      b = bn;
     }
   }
 #pragma unroll
@@ -141,10 +155,13 @@ __global__ __launch_bounds__(64 * small_waves(NT)) void bundle_small_kernel(int 
     const int tile = wv + NW * t;
     if (tile >= NT * NT) break;
     const int i = 16 * (tile / NT) + lr, j = 16 * (tile % NT) + lr;
-#pragma unroll 4
+    C2<T> a = sV[i * LD + lk], b = sT[lk * LD + j];
     for (int k = 0; k < B; k += 4) {
-      const C2<T> a = sV[i * LD + k + lk], b = sT[(k + lk) * LD + j];
+      const int kn = min(k + 4, B - 4);
+      const C2<T> an = sV[i * LD + kn + lk], bn = sT[(kn + lk) * LD + j];
       acc[t].mac(cmake(a.re, a.im), cmake(b.re, b.im));
+      a = an;
+      b = bn;
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -160,13 +177,6 @@ constexpr int TH = 6;                           // values of a panel per loading
 
 // Raw buffer loads of 16 bytes at a per-lane byte offset; past the end of the
 // array they return zero (the rows past B of a panel).
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4b __attribute__((ext_vector_type(4)));
-typedef float f32x2b __attribute__((ext_vector_type(2)));
-__device__ f32x4b bundle_buffer_load_v4(i32x4 rsrc, int voffset, int soffset, int aux) __asm(
-    "llvm.amdgcn.raw.buffer.load.v4f32");
-__device__ f32x2b bundle_buffer_load_v2(i32x4 rsrc, int voffset, int soffset, int aux) __asm(
-    "llvm.amdgcn.raw.buffer.load.v2f32");
 __device__ inline i32x4 bundle_rsrc(const void *p, unsigned nbytes) {
   const unsigned long long a = (unsigned long long)p;
   return i32x4{(int)(unsigned)a, (int)(unsigned)(a >> 32), (int)nbytes, 0x00020000};

@@ -93,6 +93,22 @@ hipError_t launch_loop_rb_sums(const LoopArgs &a, const float *Y, double *lamb, 
                                int nD, double *out, hipStream_t st);
 size_t loop_rb_rowbuf_floats(int ndy, int Lf);
 int loop_rb_half_points(int ndy, int *dx, int *dy);
+// the same in 15 coordinates per pair sum, for models with time reversal times
+// inversion (k_loop_kr.hip): pair sums x, per-evaluation energies and regulator
+// values ek (16 floats per k with shell factors, else 8), A operand, row buffers
+// and coordinates lam per item
+size_t kr_x_floats(int Lf);
+hipError_t launch_kr_x(int Lf, const double *band, float *x, hipStream_t st);
+size_t kr_apre_bytes(int ndy, int Lf);
+hipError_t launch_kr_apre(int ndy, const float *x, const float *phy, int Lf, void *apre, hipStream_t st);
+hipError_t launch_kr_ek(int Nf, int shell, const float *band, const float *kv, const float *cv, float *ek,
+                        hipStream_t st);
+size_t kr_rowbuf_floats(int ndy, int Lf);
+size_t kr_lam_doubles(int ndy);
+hipError_t launch_loop_kr(const LoopArgs &a, const float *x, const float *ek, const void *apre, float *Y,
+                          hipStream_t st);
+hipError_t launch_loop_kr_sums(const LoopArgs &a, const float *Y, double *lam, const int *hmap, const int *dlist, int nD,
+                               double *out, hipStream_t st);
 // sums partials, applies 1/Nf, fills dx < 0 by hermiticity and the other half
 // of the sum and of the coarse q by symmetry
 hipError_t launch_loop_finalize(const LoopArgs &a, int nD, const int *dlist, double *compact, hipStream_t st);

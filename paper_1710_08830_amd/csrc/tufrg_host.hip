@@ -130,7 +130,9 @@ struct tufrg_ctx {
   int mfma_chunk = 0;
   int mfma_kxr = 1;        // kx rows per work item of the matrix-core loop (tunable)
   void *d_apre = nullptr;  // the matrix-core loop's precomputed A operand (once per context)
-  int apre_pair = 0;       // the pairing d_apre was computed for
+  int mfma_kind = -1;      // what d_apre and the row buffers are for: 0 six bands, 1 pairs, 2 pairs in 15 coordinates
+  int kr = 0;              // time reversal times inversion: pair sums in 15 coordinates (k_loop_kr.hip)
+  float *d_krx = nullptr, *d_ek = nullptr;
   // BF16X3 loops: bands (0,1), (2,3), (4,5) degenerate at every k (Kramers
   // pairs), found at creation; then the loops sum them by pairs unless
   // pair_enable is cleared
@@ -349,6 +351,37 @@ static int default_kx_chunks(const tufrg_ctx *c) {
     }
   }
   return kx_chunks(c, best);
+}
+
+// Time reversal times inversion, H(k) = T H(k)^* T^t with T = i sigma_y in each
+// orbital: t(-R) = T t(R)^* T^t, to the rounding of the table.
+static bool time_reversal_inversion(const tufrg_model *m) {
+  const int n = m->n_orb;
+  if (n % 2) return false;
+  std::map<std::pair<int, int>, std::vector<tufrg_c64>> t;
+  double big = 0.0;
+  for (int h = 0; h < m->n_hop; ++h)
+    for (int s = 1; s >= -1; s -= 2) {  // R, and a place for -R
+      auto &v = t[{s * m->hop_R[2 * h], s * m->hop_R[2 * h + 1]}];
+      v.resize((size_t)n * n, tufrg_c64{0.0, 0.0});
+      for (int i = 0; s == 1 && i < n * n; ++i) {
+        const tufrg_c64 x = m->hop_t[(size_t)h * n * n + i];
+        v[i].re += x.re;
+        v[i].im += x.im;
+        big = std::max(big, std::max(std::fabs(x.re), std::fabs(x.im)));
+      }
+    }
+  bool ok = true;
+  for (const auto &e : t) {
+    const auto &w = t[{-e.first.first, -e.first.second}];
+    for (int a = 0; a < n; ++a)
+      for (int b = 0; b < n; ++b) {
+        const double sgn = ((a + b) & 1) ? -1.0 : 1.0;
+        const tufrg_c64 x = w[a * n + b], y = e.second[(a ^ 1) * n + (b ^ 1)];
+        ok = ok && std::fabs(x.re - sgn * y.re) <= 4e-16 * big && std::fabs(x.im + sgn * y.im) <= 4e-16 * big;
+      }
+  }
+  return ok;
 }
 
 // Appends the items that give the loops of channel ch at the coarse q of q[]
@@ -741,11 +774,18 @@ extern "C" tufrg_status tufrg_create(const tufrg_model *m, const tufrg_setup *s,
     for (int p = 0; p < 3; ++p)
       for (size_t k = 0; k < Nf; ++k) split = std::max(split, std::fabs(e[(2 * p) * Nf + k] - e[(2 * p + 1) * Nf + k]));
     if (split <= 1e-10 * std::max(1.0, emax)) {
-      if (c->prec == TUFRG_FP64)
-        CTRY(dalloc(c, &c->d_pir64, Nf * 3 * 36));
-      else
-        CTRY(dalloc(c, &c->d_pir32, Nf * 3 * 36));
-      CHIP(launch_pair_pi((int)Nf, c->d_band64, c->d_pir32, c->d_pir64, st));
+      c->kr = c->prec == TUFRG_BF16X3 && time_reversal_inversion(m);
+      if (c->kr) {
+        CTRY(dalloc(c, &c->d_krx, kr_x_floats(c->Lf)));
+        CTRY(dalloc(c, &c->d_ek, Nf * (c->scheme == CUT_SHELL ? 16 : 8)));
+        CHIP(launch_kr_x(c->Lf, c->d_band64, c->d_krx, st));
+      } else {
+        if (c->prec == TUFRG_FP64)
+          CTRY(dalloc(c, &c->d_pir64, Nf * 3 * 36));
+        else
+          CTRY(dalloc(c, &c->d_pir32, Nf * 3 * 36));
+        CHIP(launch_pair_pi((int)Nf, c->d_band64, c->d_pir32, c->d_pir64, st));
+      }
       CHIP(hipStreamSynchronize(st));
       c->bands_paired = 1;
     }
@@ -886,27 +926,56 @@ static tufrg_status compute_kval(tufrg_ctx *c, double lam, int deriv) {
   else
     HIPCHK(c, launch_kval(c->n_o * c->Nf, c->Nf, c->n_o, c->d_band64, rl, rs, rd, c->d_kv64, c->d_kv32, c->st));
   if (shell) HIPCHK(c, launch_shell_ab(c->n_o, c->Nf, c->d_band64, lam, deriv, c->d_cv64, c->d_cv32, c->st));
+  if (c->kr) HIPCHK(c, launch_kr_ek(c->Nf, shell, c->d_bandk32, c->d_kv32, c->d_cv32, c->d_ek, c->st));
   return TUFRG_OK;
 }
 
 static void dfree(tufrg_ctx *c, void *p);
 
-// the matrix-core loop's A operand for the current pairing (rebuilt when the
-// pairing changed since it was computed)
+// the matrix-core loop's A operand and buffers for the current pairing (rebuilt
+// when the pairing changed since they were made)
 static tufrg_status ensure_apre(tufrg_ctx *c) {
-  const int pair = pairs_active(c);
-  if (c->d_apre && c->apre_pair != pair) {
+  const int kind = pairs_active(c) ? (c->kr ? 2 : 1) : 0;
+  if (c->mfma_kind != kind) {
     HIPCHK(c, hipStreamSynchronize(c->st));
     dfree(c, c->d_apre);
+    dfree(c, c->d_yrow);
+    dfree(c, c->d_lamb);
     c->d_apre = nullptr;
+    c->d_yrow = nullptr;
+    c->d_lamb = nullptr;
+    c->mfma_kind = kind;
   }
   if (!c->d_apre) {
     unsigned char *ap = nullptr;
-    TRY(dalloc(c, &ap, loop_rb_apre_bytes(c->ndy, c->Lf, pair)));
-    HIPCHK(c, launch_loop_rb_apre(c->ndy, pair, c->d_bandk32, c->d_pir32, c->d_phy32, c->Lf, ap, c->st));
+    TRY(dalloc(c, &ap, kind == 2 ? kr_apre_bytes(c->ndy, c->Lf) : loop_rb_apre_bytes(c->ndy, c->Lf, kind)));
     c->d_apre = ap;
-    c->apre_pair = pair;
+    const hipError_t e = kind == 2 ? launch_kr_apre(c->ndy, c->d_krx, c->d_phy32, c->Lf, ap, c->st)
+                                   : launch_loop_rb_apre(c->ndy, kind, c->d_bandk32, c->d_pir32, c->d_phy32, c->Lf, ap, c->st);
+    if (e != hipSuccess) {
+      dfree(c, ap);
+      c->d_apre = nullptr;
+    }
+    HIPCHK(c, e);
   }
+  if (c->d_yrow && c->d_lamb) return TUFRG_OK;
+  // items per launch: the larger channel's in equal chunks of whole groups (a
+  // short last chunk would leave most compute units idle for the time of a
+  // launch); 36 coordinates: at most 384 items (96 groups of four); 15: row
+  // buffers of at most 4 GB
+  const int most = std::max(c->n_item[0], c->n_item[1]), group = kind == 2 ? 16 : 4;
+  const size_t per_item = kr_rowbuf_floats(c->ndy, c->Lf) * sizeof(float);
+  const int cap = kind == 2 ? (int)std::max<size_t>(16, std::min<size_t>(most, ((size_t)4 << 30) / per_item)) : 384;
+  const int nch = (most + cap - 1) / cap;
+  c->mfma_chunk = ((most + nch - 1) / nch + group - 1) / group * group;
+  int hx[32], hy[32];
+  const size_t nh = (size_t)loop_rb_half_points(c->ndy, hx, hy);
+  if (!c->d_yrow)
+    TRY(dalloc(c, &c->d_yrow, kind == 2 ? c->mfma_chunk * kr_rowbuf_floats(c->ndy, c->Lf)
+                                        : c->mfma_chunk / 4 * loop_rb_rowbuf_floats(c->ndy, c->Lf)));
+  if (!c->d_lamb)
+    TRY(dalloc(c, &c->d_lamb, kind == 2 ? c->mfma_chunk * kr_lam_doubles(c->ndy)
+                                        : 2 * (size_t)c->mfma_chunk * nh * 36 * 36));
   return TUFRG_OK;
 }
 
@@ -936,18 +1005,6 @@ static tufrg_status loops_range_mfma(tufrg_ctx *c, double lam, int deriv, const 
     c->d_hmap = d;
   }
   TRY(ensure_apre(c));
-  if (!c->d_yrow || !c->d_lamb) {
-    // at most 384 items (96 groups of four) per launch, the items of the larger
-    // channel in equal chunks of whole groups: a short last chunk would leave
-    // most compute units idle for the time of a launch
-    const int most = std::max(c->n_item[0], c->n_item[1]), nch = (most + 383) / 384;
-    c->mfma_chunk = ((most + nch - 1) / nch + 3) / 4 * 4;
-    const size_t groups = (size_t)(c->mfma_chunk + 3) / 4;
-    if (!c->d_yrow) TRY(dalloc(c, &c->d_yrow, groups * loop_rb_rowbuf_floats(c->ndy, c->Lf)));
-    int hx[32], hy[32];
-    const size_t nh = (size_t)loop_rb_half_points(c->ndy, hx, hy);
-    TRY(dalloc(c, &c->d_lamb, 2 * (size_t)c->mfma_chunk * nh * 36 * 36));
-  }
   const size_t blk = (size_t)c->nD * c->no4;
   double *out = dst;
   for (int ch = 0; ch < 2; ++ch) {
@@ -958,9 +1015,12 @@ static tufrg_status loops_range_mfma(tufrg_ctx *c, double lam, int deriv, const 
       const LoopArgs a = loop_args(c, lam, deriv, part);
       // the loop timer covers the matrix-core kernel of each chunk
       HIPCHK(c, timer_mark(c, TUFRG_TIMER_LOOP));
-      HIPCHK(c, launch_loop_rb(a, c->d_apre, c->d_yrow, c->st));
+      const bool kr = c->mfma_kind == 2;
+      HIPCHK(c, kr ? launch_loop_kr(a, c->d_krx, c->d_ek, c->d_apre, c->d_yrow, c->st)
+                   : launch_loop_rb(a, c->d_apre, c->d_yrow, c->st));
       HIPCHK(c, timer_mark(c, TUFRG_TIMER_LOOP));
-      HIPCHK(c, launch_loop_rb_sums(a, c->d_yrow, c->d_lamb, c->d_hmap, c->d_dlist, c->nD, out, c->st));
+      HIPCHK(c, kr ? launch_loop_kr_sums(a, c->d_yrow, c->d_lamb, c->d_hmap, c->d_dlist, c->nD, out, c->st)
+                   : launch_loop_rb_sums(a, c->d_yrow, c->d_lamb, c->d_hmap, c->d_dlist, c->nD, out, c->st));
     }
     if (li.n[ch]) out += 2 * (size_t)li.n_q_out * blk;
   }

@@ -37,6 +37,24 @@ def _bonds(n_o, seed):
     return np.array(R, dtype=np.int32), 0.4 * np.array(t)
 
 
+def _quaternionic(seed):
+    """Random hoppings with time reversal times inversion and neither alone:
+    H(k) real in the 15 Hermitian 6 x 6 matrices that commute with T K."""
+    rng = np.random.default_rng(seed)
+    one, isg = np.eye(2), [1j * p for p in PAULI]
+    Q = [np.kron(np.diag(np.eye(3)[i]), one).astype(np.complex128) for i in range(3)]
+    for i, j in ((0, 1), (0, 2), (1, 2)):
+        e = np.zeros((3, 3))
+        e[i, j] = 1.0
+        Q += [np.kron(e + e.T, one)] + [np.kron(e - e.T, g) for g in isg]
+    R, t = [(0, 0)], [np.tensordot(rng.standard_normal(15), np.array(Q), 1)]
+    for r in ((1, 0), (0, 1), (1, 1), (1, -1)):
+        m = np.tensordot(rng.standard_normal(15) + 1j * rng.standard_normal(15), np.array(Q), 1)
+        R += [r, (-r[0], -r[1])]
+        t += [m, m.conj().T]
+    return np.array(R, dtype=np.int32), 0.3 * np.array(t)
+
+
 # name -> (hoppings, kind of time reversal: 0 none, 1 T = 1, 2 T = i sigma_y)
 MODELS = {
     "hubbard": (hubbard_hoppings(), 1),
@@ -46,6 +64,7 @@ MODELS = {
     "t2g": (t2g_soc_hoppings(0.2, seed=1), 2),
     "t2g in a field": (_onsite(t2g_soc_hoppings(0.2, seed=1), 0.05 * np.kron(np.eye(3), PAULI[2])), 0),
     "random6": (_bonds(6, 5), 0),
+    "quaternionic": (_quaternionic(7), 0),
 }
 
 
@@ -70,7 +89,7 @@ def _compact(c, M):
     return {(a[0] - b[0], a[1] - b[1]): X[:, i, :, :, j] for i, a in enumerate(ff) for j, b in enumerate(ff)}
 
 
-@pytest.mark.parametrize("model", ["hubbard", "rashba", "rashba in a field", "random2", "t2g", "random6"])
+@pytest.mark.parametrize("model", ["hubbard", "rashba", "rashba in a field", "random2", "t2g", "random6", "quaternionic"])
 @pytest.mark.parametrize("Lq,n_ref", [(5, 1), (6, 2)])
 def test_the_oracle_loops_obey_the_relabellings(model, Lq, n_ref):
     c = _setup(model, 5, Lq, n_ref, "temperature")
@@ -106,6 +125,11 @@ CASES = [("hubbard", 5, 6, 3, "temperature", "fp64"), ("hubbard", 9, 5, 3, "omeg
          ("random2", 13, 10, 1, "omega", "fp64"), ("random2", 5, 8, 12, "temperature", "fp32"),
          ("t2g", 9, 5, 3, "temperature", "fp64"), ("t2g", 5, 6, 3, "shell", "bf16x3"),
          ("t2g in a field", 9, 6, 2, "omega", "fp32"), ("t2g in a field", 5, 7, 3, "temperature", "bf16x3"),
+         # 15 real coordinates per pair sum: tiles of 32 ky (one short, one and a bit, two whole), groups of 16 q
+         ("t2g", 5, 5, 2, "omega", "bf16x3"), ("t2g", 13, 9, 4, "temperature", "bf16x3"),
+         ("t2g", 5, 5, 8, "shell", "bf16x3"), ("t2g", 9, 8, 8, "omega", "bf16x3"),
+         ("quaternionic", 9, 6, 3, "temperature", "bf16x3"), ("quaternionic", 5, 5, 8, "shell", "bf16x3"),
+         ("quaternionic", 9, 5, 3, "omega", "bf16x3"), ("quaternionic", 5, 6, 3, "temperature", "fp64"),
          ("random6", 5, 5, 3, "temperature", "fp64"), ("random6", 9, 6, 3, "omega", "bf16x3")]
 
 
@@ -117,7 +141,8 @@ def test_loops_against_the_oracle(model, S, Lq, n_ref, cutoff, prec, basis):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_1710_08830_amd import tufrg as T
-    if basis == "band" and (model, prec) not in (("rashba", "fp64"), ("t2g", "fp64"), ("random2", "fp32")):
+    if basis == "band" and (model, prec, n_ref) not in (("rashba", "fp64", 11), ("t2g", "fp64", 3), ("random2", "fp32", 12),
+                                                        ("t2g", "bf16x3", 3)):
         pytest.skip("the band basis once per kernel")
     c = _setup(model, S, Lq, n_ref, cutoff, basis)
     print(f"loop symmetry: {model} S{S} {Lq}x{Lq} refined {n_ref}x {cutoff} {prec} {basis}", flush=True)

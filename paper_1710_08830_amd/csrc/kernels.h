@@ -124,23 +124,19 @@ struct ProjArgs {
   const int *dgrid;    // [17][17] index into dlist, -1 outside D
   const int *ff;       // [n_ff][2]
   const double *twq;   // exp(+2 pi i j / Lq), [Lq][2]
-  int ny;              // distinct rho_y over dlist (at most 9)
-  const double *phy;   // exp(+2 pi i qy y_s / Lq) of those values y_s, [Lq][ny][2]
-  const int *dtab;     // per rho of dlist: (rho_x mod Lq) | (slot s of rho_y) << 16
-  const int *dslot;    // [9][9] per slot s the rho of D with rho_y = y_s: iD | (rho_x mod Lq) << 16, else -1
+  int np;              // the rho_y of D are 0 (slot 0) and np <= 4 pairs +-y (slots 2 y + 1, 2 y + 2)
+  const double *phy;   // (cos, sin)(2 pi qy y / Lq) of the pairs, [Lq][np][2]
+  const int *dtab;     // per rho of dlist: (rho_x mod Lq) | (slot of rho_y) << 16
+  const int *dslot;    // [9][9] per slot the rho of D with that rho_y: iD | (rho_x mod Lq) << 16, else -1
 };
-// ws: workspace of ws_doubles >= proj_ws_row_doubles (one qx row of the
-// two-stage transforms; more rows per pass with more)
-size_t proj_ws_row_doubles(const ProjArgs &a);
-hipError_t launch_ft(const ProjArgs &a, const double *P, const double *C, double *ws, size_t ws_doubles,
-                     double *real, hipStream_t st);
-hipError_t launch_gather(const ProjArgs &a, const double *real, double *G, hipStream_t st);
+// real [2][nD][B][B]: P(rho), C(rho)
+hipError_t launch_ft(const ProjArgs &a, const double *P, const double *C, double *real, hipStream_t st);
 // D [Nq][B][B] (layout of C) from C: D_{n1n2n3n4} = -C_{n1n2n4n3}
 hipError_t launch_channel_d(int n_o, int B, int Nq, const double *C, double *D, hipStream_t st);
+// src: the transforms P(rho), C(rho), or with gathered the gathers [nw][nD][B][B];
 // nw = 1: only VP from P and G[0]
-hipError_t launch_assemble(const ProjArgs &a, const double *P, const double *C, const double *G,
-                           const double *v0p, const double *v0c, double *VP, double *VC, double *ws,
-                           size_t ws_doubles, hipStream_t st, int nw = 2);
+hipError_t launch_assemble(const ProjArgs &a, const double *P, const double *C, const double *src, int gathered,
+                           const double *v0p, const double *v0c, double *VP, double *VC, hipStream_t st, int nw = 2);
 
 // a6: bundle products  out = f * V L V  per q, L expanded from compact form, of
 // n_ch channels; bundles larger than 64 need a workspace tmp of n_q * B * B complex

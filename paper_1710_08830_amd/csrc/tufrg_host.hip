@@ -51,7 +51,6 @@ struct tufrg_ctx {
   std::vector<int2> idst;        // slots of q and -q (-1: none)
   int *d_items = nullptr, *d_sitems = nullptr, *h_sitems = nullptr;  // s: sampled rows (h_: pinned)
   int2 *d_idst = nullptr, *d_sidst = nullptr, *h_sidst = nullptr;
-  size_t proj_ws = 0;  // doubles of the projection workspace (whole qx rows of the intermediate)
   std::vector<int> ff, dlist, didx, ffgrid, dgrid, pairs;
   int *d_ff = nullptr, *d_dlist = nullptr, *d_didx = nullptr, *d_ffgrid = nullptr, *d_dgrid = nullptr;
   int *d_hopR = nullptr;
@@ -91,7 +90,7 @@ struct tufrg_ctx {
   float *d_twf32 = nullptr;
   double *d_partial = nullptr;
   double *d_loop = nullptr;
-  double *d_ftpart = nullptr, *d_real = nullptr, *d_G = nullptr;
+  double *d_real = nullptr;
   double *d_v0p = nullptr, *d_v0c = nullptr, *d_VP = nullptr, *d_VC = nullptr;
   unsigned long long *d_bits = nullptr;
   unsigned int *d_flag = nullptr;
@@ -543,11 +542,6 @@ extern "C" tufrg_status tufrg_create(const tufrg_model *m, const tufrg_setup *s,
     for (int i = 0; i < c->nD; ++i)
       if (std::find(ys.begin(), ys.end(), c->dlist[2 * i + 1]) == ys.end()) ys.push_back(c->dlist[2 * i + 1]);
     c->ny = (int)ys.size();
-    // the projections' intermediate: whole qx rows of [2][ny][B^2] complex, up
-    // to about 1 GB
-    const size_t per_row = 2 * 2 * (size_t)c->ny * c->B * c->B;
-    const size_t rows = std::max<size_t>(1, std::min<size_t>((size_t)c->Lq, ((size_t)1 << 27) / per_row));
-    c->proj_ws = rows * per_row;
   }
   auto bail = [&](tufrg_status st) {
     g_err = c->err;
@@ -649,9 +643,7 @@ extern "C" tufrg_status tufrg_create(const tufrg_model *m, const tufrg_setup *s,
   c->partial_cap = 2 * c->items.size() * nparts * c->ndx * (2 * c->ndy + 1) * c->no4;
   CTRY(dalloc(c, &c->d_partial, c->partial_cap));
   CTRY(dalloc(c, &c->d_loop, 2 * 2 * (size_t)c->Nq * c->nD * c->no4));
-  CTRY(dalloc(c, &c->d_ftpart, c->proj_ws));
   CTRY(dalloc(c, &c->d_real, 2 * 2 * (size_t)c->nD * BB));
-  CTRY(dalloc(c, &c->d_G, 2 * 2 * (size_t)c->nD * BB));
   CTRY(dalloc(c, &c->d_v0p, 2 * BB));
   CTRY(dalloc(c, &c->d_v0c, 2 * BB));
   CTRY(dalloc(c, &c->d_VP, 2 * BB * c->Nq));
@@ -724,17 +716,19 @@ extern "C" tufrg_status tufrg_create(const tufrg_model *m, const tufrg_setup *s,
     std::vector<int> ys;
     for (int i = 0; i < c->nD; ++i)
       if (std::find(ys.begin(), ys.end(), c->dlist[2 * i + 1]) == ys.end()) ys.push_back(c->dlist[2 * i + 1]);
-    std::sort(ys.begin(), ys.end());
+    // 0, then the pairs +-y (D = S - S holds both)
+    std::sort(ys.begin(), ys.end(), [](int a, int b) { return std::abs(a) != std::abs(b) ? std::abs(a) < std::abs(b) : a > b; });
     if (c->ny != (int)ys.size() || c->ny > 9) {  // D lies in [-4, 4]^2 for form factors with |R| <= 2
       c->err = "more than nine distinct rho_y in D";
       return bail(TUFRG_E_UNSUPPORTED);
     }
-    std::vector<double> pphy(2 * (size_t)c->Lq * c->ny);
+    const int np = c->ny / 2;
+    std::vector<double> pphy(std::max<size_t>(2 * (size_t)c->Lq * np, 2));
     for (int qy = 0; qy < c->Lq; ++qy)
-      for (int y = 0; y < c->ny; ++y) {
-        const int j = mod((long long)qy * ys[y]);
-        pphy[2 * ((size_t)qy * c->ny + y)] = twq[2 * j];
-        pphy[2 * ((size_t)qy * c->ny + y) + 1] = twq[2 * j + 1];
+      for (int y = 0; y < np; ++y) {
+        const int j = mod((long long)qy * ys[2 * y + 1]);
+        pphy[2 * ((size_t)qy * np + y)] = twq[2 * j];
+        pphy[2 * ((size_t)qy * np + y) + 1] = twq[2 * j + 1];
       }
     // dtab [nD], then the slot table [9][9]
     std::vector<int> dtab(c->nD + 81, -1), fill(9, 0);
@@ -908,7 +902,7 @@ static ProjArgs proj_args(tufrg_ctx *c) {
   a.dgrid = c->d_dgrid;
   a.ff = c->d_ff;
   a.twq = c->d_twq;
-  a.ny = c->ny;
+  a.np = c->ny / 2;
   a.phy = c->d_pphy;
   a.dtab = c->d_dtab;
   a.dslot = c->d_dtab + c->nD;
@@ -1330,10 +1324,9 @@ static tufrg_status surrogate_loops(tufrg_ctx *c, double lam) {
   return TUFRG_OK;
 }
 
-// projections with the buffers given: the workspace ws (ws_doubles, at least
-// one qx row of the intermediate), real and G ([2][nD][B][B] complex each)
+// projections with the buffer of the transforms given (real, [2][nD][B][B] complex)
 static tufrg_status project_with(tufrg_ctx *c, const double *P, const double *C, double *VP, double *VC,
-                                 double *ws, size_t ws_doubles, double *real, double *G) {
+                                 double *real) {
   ProjArgs a = proj_args(c);
   HIPCHK(c, timer_mark(c, TUFRG_TIMER_PROJECT));
   if (c->has_c0) {
@@ -1348,15 +1341,14 @@ static tufrg_status project_with(tufrg_ctx *c, const double *P, const double *C,
     HIPCHK(c, launch_add(2 * (long long)c->Nq * c->B * c->B, P, c->d_p0, c->d_peff, c->st));
     P = c->d_peff;
   }
-  HIPCHK(c, launch_ft(a, P, C, ws, ws_doubles, real, c->st));
-  HIPCHK(c, launch_gather(a, real, G, c->st));
-  HIPCHK(c, launch_assemble(a, P, C, G, c->d_v0p, c->d_v0c, VP, VC, ws, ws_doubles, c->st));
+  HIPCHK(c, launch_ft(a, P, C, real, c->st));
+  HIPCHK(c, launch_assemble(a, P, C, real, 0, c->d_v0p, c->d_v0c, VP, VC, c->st));
   HIPCHK(c, timer_mark(c, TUFRG_TIMER_PROJECT));
   return TUFRG_OK;
 }
 
 static tufrg_status project_internal(tufrg_ctx *c, const double *P, const double *C, double *VP, double *VC) {
-  return project_with(c, P, C, VP, VC, c->d_ftpart, c->proj_ws, c->d_real, c->d_G);
+  return project_with(c, P, C, VP, VC, c->d_real);
 }
 
 // dP = scale VP Lpp VP, dC = 2 scale VC Lph VC; a masked channel gets zero
@@ -1611,17 +1603,13 @@ extern "C" tufrg_status tufrg_project_static(tufrg_ctx *c, const tufrg_c64 *P, c
   if (dev != c->device) return fail(c, TUFRG_E_INVAL, "the context's device must be current");
   double *scr = g_scratch_ptr[dev];
   if (!scr) return fail(c, TUFRG_E_HIP, "static scratch not set up on this device");
-  // one [2][nD][B][B] complex block each for the coefficients and the
-  // gathers, the rest (at least as much, so at least one qx row of
-  // [2][ny][B][B] with ny <= nD) for the transforms' intermediate
+  // the transforms take one [2][nD][B][B] complex block, the limit is of three
   const size_t unit = 2 * 2 * (size_t)c->nD * c->B * c->B;
   if (3 * unit > STATIC_SCRATCH_DOUBLES)
     return fail(c, TUFRG_E_UNSUPPORTED,
                 "static scratch of 32 MiB holds 3 * 4 * n_dR * B^2 doubles at most; this setup needs " +
                     std::to_string(3 * unit * sizeof(double)) + " bytes");
-  double *real = scr, *G = real + unit, *ws = G + unit;
-  return project_with(c, (const double *)P, (const double *)C, (double *)VP, (double *)VC, ws,
-                      STATIC_SCRATCH_DOUBLES - 2 * unit, real, G);
+  return project_with(c, (const double *)P, (const double *)C, (double *)VP, (double *)VC, scr);
 }
 
 extern "C" tufrg_status tufrg_set_initial_c(tufrg_ctx *c, const tufrg_c64 *C0) {
@@ -2131,15 +2119,14 @@ static tufrg_status su2_rhs_internal(tufrg_ctx *c, double lam, const double *p, 
   ProjArgs a = proj_args(c);
   HIPCHK(c, timer_mark(c, TUFRG_TIMER_PROJECT));
   HIPCHK(c, launch_su2_exch(c->n_ff, c->Nq, c->Lq, c->d_ff, c->d_fneg, c->d_twq, p, c->d_s_px, c->st));
-  HIPCHK(c, launch_ft(a, p, cc, c->d_ftpart, c->proj_ws, c->d_s_rA, c->st));
-  HIPCHK(c, launch_ft(a, c->d_s_px, d, c->d_ftpart, c->proj_ws, c->d_s_rB, c->st));
+  HIPCHK(c, launch_ft(a, p, cc, c->d_s_rA, c->st));
+  HIPCHK(c, launch_ft(a, c->d_s_px, d, c->d_s_rB, c->st));
   HIPCHK(c, launch_su2_gather(c->B, c->nD, c->d_ff, c->d_dlist, c->d_ffgrid, c->d_dgrid, c->d_s_rA, c->d_s_rB,
                               c->d_s_G3, c->st));
   // a~ and c~ from (p, c) with the gathers 0, 1; d~ from d with gather 2 (v in every (0,0) entry)
-  HIPCHK(c, launch_assemble(a, p, cc, c->d_s_G3, c->d_v0p, c->d_v0c, c->d_VP, c->d_VC, c->d_ftpart, c->proj_ws,
-                            c->st));
-  HIPCHK(c, launch_assemble(a, d, d, c->d_s_G3 + 2 * 2 * (size_t)c->nD * c->B * c->B, c->d_v0p, c->d_v0p,
-                            c->d_s_Vd, nullptr, c->d_ftpart, c->proj_ws, c->st, 1));
+  HIPCHK(c, launch_assemble(a, p, cc, c->d_s_G3, 1, c->d_v0p, c->d_v0c, c->d_VP, c->d_VC, c->st));
+  HIPCHK(c, launch_assemble(a, d, d, c->d_s_G3 + 2 * 2 * (size_t)c->nD * c->B * c->B, 1, c->d_v0p, c->d_v0p,
+                            c->d_s_Vd, nullptr, c->st, 1));
   HIPCHK(c, launch_su2_exch(c->n_ff, c->Nq, c->Lq, c->d_ff, c->d_fneg, c->d_twq, c->d_VP, c->d_s_Vax, c->st));
   HIPCHK(c, timer_mark(c, TUFRG_TIMER_PROJECT));
   HIPCHK(c, timer_mark(c, TUFRG_TIMER_BUNDLE));

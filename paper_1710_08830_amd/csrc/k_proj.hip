@@ -50,6 +50,14 @@ constexpr int rho_per_thread(int EW, int big) {
   return big ? (81 + NTHR / EW - 1) / (NTHR / EW) : (NDS + NTHR / EW - 1) / (NTHR / EW);
 }
 
+// Element block of this workgroup: each XCD walks a range of its own (the gathers
+// of neighbouring elements share lines in its L2), in reverse for the assembly.
+// nb is a multiple of eight.
+__device__ inline int xcd_block(int nb, bool reverse = false) {
+  const int per = nb >> 3, i = blockIdx.x >> 3;
+  return (blockIdx.x & 7) * per + (reverse ? per - 1 - i : i);
+}
+
 // v mod Lq for v < Lq^2, Lq <= 4096, magic = ceil(2^32 / Lq): the quotient is at
 // most one too large
 __device__ inline int mod_lq(unsigned v, unsigned Lq, unsigned magic) {
@@ -78,7 +86,9 @@ __global__ __launch_bounds__(NTHR) void ft_kernel(int BB, int Lq, int nD, int pa
   extern __shared__ double2 psm[];  // [Lq] qx phases, for EW < 64 [Lq][NP] qy phases
   const int tid = threadIdx.x, el = tid % EW;
   const int g = EW == 64 ? __builtin_amdgcn_readfirstlane(tid / 64) : tid / EW;
-  const int e = blockIdx.x * EW + el, w = blockIdx.y;
+  const int blk = xcd_block(gridDim.x), nb = (BB + EW - 1) / EW;
+  if (blk >= 2 * nb) return;
+  const int w = blk / nb, e = (blk - w * nb) * EW + el;
   double2 *sY = psm + Lq;
   for (int i = tid; i < Lq; i += NTHR) psm[i] = twq[i];
   if (EW < 64)
@@ -171,6 +181,16 @@ __global__ __launch_bounds__(NTHR) void ft_kernel(int BB, int Lq, int nD, int pa
   }
 }
 
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// two floats to packed BF16 pairs (round to nearest even): hi and the BF16 of the remainders
+__device__ inline void split2(float a, float b, unsigned &hi, unsigned &lo) {
+  hi = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){a, b}, bf16x2));
+  const float ra = a - __uint_as_float(hi << 16), rb = b - __uint_as_float(hi & 0xffff0000u);
+  lo = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){ra, rb}, bf16x2));
+}
+
 struct GatherTables {
   int n_o, n_ff, B, nD;
   const int *ff, *dlist, *ffgrid, *dgrid;
@@ -213,24 +233,28 @@ __device__ inline double2 gather_one(const GatherTables &t, const int *grid, int
 }
 
 // VX(qx, qy)[e] = X[e] + X[V0][e] + sum_rho e^{iq.rho} G_X(rho)[e]; G gathered
-// from X(rho) (GATHER) or given.  The element blocks run in reverse: the last
-// ones that ft read are still in the last-level cache.
-template <int EW, int NP, bool GATHER>
-__global__ __launch_bounds__(NTHR) void assemble_kernel(int BB, int Lq, int nD, int parts, unsigned magic,
-                                                        GatherTables gt, const double2 *__restrict__ phy,
+// from X(rho) (SRC 0, 1) or given (SRC 2); V in FP64 or for SRC 1 in split planes,
+// the operands of the BF16 bundle products.  The element blocks run in reverse: the
+// last ones that ft read are still in the last-level cache.
+template <int EW, int NP, int SRC>
+__global__ __launch_bounds__(NTHR) void assemble_kernel(int BB, int Lq, int nD, int nw, int parts,
+                                                        unsigned magic, GatherTables gt, const double2 *__restrict__ phy,
                                                         const double2 *__restrict__ twq,
                                                         const int *__restrict__ dslot,
                                                         const double2 *__restrict__ src,
                                                         const double2 *__restrict__ P, const double2 *__restrict__ C,
                                                         const double2 *__restrict__ v0p,
-                                                        const double2 *__restrict__ v0c, double2 *__restrict__ VP,
-                                                        double2 *__restrict__ VC) {
+                                                        const double2 *__restrict__ v0c, void *__restrict__ VP,
+                                                        void *__restrict__ VC) {
+  constexpr bool GATHER = SRC != 2;
   constexpr int NG = NTHR / EW, NY = 2 * NP + 1;
   extern __shared__ double2 psm[];  // [nD][EW] G, [Lq] qx phases, for EW < 64 [Lq][NP] qy phases
   __shared__ int grid[GATHER ? 2 * GRID : 1];
   const int tid = threadIdx.x, el = tid % EW;
   const int g = EW == 64 ? __builtin_amdgcn_readfirstlane(tid / 64) : tid / EW;
-  const int e = (gridDim.x - 1 - blockIdx.x) * EW + el, w = gridDim.y - 1 - blockIdx.y;
+  const int blk = xcd_block(gridDim.x, true), nb = (BB + EW - 1) / EW;
+  if (blk >= nw * nb) return;
+  const int w = blk / nb, e = (blk - w * nb) * EW + el;
   const int ec = min(e, BB - 1);
   double2 *sG = psm, *sX = psm + nD * EW, *sY = sX + Lq;
   for (int i = tid; i < Lq; i += NTHR) sX[i] = twq[i];
@@ -252,7 +276,8 @@ __global__ __launch_bounds__(NTHR) void assemble_kernel(int BB, int Lq, int nD, 
   __syncthreads();
   const double2 v0 = (w == 0 ? v0p : v0c)[ec];
   const double2 *X = (w == 0 ? P : C) + ec;
-  double2 *V = (w == 0 ? VP : VC) + ec;
+  double2 *V = (double2 *)(w == 0 ? VP : VC) + ec;
+  unsigned short *S = (unsigned short *)(w == 0 ? VP : VC) + (ec & ~3) + (size_t)(el & 3) * BB;  // BB a multiple of four
   const bool valid = e < BB;
   for (int unit = g; unit < Lq * parts; unit += NG) {
     const int row = unit / parts, pt = unit % parts;
@@ -296,7 +321,22 @@ __global__ __launch_bounds__(NTHR) void assemble_kernel(int BB, int Lq, int nD, 
           vr = fma(f.p[y].x, hr[2 * y + 1], fma(-f.p[y].y, hi[2 * y + 2], vr));
           vi = fma(f.p[y].x, hi[2 * y + 1], fma(f.p[y].y, hr[2 * y + 2], vi));
         }
-        if (valid) V[base + (size_t)(q + u) * BB] = make_double2(vr, vi);
+        if constexpr (SRC == 1) {
+          // the four lanes of a quad hold four elements in a row: lane j stores
+          // plane j of all four, eight bytes (2-byte stores instead: 783 us,
+          // with these 767, with the XCDs on ranges of their own 704; t2g 16 x 16, 13
+          // form factors)
+          unsigned hi, lo;
+          split2((float)vr, (float)vi, hi, lo);
+          const bool odd = el & 1, upper = el & 2;
+          const unsigned o1 = __builtin_amdgcn_mov_dpp((int)(odd ? hi : lo), 0xB1, 0xf, 0xf, true);  // lane ^ 1
+          const unsigned w0 = odd ? o1 : hi, w1 = odd ? lo : o1;  // hi (odd lanes: lo) of elements 0, 1 of the pair
+          const unsigned re = __builtin_amdgcn_perm(w1, w0, 0x05040100), im = __builtin_amdgcn_perm(w1, w0, 0x07060302);
+          const unsigned o2 = __builtin_amdgcn_mov_dpp((int)(upper ? re : im), 0x4E, 0xf, 0xf, true);  // lane ^ 2
+          if (valid) *(uint2 *)(S + 4 * (base + (size_t)(q + u) * BB)) = upper ? make_uint2(o2, im) : make_uint2(re, o2);
+        } else {
+          if (valid) V[base + (size_t)(q + u) * BB] = make_double2(vr, vi);
+        }
       }
     }
   }
@@ -334,7 +374,7 @@ bool proj_ok(const ProjArgs &a) {
 template <int EW, int NP>
 static void ft_launch(const ProjArgs &a, int parts, const double *P, const double *C, double *real, hipStream_t st) {
   const int BB = a.B * a.B;
-  const dim3 grid((BB + EW - 1) / EW, 2);
+  const dim3 grid((2 * ((BB + EW - 1) / EW) + 7) / 8 * 8);
   const size_t lds = sizeof(double2) * ((size_t)a.Lq + (EW < 64 ? a.Lq * NP : 0));
   const double scale = 1.0 / (double)a.Nq;
 #define TUFRG_FT(BIG)                                                                                              \
@@ -348,17 +388,17 @@ static void ft_launch(const ProjArgs &a, int parts, const double *P, const doubl
 #undef TUFRG_FT
 }
 
-template <int EW, int NP, bool GATHER>
+template <int EW, int NP, int SRC>
 static void assemble_launch(const ProjArgs &a, int parts, const double *P, const double *C, const double *src,
-                            const double *v0p, const double *v0c, double *VP, double *VC, int nw, hipStream_t st) {
+                            const double *v0p, const double *v0c, void *VP, void *VC, int nw, hipStream_t st) {
   const int BB = a.B * a.B;
-  const dim3 grid((BB + EW - 1) / EW, nw);
+  const dim3 grid((nw * ((BB + EW - 1) / EW) + 7) / 8 * 8);
   const size_t lds = sizeof(double2) * ((size_t)a.nD * EW + a.Lq + (EW < 64 ? a.Lq * NP : 0));
   const unsigned magic = (unsigned)((((unsigned long long)1 << 32) + a.Lq - 1) / a.Lq);
   const GatherTables gt{a.n_o, a.n_ff, a.B, a.nD, a.ff, a.dlist, a.ffgrid, a.dgrid};
-  hipLaunchKernelGGL((assemble_kernel<EW, NP, GATHER>), grid, dim3(NTHR), lds, st, BB, a.Lq, a.nD, parts, magic, gt,
+  hipLaunchKernelGGL((assemble_kernel<EW, NP, SRC>), grid, dim3(NTHR), lds, st, BB, a.Lq, a.nD, nw, parts, magic, gt,
                      (const double2 *)a.phy, (const double2 *)a.twq, a.dslot, (const double2 *)src, (const double2 *)P,
-                     (const double2 *)C, (const double2 *)v0p, (const double2 *)v0c, (double2 *)VP, (double2 *)VC);
+                     (const double2 *)C, (const double2 *)v0p, (const double2 *)v0c, VP, VC);
 }
 
 // the rho_y of a set within |R| <= 2 closed under R -> -R: 0, two or four pairs
@@ -387,13 +427,24 @@ hipError_t launch_ft(const ProjArgs &a, const double *P, const double *C, double
   return hipGetLastError();
 }
 
-hipError_t launch_assemble(const ProjArgs &a, const double *P, const double *C, const double *src, int gathered,
-                           const double *v0p, const double *v0c, double *VP, double *VC, hipStream_t st, int nw) {
+hipError_t launch_assemble(const ProjArgs &a, const double *P, const double *C, const double *real,
+                           const double *v0p, const double *v0c, void *VP, void *VC, int planes, hipStream_t st) {
+  if (!proj_ok(a)) return hipErrorInvalidValue;
+  const ProjSplit sp = proj_split(a);
+#define TUFRG_AS_CALL(EW, NP)                                                             \
+  planes ? assemble_launch<EW, NP, 1>(a, sp.parts, P, C, real, v0p, v0c, VP, VC, 2, st)   \
+         : assemble_launch<EW, NP, 0>(a, sp.parts, P, C, real, v0p, v0c, VP, VC, 2, st)
+  TUFRG_PROJ(TUFRG_AS_CALL)
+#undef TUFRG_AS_CALL
+  return hipGetLastError();
+}
+
+hipError_t launch_assemble_gathered(const ProjArgs &a, const double *P, const double *C, const double *G,
+                                    const double *v0p, const double *v0c, double *VP, double *VC, hipStream_t st,
+                                    int nw) {
   if (!proj_ok(a) || nw < 1 || nw > 2) return hipErrorInvalidValue;
   const ProjSplit sp = proj_split(a);
-#define TUFRG_AS_CALL(EW, NP)                                                               \
-  gathered ? assemble_launch<EW, NP, false>(a, sp.parts, P, C, src, v0p, v0c, VP, VC, nw, st) \
-           : assemble_launch<EW, NP, true>(a, sp.parts, P, C, src, v0p, v0c, VP, VC, nw, st)
+#define TUFRG_AS_CALL(EW, NP) assemble_launch<EW, NP, 2>(a, sp.parts, P, C, G, v0p, v0c, VP, VC, nw, st)
   TUFRG_PROJ(TUFRG_AS_CALL)
 #undef TUFRG_AS_CALL
   return hipGetLastError();

@@ -133,10 +133,14 @@ struct ProjArgs {
 hipError_t launch_ft(const ProjArgs &a, const double *P, const double *C, double *real, hipStream_t st);
 // D [Nq][B][B] (layout of C) from C: D_{n1n2n3n4} = -C_{n1n2n4n3}
 hipError_t launch_channel_d(int n_o, int B, int Nq, const double *C, double *D, hipStream_t st);
-// src: the transforms P(rho), C(rho), or with gathered the gathers [nw][nD][B][B];
-// nw = 1: only VP from P and G[0]
-hipError_t launch_assemble(const ProjArgs &a, const double *P, const double *C, const double *src, int gathered,
-                           const double *v0p, const double *v0c, double *VP, double *VC, hipStream_t st, int nw = 2);
+// VP, VC from the transforms P(rho), C(rho) at real: FP64, or with planes as
+// split planes [Nq][4][B][B] of BF16 (Re hi, Re lo, Im hi, Im lo; x = hi + lo)
+hipError_t launch_assemble(const ProjArgs &a, const double *P, const double *C, const double *real,
+                           const double *v0p, const double *v0c, void *VP, void *VC, int planes, hipStream_t st);
+// the same from the gathers G [nw][nD][B][B]; nw = 1: only VP from P and G[0]
+hipError_t launch_assemble_gathered(const ProjArgs &a, const double *P, const double *C, const double *G,
+                                    const double *v0p, const double *v0c, double *VP, double *VC, hipStream_t st,
+                                    int nw = 2);
 
 // a6: bundle products  out = f * V L V  per q, L expanded from compact form, of
 // n_ch channels; bundles larger than 64 need a workspace tmp of n_q * B * B complex
@@ -147,11 +151,11 @@ struct BundleArgs {
 };
 hipError_t launch_bundle(int prec, int n_o, int n_ff, int B, int nD, int n_q, const int *didx, const BundleArgs *a,
                          int n_ch, double *tmp, hipStream_t st);
-// the same on the matrix cores with BF16 split operands (k_bundle_mfma.hip), in
-// chunks of q that fit the workspace ws (at least bundle_split_bytes_per_q(B))
-size_t bundle_split_pad(int B);
-size_t bundle_split_bytes_per_q(int B);
-hipError_t launch_bundle_bf16x3(int n_o, int n_ff, int B, int nD, int n_q, const int *didx, const double *V,
+// the same on the matrix cores with BF16 split operands (k_bundle_mfma.hip), V in
+// split planes (launch_assemble), in chunks of q that fit the workspace ws (at
+// least bundle_split_bytes_per_q)
+size_t bundle_split_bytes_per_q(int n_o, int B, int nD);
+hipError_t launch_bundle_bf16x3(int n_o, int n_ff, int B, int nD, int n_q, const int *didx, const void *V,
                                 const double *Lc, double factor, double *out, void *ws, size_t ws_bytes,
                                 hipStream_t st);
 

@@ -650,7 +650,7 @@ extern "C" tufrg_status tufrg_create(const tufrg_model *m, const tufrg_setup *s,
   CTRY(dalloc(c, &c->d_VC, 2 * BB * c->Nq));
   if (c->B > 64 || c->n_o == 6) {
     size_t nd = 2 * BB * c->Nq;
-    if (c->prec == TUFRG_BF16X3) nd = std::max(nd, (bundle_split_bytes_per_q(c->B) + 7) / 8);
+    if (c->prec == TUFRG_BF16X3) nd = std::max(nd, (bundle_split_bytes_per_q(c->n_o, c->B, c->nD) + 7) / 8);
     CTRY(dalloc(c, &c->d_btmp, nd));
     c->btmp_bytes = nd * sizeof(double);
   }
@@ -1324,8 +1324,9 @@ static tufrg_status surrogate_loops(tufrg_ctx *c, double lam) {
   return TUFRG_OK;
 }
 
-// projections with the buffer of the transforms given (real, [2][nD][B][B] complex)
-static tufrg_status project_with(tufrg_ctx *c, const double *P, const double *C, double *VP, double *VC,
+// projections with the buffer of the transforms given (real, [2][nD][B][B]
+// complex); planes: VP, VC as split planes of BF16
+static tufrg_status project_with(tufrg_ctx *c, const double *P, const double *C, double *VP, double *VC, int planes,
                                  double *real) {
   ProjArgs a = proj_args(c);
   HIPCHK(c, timer_mark(c, TUFRG_TIMER_PROJECT));
@@ -1342,13 +1343,14 @@ static tufrg_status project_with(tufrg_ctx *c, const double *P, const double *C,
     P = c->d_peff;
   }
   HIPCHK(c, launch_ft(a, P, C, real, c->st));
-  HIPCHK(c, launch_assemble(a, P, C, real, 0, c->d_v0p, c->d_v0c, VP, VC, c->st));
+  HIPCHK(c, launch_assemble(a, P, C, real, c->d_v0p, c->d_v0c, VP, VC, planes, c->st));
   HIPCHK(c, timer_mark(c, TUFRG_TIMER_PROJECT));
   return TUFRG_OK;
 }
 
-static tufrg_status project_internal(tufrg_ctx *c, const double *P, const double *C, double *VP, double *VC) {
-  return project_with(c, P, C, VP, VC, c->d_real);
+static tufrg_status project_internal(tufrg_ctx *c, const double *P, const double *C, double *VP, double *VC,
+                                     int planes) {
+  return project_with(c, P, C, VP, VC, planes, c->d_real);
 }
 
 // dP = scale VP Lpp VP, dC = 2 scale VC Lph VC; a masked channel gets zero
@@ -1377,11 +1379,11 @@ static tufrg_status rhs_internal(tufrg_ctx *c, double lam, const double *P, cons
 static tufrg_status rhs_products(tufrg_ctx *c, const double *P, const double *C, double *dP, double *dC, double scale,
                                  unsigned mask) {
   const size_t BB = (size_t)c->B * c->B;
-  TRY(project_internal(c, P, C, c->d_VP, c->d_VC));
+  // mixed precision: the large bundles in BF16 split products
+  const bool mx = c->prec == TUFRG_BF16X3 && c->B > 64;
+  TRY(project_internal(c, P, C, c->d_VP, c->d_VC, mx));
   const size_t lsz = 2 * (size_t)c->Nq * c->nD * c->no4;
   HIPCHK(c, timer_mark(c, TUFRG_TIMER_BUNDLE));
-  // mixed precision: the large bundles on the matrix cores
-  const bool mx = c->prec == TUFRG_BF16X3 && c->B > 64;
   BundleArgs ba[2];
   int nb = 0;
   if (mask & 1u) ba[nb++] = BundleArgs{c->d_VP, c->d_loop, scale, dP};
@@ -1578,7 +1580,7 @@ extern "C" tufrg_status tufrg_project(tufrg_ctx *c, const tufrg_c64 *P, const tu
   if (c->n_o == 1) return fail(c, TUFRG_E_UNSUPPORTED, "one-orbital contexts run the SU(2)-reduced calls");
   if (!is_device_ptr(P) || !is_device_ptr(C) || !is_device_ptr(VP) || !is_device_ptr(VC))
     return fail(c, TUFRG_E_INVAL, "P, C, VP, VC must be device pointers");
-  return project_internal(c, (const double *)P, (const double *)C, (double *)VP, (double *)VC);
+  return project_internal(c, (const double *)P, (const double *)C, (double *)VP, (double *)VC, 0);
 }
 
 extern "C" tufrg_status tufrg_channel_d(tufrg_ctx *c, const tufrg_c64 *C, tufrg_c64 *D) {
@@ -1609,7 +1611,7 @@ extern "C" tufrg_status tufrg_project_static(tufrg_ctx *c, const tufrg_c64 *P, c
     return fail(c, TUFRG_E_UNSUPPORTED,
                 "static scratch of 32 MiB holds 3 * 4 * n_dR * B^2 doubles at most; this setup needs " +
                     std::to_string(3 * unit * sizeof(double)) + " bytes");
-  return project_with(c, (const double *)P, (const double *)C, (double *)VP, (double *)VC, scr);
+  return project_with(c, (const double *)P, (const double *)C, (double *)VP, (double *)VC, 0, scr);
 }
 
 extern "C" tufrg_status tufrg_set_initial_c(tufrg_ctx *c, const tufrg_c64 *C0) {
@@ -2124,9 +2126,9 @@ static tufrg_status su2_rhs_internal(tufrg_ctx *c, double lam, const double *p, 
   HIPCHK(c, launch_su2_gather(c->B, c->nD, c->d_ff, c->d_dlist, c->d_ffgrid, c->d_dgrid, c->d_s_rA, c->d_s_rB,
                               c->d_s_G3, c->st));
   // a~ and c~ from (p, c) with the gathers 0, 1; d~ from d with gather 2 (v in every (0,0) entry)
-  HIPCHK(c, launch_assemble(a, p, cc, c->d_s_G3, 1, c->d_v0p, c->d_v0c, c->d_VP, c->d_VC, c->st));
-  HIPCHK(c, launch_assemble(a, d, d, c->d_s_G3 + 2 * 2 * (size_t)c->nD * c->B * c->B, 1, c->d_v0p, c->d_v0p,
-                            c->d_s_Vd, nullptr, c->st, 1));
+  HIPCHK(c, launch_assemble_gathered(a, p, cc, c->d_s_G3, c->d_v0p, c->d_v0c, c->d_VP, c->d_VC, c->st));
+  HIPCHK(c, launch_assemble_gathered(a, d, d, c->d_s_G3 + 2 * 2 * (size_t)c->nD * c->B * c->B, c->d_v0p,
+                                     c->d_v0p, c->d_s_Vd, nullptr, c->st, 1));
   HIPCHK(c, launch_su2_exch(c->n_ff, c->Nq, c->Lq, c->d_ff, c->d_fneg, c->d_twq, c->d_VP, c->d_s_Vax, c->st));
   HIPCHK(c, timer_mark(c, TUFRG_TIMER_PROJECT));
   HIPCHK(c, timer_mark(c, TUFRG_TIMER_BUNDLE));

@@ -190,19 +190,33 @@ struct degen_rel<float> {
   static constexpr float v = 2e-2f;
 };
 
-// (g(x) - g(y)) / (x - y) given gx = g(x), gy = g(y).
+// Mean of K' over [x, y], x and y closer than the switch.  Omega scheme: K' is
+// even with a kink at 0, an interval around 0 is the two from 0 to |x| and |y|.
 template <typename T>
-__device__ inline T divided_difference(T x, T y, T gx, T gy, T lam, int scheme, int deriv) {
-  T d = x - y;
-  T scale = (scheme == CUT_TEMPERATURE) ? lam : lam + fabs(x) + fabs(y);
-  if (fabs(d) > degen_rel<T>::v * scale) return (gx - gy) * rcp_fast(d);
+__device__ inline T near_mean(T x, T y, T lam, int scheme, int deriv) {
   if (scheme == CUT_OMEGA && x * y < T(0)) {
-    T w1 = fabs(x) / (fabs(x) + fabs(y));
-    return w1 * gl2_mean(x, T(0), lam, scheme, deriv) +
-           (T(1) - w1) * gl2_mean(T(0), y, lam, scheme, deriv);
+    const T a = fabs(x), b = fabs(y), w = a / (a + b);
+    if (sizeof(T) == 8)
+      return w * gl2_mean(a, T(0), lam, scheme, deriv) + (T(1) - w) * gl2_mean(T(0), b, lam, scheme, deriv);
+    return w * mid_mean(a, T(0), lam, scheme, deriv) + (T(1) - w) * mid_mean(T(0), b, lam, scheme, deriv);
   }
   if (sizeof(T) == 8 && scheme == CUT_OMEGA) return gl2_mean(x, y, lam, scheme, deriv);
   return mid_mean(x, y, lam, scheme, deriv);
+}
+
+// x - y = d too small for the quotient
+template <typename T>
+__device__ inline bool near_degenerate(T d, T x, T y, T lam, int scheme) {
+  const T scale = scheme == CUT_TEMPERATURE ? lam : lam + fabs(x) + fabs(y);
+  return !(fabs(d) > degen_rel<T>::v * scale);
+}
+
+// (g(x) - g(y)) / (x - y) given gx = g(x), gy = g(y).
+template <typename T>
+__device__ inline T divided_difference(T x, T y, T gx, T gy, T lam, int scheme, int deriv) {
+  const T d = x - y;
+  if (!near_degenerate(d, x, y, lam, scheme)) return (gx - gy) * rcp_fast(d);
+  return near_mean(x, y, lam, scheme, deriv);
 }
 
 }  // namespace tufrg

@@ -61,14 +61,6 @@ __device__ constexpr int REAL_TAU[NREAL] = {0, 5, 10, 15};
 __device__ constexpr int CPLX_TAU[NCPLX] = {1, 11, 2, 7, 3, 6};
 __device__ constexpr int CPLX_PARTNER[NCPLX] = {4, 14, 8, 13, 12, 9};
 
-template <typename T, int SCHEME>
-__device__ inline bool nondegenerate(T den, T x, T y, T lam) {
-  if constexpr (dd_scheme(SCHEME) == CUT_TEMPERATURE)
-    return fabs(den) > degen_rel<T>::v * lam;
-  else
-    return fabs(den) > degen_rel<T>::v * (lam + fabs(x) + fabs(y));
-}
-
 }  // namespace
 
 template <typename T>
@@ -162,24 +154,29 @@ __device__ inline void loop_no2_body(const T *__restrict__ ekv, const T *__restr
       const T epn[2] = {cp.ek.x, cp.ek.y}, Kpn[2] = {cp.ek.z, cp.ek.w};
       const T X0 = cp.pk.x, X1 = cp.pk.y, Xr = cp.pk.z, Xi = sg * cp.pk.w;
       // loop kernels L_mn: pp (K(e1)+K(e2))/(e1+e2), ph -(K(e1)-K(e2))/(e1-e2); divided
-      // difference of K at x = e_m(k), y = -sg e_n(k'); one branch for the rare near-degenerate lanes
-      T L[2][2];
-      bool ok = true;
+      // difference of K at x = e_m(k), y = -sg e_n(k').  A branch for the waves with a
+      // near-degenerate lane (one test of the smallest difference against the widest
+      // switch), which takes the mean for the pairs that are (all four there: Rashba
+      // FP32, 9 form factors, L 24: 562 us, the pairs alone 548)
+      T L[2][2], den[2][2];
 #pragma unroll
       for (int m = 0; m < 2; ++m)
 #pragma unroll
         for (int n = 0; n < 2; ++n) {
-          const T den = ekm[m] + sg * epn[n];
-          ok = ok && nondegenerate<T, SCHEME>(den, ekm[m], sg * epn[n], lam);
-          L[m][n] = sg * (Kkm[m] + sg * Kpn[n]) * rcp_fast(den);
+          den[m][n] = ekm[m] + sg * epn[n];
+          L[m][n] = sg * (Kkm[m] + sg * Kpn[n]) * rcp_fast(den[m][n]);
         }
-      if (__builtin_expect(!ok, 0)) {
+      const T dmin = fmin(fmin(fmin(fabs(den[0][0]), fabs(den[0][1])), fabs(den[1][0])), fabs(den[1][1]));
+      const T ex = dd_scheme(SCHEME) == CUT_TEMPERATURE
+                       ? lam
+                       : lam + fmax(fabs(ekm[0]), fabs(ekm[1])) + fmax(fabs(epn[0]), fabs(epn[1]));
+      if (__builtin_expect(!(dmin > degen_rel<T>::v * ex), 0)) {
 #pragma unroll
         for (int m = 0; m < 2; ++m)
 #pragma unroll
           for (int n = 0; n < 2; ++n)
-            L[m][n] = sg * divided_difference(ekm[m], -sg * epn[n], Kkm[m], -sg * Kpn[n], lam, dd_scheme(SCHEME),
-                                              deriv);
+            if (near_degenerate(den[m][n], ekm[m], epn[n], lam, dd_scheme(SCHEME)))
+              L[m][n] = sg * near_mean(ekm[m], -sg * epn[n], lam, dd_scheme(SCHEME), deriv);
       }
       if constexpr (SHELL) {
         // shell factor a_m(k) b_n(k') + b_m(k) a_n(k')
@@ -300,6 +297,101 @@ struct loop_waves {
   static constexpr int v = (sizeof(T) == 4) ? 4 : 2;
 };
 
+// End of a kx chunk: the sums over the wave's 64 ky with e^{-i 2 pi ky dy / Lf}.
+// The 16 real values of each of the 2 NDX - 1 kx sums (S, and A, B per dx) go
+// through LDS into the left operand of 16 x 16 x 4 matrix products against the
+// real phases (1, and cos, sin per dy), K the ky; the entries are put together
+// from these at the end.  With vector sums over the rebuilt 16 complex entries
+// (three times the products, an LDS read for each) the kernel took 35 -> 24 us
+// (Hubbard, 5 form factors, FP64, L 8), 87 -> 64 (Rashba, 13, FP64, L 15), 548 ->
+// 528 (Rashba, 9, FP32, L 24).  The products with the kx phases stay in the vector
+// unit: on the 4 x 4 x 1 matrix instruction, which is outer products of the lanes'
+// own values, they took as long (542 us), as it keeps the vector unit from issuing.
+constexpr int LDB = 68;  // row stride of the wave's LDS: 16 rows x 4 ky on different banks
+
+typedef float f32x4a __attribute__((ext_vector_type(4)));
+typedef double f64x4a __attribute__((ext_vector_type(4)));
+__device__ inline void mac16(f32x4a &c, float a, float b) { c = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+__device__ inline void mac16(f64x4a &c, double a, double b) { c = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+template <typename T>
+struct Acc16;
+template <>
+struct Acc16<float> {
+  typedef f32x4a type;
+  static __device__ inline int row(int lane, int r) { return 4 * (lane >> 4) + r; }
+};
+template <>
+struct Acc16<double> {
+  typedef f64x4a type;
+  static __device__ inline int row(int lane, int r) { return 4 * r + (lane >> 4); }
+};
+
+// per tau: index of its (real part's) value, bit 4: complex, bit 5: the partner (conjugate)
+__device__ constexpr unsigned char TAU_VALUE[16] = {0, 16 + 4, 16 + 8, 16 + 12, 48 + 4, 1, 16 + 14, 16 + 10,
+                                                    48 + 8, 48 + 14, 2, 16 + 6, 48 + 12, 48 + 10, 48 + 6, 3};
+
+template <typename T, int NDX, int NDY, int QW>
+__device__ __forceinline__ void loop_no2_contract(const T (&Sr)[NREAL], const T (&Sc)[NCPLX][2],
+                                                  const T (&Ar)[NDX - 1][NREAL], const T (&Br)[NDX - 1][NREAL],
+                                                  const T (&Ac)[NDX - 1][NCPLX][2], const T (&Bc)[NDX - 1][NCPLX][2],
+                                                  const double *__restrict__ tw, int Lf, int kyb, T (&buf)[32][LDB],
+                                                  T (&phy)[2 * NDY + 1][64], T *__restrict__ out, bool valid) {
+  constexpr int NPH = 2 * NDY + 1, NDY2 = 2 * NDY + 1, NV = 2 * NDX - 1;
+  static_assert(NV * 16 * NPH <= 32 * LDB, "the sums fit the wave's LDS");
+  const int lane = threadIdx.x & 63;
+  for (int i = threadIdx.x; i < NPH * 64; i += 64 * QW) {
+    const int p = i >> 6, l = i & 63, k = kyb * 64 + l, j = (k * ((p + 1) >> 1)) % Lf;
+    phy[p][l] = k < Lf ? (p == 0 ? T(1) : (T)tw[2 * j + 1 - (p & 1)]) : T(0);
+  }
+  __syncthreads();
+  const int col = lane & 15, kg = lane >> 4;
+  T ph[16];
+#pragma unroll
+  for (int s = 0; s < 16; ++s) {
+    const T v = phy[min(col, NPH - 1)][4 * s + kg];
+    ph[s] = col < NPH ? v : T(0);
+  }
+  typename Acc16<T>::type acc[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const int h = 16 * (v & 1), d = (v - 1) >> 1;
+#pragma unroll
+    for (int t = 0; t < NREAL; ++t) buf[h + t][lane] = v == 0 ? Sr[t] : (v & 1) ? Ar[d][t] : Br[d][t];
+#pragma unroll
+    for (int t = 0; t < 2 * NCPLX; ++t)
+      buf[h + NREAL + t][lane] = v == 0 ? Sc[t >> 1][t & 1] : (v & 1) ? Ac[d][t >> 1][t & 1] : Bc[d][t >> 1][t & 1];
+    __builtin_amdgcn_wave_barrier();  // the wave's own LDS
+    acc[v] = typename Acc16<T>::type{0, 0, 0, 0};
+#pragma unroll
+    for (int s = 0; s < 16; ++s) mac16(acc[v], buf[h + col][4 * s + kg], ph[s]);
+  }
+  __builtin_amdgcn_wave_barrier();
+  T *R = &buf[0][0];  // [vector][value][phase]
+  if (col < NPH) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) R[(v * 16 + Acc16<T>::row(lane, r)) * NPH + col] = acc[v][r];
+  }
+  __builtin_amdgcn_wave_barrier();
+  for (int o = lane; o < NDX * NDY2 * 16; o += 64) {
+    const int t = o & 15, dyi = (o >> 4) % NDY2, dx = (o >> 4) / NDY2, dy = dyi - NDY, y = abs(dy);
+    const int code = TAU_VALUE[t], i0 = code & 15;
+    const T pf = (code & 16) ? ((code & 32) ? T(-1) : T(1)) : T(0), bw = dx ? T(1) : T(0);
+    const T sy = dy == 0 ? T(0) : dy < 0 ? T(-1) : T(1);
+    const int jc = y ? 2 * y - 1 : 0, js = 2 * y;
+    const T *A = R + (dx ? 2 * dx - 1 : 0) * 16 * NPH, *B = R + 2 * dx * 16 * NPH;
+    const int k0 = i0 * NPH, k1 = (i0 + ((code >> 4) & 1)) * NPH;
+    // the entry's kx sum: re = A.re -+ B.im, im = +-A.im + B.re (the partner: lower sign)
+    const T rc = A[k0 + jc] - pf * bw * B[k1 + jc], ic = pf * A[k1 + jc] + bw * B[k0 + jc];
+    const T rs = sy * (A[k0 + js] - pf * bw * B[k1 + js]), is = sy * (pf * A[k1 + js] + bw * B[k0 + js]);
+    if (valid) {
+      out[2 * o] = rc - is;
+      out[2 * o + 1] = ic + rs;
+    }
+  }
+}
+
 // One work item (ky block, item group, kx chunk, channel) of QW waves, w its
 // index; bufs and phy are the workgroup's LDS.
 template <typename T, int NDX, int NDY, int SCHEME, int QW>
@@ -308,8 +400,8 @@ __device__ __forceinline__ void loop_no2_item(const T *__restrict__ ekv, const T
                                               const T *__restrict__ twk, int Lq, int n_ref, int Lf, int nkyb,
                                               int kxper, int nparts, int half, const int *__restrict__ items, int n_pp,
                                               int n_ph, int w, T lam, int deriv,
-                                              T *__restrict__ partial, T (&bufs)[QW][32][65],
-                                              T (&phy)[2 * NDY + 1][2][64]) {
+                                              T *__restrict__ partial, T (&bufs)[QW][32][LDB],
+                                              T (&phy)[2 * NDY + 1][64]) {
   constexpr int NDY2 = 2 * NDY + 1;
   const int tid = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int kyb = w % nkyb;
@@ -359,75 +451,11 @@ __device__ __forceinline__ void loop_no2_item(const T *__restrict__ ekv, const T
                                      Sc, Ar, Br, Ac,
                                      Bc);
 
-  // rebuild all 16 entries per dx, transpose through LDS, contract with e^{-i 2 pi ky dy / Lf}
-  T(&buf)[32][65] = bufs[wv];
-  if (wv == 0) {
-#pragma unroll
-    for (int i = 0; i < NDY2; ++i) {
-      int dy = i - NDY;
-      int j = (int)(((long long)ky_raw * dy) % Lf);
-      if (j < 0) j += Lf;
-      phy[i][0][tid] = (T)tw[2 * j];
-      phy[i][1][tid] = (T)tw[2 * j + 1];
-    }
-  }
-  const T on = active ? T(1) : T(0);
-  const size_t pbase = ((size_t)it * nparts + (kyb + nkyb * kxc)) * (size_t)(NDX * NDY2 * 16);
-#pragma unroll
-  for (int dx = 0; dx < NDX; ++dx) {
-    __syncthreads();
-    if (dx == 0) {
-#pragma unroll
-      for (int t = 0; t < NREAL; ++t) {
-        buf[2 * REAL_TAU[t]][tid] = on * Sr[t];
-        buf[2 * REAL_TAU[t] + 1][tid] = T(0);
-      }
-#pragma unroll
-      for (int t = 0; t < NCPLX; ++t) {
-        buf[2 * CPLX_TAU[t]][tid] = on * Sc[t][0];
-        buf[2 * CPLX_TAU[t] + 1][tid] = on * Sc[t][1];
-        buf[2 * CPLX_PARTNER[t]][tid] = on * Sc[t][0];
-        buf[2 * CPLX_PARTNER[t] + 1][tid] = -on * Sc[t][1];
-      }
-    } else {
-      const int d = dx - 1;
-#pragma unroll
-      for (int t = 0; t < NREAL; ++t) {
-        buf[2 * REAL_TAU[t]][tid] = on * Ar[d][t];
-        buf[2 * REAL_TAU[t] + 1][tid] = on * Br[d][t];
-      }
-#pragma unroll
-      for (int t = 0; t < NCPLX; ++t) {
-        const T ar = Ac[d][t][0], ai = Ac[d][t][1], br = Bc[d][t][0], bi = Bc[d][t][1];
-        buf[2 * CPLX_TAU[t]][tid] = on * (ar - bi);
-        buf[2 * CPLX_TAU[t] + 1][tid] = on * (ai + br);
-        buf[2 * CPLX_PARTNER[t]][tid] = on * (ar + bi);
-        buf[2 * CPLX_PARTNER[t] + 1][tid] = on * (br - ai);
-      }
-    }
-    __syncthreads();
-    for (int o = tid; o < NDY2 * 16; o += 64) {
-      const int t = o & 15;
-      const int dyi = o >> 4;
-      T sr = T(0), si = T(0);
-#pragma unroll 4
-      for (int l = 0; l < 64; ++l) {
-        const T ar = buf[2 * t][l], ai = buf[2 * t + 1][l];
-        const T pr = phy[dyi][0][l], pim = phy[dyi][1][l];
-        sr = fma(pr, ar, sr);
-        sr = fma(-pim, ai, sr);
-        si = fma(pr, ai, si);
-        si = fma(pim, ar, si);
-      }
-      const size_t idx = pbase + ((size_t)(dx * NDY2 + dyi) * 16 + t);
-      if (qvalid) {
-        partial[2 * idx] = sr;
-        partial[2 * idx + 1] = si;
-      }
-    }
-  }
+  loop_no2_contract<T, NDX, NDY, QW>(Sr, Sc, Ar, Br, Ac, Bc, tw, Lf, kyb, bufs[wv], phy,
+                                     partial + 2 * ((size_t)it * nparts + (kyb + nkyb * kxc)) *
+                                                   (size_t)(NDX * NDY2 * 16),
+                                     qvalid);
 }
-
 
 template <typename T, int NDX, int NDY, int SCHEME, int QW>
 __global__ __launch_bounds__(64 * QW, (NDX > 3 ? (sizeof(T) == 8 ? 1 : 2) : (sizeof(T) == 8 ? 2 : 4))) void loop_no2_kernel(const T *__restrict__ ekv, const T *__restrict__ pi4, const T *__restrict__ cvp,
@@ -436,8 +464,8 @@ __global__ __launch_bounds__(64 * QW, (NDX > 3 ? (sizeof(T) == 8 ? 1 : 2) : (siz
                                                            int half, const int *__restrict__ items, int n_pp,
                                                            int n_ph, int n_work, T lam, int deriv,
                                                            T *__restrict__ partial) {
-  __shared__ T bufs[QW][32][65];
-  __shared__ T phy[2 * NDY + 1][2][64];
+  __shared__ T bufs[QW][32][LDB];
+  __shared__ T phy[2 * NDY + 1][64];
   const int xcd = blockIdx.x % N_XCD, slot = blockIdx.x / N_XCD;
   const int base = n_work / N_XCD, rem = n_work % N_XCD;
   if (slot >= base + (xcd < rem ? 1 : 0)) return;  // padding workgroup, no work
@@ -452,8 +480,8 @@ __global__ __launch_bounds__(64 * QW, (NDX > 3 ? (sizeof(T) == 8 ? 1 : 2) : (siz
 // own launch.
 template <typename T, int NDX, int NDY, int SCHEME, int QW>
 __global__ __launch_bounds__(64 * QW, (NDX > 3 ? (sizeof(T) == 8 ? 1 : 2) : (sizeof(T) == 8 ? 2 : 4))) void loop_no2_batch_kernel(const No2Inst *__restrict__ inst, int n_inst, int n_work) {
-  __shared__ T bufs[QW][32][65];
-  __shared__ T phy[2 * NDY + 1][2][64];
+  __shared__ T bufs[QW][32][LDB];
+  __shared__ T phy[2 * NDY + 1][64];
   const int xcd = blockIdx.x % N_XCD, slot = blockIdx.x / N_XCD;
   const int base = n_work / N_XCD, rem = n_work % N_XCD;
   if (slot >= base + (xcd < rem ? 1 : 0)) return;  // padding workgroup, no work

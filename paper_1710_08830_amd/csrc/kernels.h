@@ -188,8 +188,15 @@ hipError_t launch_zgemm_batched(int n, int n_q, int opA, int opB, const double *
                                 hipStream_t st);
 
 // a7: ODE updates and reductions
-hipError_t launch_axpy_max(long long n, const double *x, double h, const double *dx, double *y,
-                           unsigned long long *maxbits, unsigned int *flag, hipStream_t st);
+struct StepArrays {
+  const double *x[3], *dx[3];
+  double *y[3];
+};
+// y = x + h dx per array (null dx: no update; null y: no result), max |y| and the
+// non-finite flag over all to out_bits, out_flag; bits, flag, ticket zero between launches
+hipError_t launch_step_max(long long n, const StepArrays &a, int n_arr, double h, unsigned long long *bits,
+                           unsigned int *flag, unsigned int *ticket, unsigned long long *out_bits,
+                           unsigned int *out_flag, hipStream_t st);
 hipError_t launch_lincomb(long long n, const double *x, int nk, const double *const *k, const double *coef,
                           double h, double *y, hipStream_t st);
 hipError_t launch_dp_error(long long n, const double *x0, const double *x1, int nk, const double *const *k,

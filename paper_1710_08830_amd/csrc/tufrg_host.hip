@@ -656,6 +656,8 @@ extern "C" tufrg_status tufrg_create(const tufrg_model *m, const tufrg_setup *s,
   }
   CTRY(dalloc(c, &c->d_bits, 4));
   CTRY(dalloc(c, &c->d_flag, 4));
+  // [0] the error norm's, [1] and d_flag[2] the accumulators and ticket of step_max, zero between launches
+  for (int i = 1; i < 3; ++i) CHIP(launch_clear_reduce(c->d_bits + i, c->d_flag + i, c->st));
   CHIP(hipHostMalloc((void **)&c->h_bits, 4 * sizeof(unsigned long long), hipHostMallocDefault));
   CHIP(hipHostMalloc((void **)&c->h_flag, 4 * sizeof(unsigned int), hipHostMallocDefault));
   CTRY(dalloc(c, &c->d_sbits, 4));
@@ -1755,9 +1757,8 @@ extern "C" tufrg_status tufrg_sur_loops(tufrg_ctx *c, double lambda, tufrg_c64 *
 // ---------------------------------------------------------------------------
 // flow
 
-static tufrg_status read_reduce(tufrg_ctx *c, double *val, bool *bad) {
-  HIPCHK(c, hipMemcpyAsync(c->h_bits, c->d_bits, sizeof(unsigned long long), hipMemcpyDeviceToHost, c->st));
-  HIPCHK(c, hipMemcpyAsync(c->h_flag, c->d_flag, sizeof(unsigned int), hipMemcpyDeviceToHost, c->st));
+// the maximum and flag at h_bits, h_flag once the stream is done
+static tufrg_status read_pinned(tufrg_ctx *c, double *val, bool *bad) {
   HIPCHK(c, hipStreamSynchronize(c->st));
   unsigned long long b = c->h_bits[0];
   double v;
@@ -1767,12 +1768,30 @@ static tufrg_status read_reduce(tufrg_ctx *c, double *val, bool *bad) {
   return TUFRG_OK;
 }
 
+static tufrg_status read_reduce(tufrg_ctx *c, double *val, bool *bad) {
+  HIPCHK(c, hipMemcpyAsync(c->h_bits, c->d_bits, sizeof(unsigned long long), hipMemcpyDeviceToHost, c->st));
+  HIPCHK(c, hipMemcpyAsync(c->h_flag, c->d_flag, sizeof(unsigned int), hipMemcpyDeviceToHost, c->st));
+  return read_pinned(c, val, bad);
+}
+
+// x += h dx for the n arrays of a state (null dx: only the maximum), its maximum
+// and flag to h_bits, h_flag or to the given slots
+static hipError_t launch_step(tufrg_ctx *c, int n, double *const *x, const double *const *dx, double h,
+                              unsigned long long *bits = nullptr, unsigned int *flag = nullptr) {
+  StepArrays a{};
+  for (int i = 0; i < n; ++i) {
+    a.x[i] = x[i];
+    a.dx[i] = dx ? dx[i] : nullptr;
+    a.y[i] = dx ? x[i] : nullptr;
+  }
+  return launch_step_max((long long)c->Nq * c->B * c->B, a, n, h, c->d_bits + 1, c->d_flag + 1, c->d_flag + 2,
+                         bits ? bits : c->h_bits, flag ? flag : c->h_flag, c->st);
+}
+
 static tufrg_status state_max(tufrg_ctx *c, const double *P, const double *C, double *m, bool *bad) {
-  const long long n = (long long)c->Nq * c->B * c->B;
-  HIPCHK(c, launch_clear_reduce(c->d_bits, c->d_flag, c->st));
-  HIPCHK(c, launch_axpy_max(n, P, 0.0, nullptr, nullptr, c->d_bits, c->d_flag, c->st));
-  HIPCHK(c, launch_axpy_max(n, C, 0.0, nullptr, nullptr, c->d_bits, c->d_flag, c->st));
-  return read_reduce(c, m, bad);
+  double *const x[2] = {(double *)P, (double *)C};
+  HIPCHK(c, launch_step(c, 2, x, nullptr, 0.0));
+  return read_pinned(c, m, bad);
 }
 
 static double lambda_c_interp(double l0, double m0, double l1, double m1, double vmax) {
@@ -1820,13 +1839,12 @@ static tufrg_status graph_prepare(tufrg_ctx *c) {
 // the sequence can be captured)
 static tufrg_status enqueue_euler_steps(tufrg_ctx *c, const tufrg_flow_opts *o, double *P, double *C, int i0, int g,
                                         unsigned mask) {
-  const long long ncx = (long long)c->B * c->B * c->Nq;
   for (int j = 0; j < g; ++j) {
     const double l0 = euler_lambda(o, i0 + j), l1 = euler_lambda(o, i0 + j + 1);
     TRY(rhs_internal(c, l0, P, C, c->d_dP, c->d_dC, 1.0, mask));
-    HIPCHK(c, launch_clear_reduce(c->d_gbits + j, c->d_gflag + j, c->st));
-    HIPCHK(c, launch_axpy_max(ncx, P, l1 - l0, c->d_dP, P, c->d_gbits + j, c->d_gflag + j, c->st));
-    HIPCHK(c, launch_axpy_max(ncx, C, l1 - l0, c->d_dC, C, c->d_gbits + j, c->d_gflag + j, c->st));
+    double *const x[2] = {P, C};
+    const double *const dx[2] = {c->d_dP, c->d_dC};
+    HIPCHK(c, launch_step(c, 2, x, dx, l1 - l0, c->d_gbits + j, c->d_gflag + j));
   }
   return TUFRG_OK;
 }
@@ -2000,11 +2018,11 @@ extern "C" tufrg_status tufrg_flow(tufrg_ctx *c, const tufrg_flow_opts *o, tufrg
       const double l0 = euler_lambda(o, i), l1 = euler_lambda(o, i + 1);
       TRY(rhs_internal(c, l0, P, C, c->d_dP, c->d_dC, 1.0, mask));
       res->n_rhs++;
-      HIPCHK(c, launch_clear_reduce(c->d_bits, c->d_flag, c->st));
-      HIPCHK(c, launch_axpy_max(ncx, P, l1 - l0, c->d_dP, P, c->d_bits, c->d_flag, c->st));
-      HIPCHK(c, launch_axpy_max(ncx, C, l1 - l0, c->d_dC, C, c->d_bits, c->d_flag, c->st));
+      double *const x[2] = {P, C};
+      const double *const dx[2] = {c->d_dP, c->d_dC};
+      HIPCHK(c, launch_step(c, 2, x, dx, l1 - l0));
       double mx;
-      TRY(read_reduce(c, &mx, &bad));
+      TRY(read_pinned(c, &mx, &bad));
       if (bad) return fail(c, TUFRG_E_NONFINITE, "non-finite state after Euler step " + std::to_string(i));
       res->n_steps++;
       res->lambda_stop = l1;
@@ -2176,11 +2194,10 @@ extern "C" tufrg_status tufrg_su2_flow(tufrg_ctx *c, const tufrg_flow_opts *o, t
   }
   if (!c->d_s_dd) TRY(dalloc(c, &c->d_s_dd, 2 * (size_t)ncx));
   auto maxof = [&](double h, const double *dx1, const double *dx2, const double *dx3, double *m, bool *bad) {
-    HIPCHK(c, launch_clear_reduce(c->d_bits, c->d_flag, c->st));
-    HIPCHK(c, launch_axpy_max(ncx, p, h, dx1, dx1 ? p : nullptr, c->d_bits, c->d_flag, c->st));
-    HIPCHK(c, launch_axpy_max(ncx, cc, h, dx2, dx2 ? cc : nullptr, c->d_bits, c->d_flag, c->st));
-    HIPCHK(c, launch_axpy_max(ncx, d, h, dx3, dx3 ? d : nullptr, c->d_bits, c->d_flag, c->st));
-    return read_reduce(c, m, bad);
+    double *const x[3] = {p, cc, d};
+    const double *const dx[3] = {dx1, dx2, dx3};
+    HIPCHK(c, launch_step(c, 3, x, dx1 ? dx : nullptr, h));
+    return read_pinned(c, m, bad);
   };
   double m_prev = 0.0;
   bool bad = false;
@@ -2432,12 +2449,9 @@ extern "C" tufrg_status tufrg_batch_flow(tufrg_batch *b, const tufrg_flow_opts *
       if ((fused ? rhs_products(c, Pi, Ci, c->d_dP, c->d_dC, 1.0, mask)
                  : rhs_internal(c, l0, Pi, Ci, c->d_dP, c->d_dC, 1.0, mask)) != TUFRG_OK)
         return inst_fail(i);
-      if (launch_clear_reduce(c->d_bits, c->d_flag, c->st) != hipSuccess ||
-          launch_axpy_max(ncx, Pi, l1 - l0, c->d_dP, Pi, c->d_bits, c->d_flag, c->st) != hipSuccess ||
-          launch_axpy_max(ncx, Ci, l1 - l0, c->d_dC, Ci, c->d_bits, c->d_flag, c->st) != hipSuccess ||
-          hipMemcpyAsync(c->h_bits, c->d_bits, sizeof(unsigned long long), hipMemcpyDeviceToHost, c->st) !=
-              hipSuccess ||
-          hipMemcpyAsync(c->h_flag, c->d_flag, sizeof(unsigned int), hipMemcpyDeviceToHost, c->st) != hipSuccess) {
+      double *const x[2] = {Pi, Ci};
+      const double *const dx[2] = {c->d_dP, c->d_dC};
+      if (launch_step(c, 2, x, dx, l1 - l0) != hipSuccess) {
         (void)hipGetLastError();
         return bfail(b, TUFRG_E_HIP, "instance " + std::to_string(i) + ": launch failed");
       }

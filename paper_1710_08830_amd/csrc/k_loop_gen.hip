@@ -18,10 +18,16 @@
 // -dy is A - iB.  At the end of the row Lc[(dx, dy)] += e^{-i kx dx} Y(dy) for
 // every (dx, dy) in D.
 //
-// Staging.  Per tile of KT consecutive ky the workgroup writes to LDS the
-// projectors Pi_m(k) as full complex NO x NO matrices, the packed X_n(k'), the
-// loop kernels L_mn and then W_m(k) as full complex matrices, so that the
-// inner loop reads one complex value of Pi and one of W per band.
+// Staging.  Tiles of KT consecutive ky go through LDS in packed Hermitian form:
+// the projectors Pi_m(k) and X_n(k'), the loop kernels L_mn and then W_m(k).  The
+// inner loop reads the two reals of an entry per band and sums the four real
+// products; the signs (conjugate entries, real diagonals) enter once per point.
+// The steps of a tile run in four stages of a pipeline with one barrier per tile,
+// the values from memory one tile ahead in registers: waiting for each tile's
+// loads and at four barriers the kernel took 1.73 ms (t2g, 13 form factors, FP64,
+// L 10 refined 6) and 1.45 ms (Zeeman, 9, FP32, L 11 refined 5), now 0.98 and
+// 0.74 ms: FP32 is then bound by vector issue and LDS reads, FP64 (13 form factors:
+// 41 complex sums a thread, six waves a CU) by the latency of the stages.
 //
 // Kramers pairs (PAIR): when bands (0,1), (2,3), (4,5) are degenerate at every
 // k, L_mn depends on the pairs only and the band sums group exactly into three
@@ -34,11 +40,6 @@
 namespace tufrg {
 
 namespace {
-
-template <typename T>
-struct alignas(2 * sizeof(T)) c2 {
-  T re, im;
-};
 
 // points (dx, dy) of the difference set: the 9-vector shell gives the 5 x 5
 // box (R = 2), the 13-vector shell the diamond |dx| + |dy| <= 4 (R = 4)
@@ -67,38 +68,15 @@ struct Shape<4> {
   __device__ static constexpr int dy(int i) { return i - row_start(dx(i)) - (row_len(dx(i)) - 1) / 2; }
 };
 
-// packed Hermitian NO x NO matrix: NO diagonal reals, then Re and Im of (lo, hi)
-// for lo < hi in row-major order; slot -> (lo, hi) of an off-diagonal pair
+// entry (r, c) of a packed Hermitian NO x NO matrix (NO diagonal reals, then Re
+// and Im of (lo, hi) for lo < hi in row-major order): offset of its real part,
+// sign of the imaginary part behind it (0: real)
 template <int NO>
-__device__ inline void pair_of(int p, int &lo, int &hi) {
-  lo = 0;
-  while (p >= NO - 1 - lo) {
-    p -= NO - 1 - lo;
-    ++lo;
-  }
-  hi = lo + 1 + p;
-}
-
-// writes packed value x of slot pl into the full complex matrix dst[NO][NO]
-template <typename T, int NO>
-__device__ inline void unpack_store(c2<T> *dst, int pl, T x) {
-  if (pl < NO) {
-    c2<T> v;
-    v.re = x;
-    v.im = T(0);
-    dst[pl * NO + pl] = v;
-    return;
-  }
-  const int q = pl - NO;
-  int lo, hi;
-  pair_of<NO>(q >> 1, lo, hi);
-  if (q & 1) {
-    dst[lo * NO + hi].im = x;
-    dst[hi * NO + lo].im = -x;
-  } else {
-    dst[lo * NO + hi].re = x;
-    dst[hi * NO + lo].re = x;
-  }
+__device__ inline int packed_of(int r, int c, int &sign) {
+  sign = r < c ? 1 : r > c ? -1 : 0;
+  if (r == c) return r;
+  const int lo = min(r, c), hi = max(r, c);
+  return NO + 2 * (lo * (2 * NO - 1 - lo) / 2 + hi - lo - 1);
 }
 
 }  // namespace
@@ -123,9 +101,6 @@ __global__ __launch_bounds__(NTHR) void loop_gen_kernel(const T *__restrict__ ba
   constexpr bool SHELL = SCHEME == CUT_SHELL;
   // band m of the sums in the arrays of all bands (paired: the first of the pair)
   constexpr int MS = PAIR ? 2 : 1;
-  // staged values per k-point: energies, packed projectors and regulator
-  // values (and the shell factors a_m, b_m of the momentum-shell scheme)
-  constexpr int NIT = NB + PK + NB + (SHELL ? 2 * NB : 0);
   const int tid = threadIdx.x;
   int w = blockIdx.x;
   const int part = w % nparts;
@@ -139,16 +114,21 @@ __global__ __launch_bounds__(NTHR) void loop_gen_kernel(const T *__restrict__ ba
   const int pidx = part * NTHR + tid;
   const bool active = pidx < n_pairs;
   const int tau = active ? pairs[2 * pidx] : 0, taub = active ? pairs[2 * pidx + 1] : 0;
-  const int xo = (tau / (NO * NO2)) * NO + (tau / NO) % NO;  // (a, c)
-  const int yo = ((tau / NO2) % NO) * NO + tau % NO;        // (b, d)
+  // Pi_m at (a, c), W_m at (b, d); ph takes the transpose of Pi_n(k')
+  int sgx, sgy;
+  const int xo = packed_of<NO>(tau / (NO * NO2), (tau / NO) % NO, sgx);
+  const int yo = packed_of<NO>((tau / NO2) % NO, tau % NO, sgy);
+  const T sx = T(sgx), sy = T(ch == 0 ? sgy : -sgy), sxy = sx * sy;
 
-  __shared__ c2<T> sP[KT][NB][NO2];  // Pi_m(k)
-  __shared__ c2<T> sW[KT][NB][NO2];  // W_m(k)
-  __shared__ T sX[KT][PK];           // X_n(k') packed
-  __shared__ T sE[KT][2][NB];        // e at k and k'
-  __shared__ T sK[KT][2][NB];        // regulator at k and k'
-  __shared__ T sL[KT][NB][NB];
-  __shared__ T sC[SHELL ? KT : 1][2][2 * NB];  // shell factors (a_m, b_m) at k and k'
+  constexpr int PU = PK / 2;                       // pairs of reals of a point's projectors
+  constexpr int EKV = 2 * NB + (SHELL ? 2 * NB : 0);  // e, K (a, b of the shell) of a point
+  constexpr int NSL = (KT * PU + NTHR - 1) / NTHR, NSE = (KT * 2 * EKV + NTHR - 1) / NTHR;
+  typedef T T2 __attribute__((ext_vector_type(2)));
+  __shared__ T2 sP[2][KT][PU];  // Pi_m(k) packed
+  __shared__ T2 sX[2][KT][PU];  // X_n(k') packed
+  __shared__ T2 sW[2][KT][PU];  // W_m(k) packed
+  __shared__ T sE[2][KT][2][EKV];
+  __shared__ T sL[2][KT][NB][NB];
   const T sg = (ch == 0) ? T(1) : T(-1);
 
   cx<T> Z[NPT];
@@ -157,75 +137,133 @@ __global__ __launch_bounds__(NTHR) void loop_gen_kernel(const T *__restrict__ ba
 
   int r0, nr, hx0, hx1;
   loop_rows(Lf, qfx, (half >> ch) & 1, r0, nr, hx0, hx1);
-  nr = min(nr, (kxc + 1) * kxper);
-  for (int r = kxc * kxper; r < nr; ++r) {
-    const int kx = r0 + r >= Lf ? r0 + r - Lf : r0 + r;
-    const T wgt = (kx == hx0 || kx == hx1) ? T(0.5) : T(1);
-    int kpx = (ch == 0) ? (qfx - kx) : (kx - qfx);
-    kpx += kpx < 0 ? Lf : 0;
-    cx<T> S = cmake(T(0), T(0)), A[NDY], B[NDY];
+  nr = min(nr, (kxc + 1) * kxper) - kxc * kxper;
+  r0 += kxc * kxper;
+  const int ntk = (Lf + KT - 1) / KT, ntile = nr * ntk;
+  const unsigned magic = 0xffffffffu / (unsigned)ntk + 1u;  // t / ntk, exact for t < 2^32 / ntk
+  struct Pos {
+    int kx, kpx, ky0;
+  };
+  auto pos = [&](int t) __attribute__((always_inline)) {
+    t = min(t, ntile - 1);
+    const int r = ntk == 1 ? t : (int)__umulhi((unsigned)t, magic);
+    Pos p;
+    p.kx = r0 + r >= Lf ? r0 + r - Lf : r0 + r;
+    p.kpx = ch == 0 ? qfx - p.kx : p.kx - qfx;
+    p.kpx += p.kpx < 0 ? Lf : 0;
+    p.ky0 = (t - r * ntk) * KT;
+    return p;
+  };
+  auto column = [&](int side, int ky) __attribute__((always_inline)) {
+    ky = min(ky, Lf - 1);
+    int kp = ch == 0 ? qfy - ky : ky - qfy;
+    kp += kp < 0 ? Lf : 0;
+    return side ? kp : ky;
+  };
+  // a tile's values on their way from memory, in registers
+  T2 rp[NSL], rx[NSL];
+  T re[NSE];
+  auto load_pi = [&](int t, int side, T2 (&v)[NSL]) __attribute__((always_inline)) {
+    const Pos p = pos(t);
 #pragma unroll
-    for (int j = 0; j < NDY; ++j) A[j] = B[j] = cmake(T(0), T(0));
-    for (int ky0 = 0; ky0 < Lf; ky0 += KT) {
-      __syncthreads();
-#pragma unroll 1
-      for (int i = tid; i < KT * 2 * NIT; i += NTHR) {
-        const int r = i % NIT, t2 = i / NIT;
-        const int j = t2 >> 1, side = t2 & 1;
-        const int ky = ky0 + j < Lf ? ky0 + j : Lf - 1;
-        int kpy = (ch == 0) ? (qfy - ky) : (ky - qfy);
-        kpy += kpy < 0 ? Lf : 0;
-        const unsigned kk = side ? (unsigned)kpx * Lf + kpy : (unsigned)kx * Lf + ky;
-        if (r < NB) {
-          sE[j][side][r] = band[(size_t)kk * NC + MS * r];
-        } else if (r < NB + PK) {
-          const int p = r - NB, m = p / NO2, pl = p % NO2;
-          T x = PAIR ? pir[(size_t)kk * PK + p] : band[(size_t)kk * NC + NO + p];
-          if (side == 0) {
-            unpack_store<T, NO>(&sP[j][m][0], pl, x);
-          } else {
-            // ph uses the transpose of Pi_n(k'): flip the imaginary parts
-            if (ch == 1 && pl >= NO && ((pl - NO) & 1)) x = -x;
-            sX[j][p] = x;
-          }
-        } else if (r < NB + PK + NB) {
-          sK[j][side][r - NB - PK] = kv[(size_t)kk * NO + MS * (r - NB - PK)];
-        } else if constexpr (SHELL) {
-          const int c = r - 2 * NB - PK;  // (a_m, b_m) of summed band c / 2
-          sC[j][side][c] = cvp[(size_t)kk * 2 * NO + 2 * MS * (c >> 1) + (c & 1)];
-        }
-      }
-      __syncthreads();
-      // loop kernels L_mn = sg * DD[K](e_m(k), -sg e_n(k'))
-      if (tid < KT * NB * NB) {
-        const int j = tid / (NB * NB), m = (tid / NB) % NB, n = tid % NB;
-        const T x = sE[j][0][m], y = -sg * sE[j][1][n];
-        T l = sg * divided_difference(x, y, sK[j][0][m], -sg * sK[j][1][n], lam, dd_scheme(SCHEME), deriv);
-        // shell scheme: times a_m(k) b_n(k') + b_m(k) a_n(k')
-        if constexpr (SHELL) l *= fma(sC[j][0][2 * m], sC[j][1][2 * n + 1], sC[j][0][2 * m + 1] * sC[j][1][2 * n]);
-        sL[j][m][n] = wgt * l;
-      }
-      __syncthreads();
-      // W_m = sum_n L_mn X_n, packed sums written as full complex matrices
-#pragma unroll 1
-      for (int i = tid; i < KT * PK; i += NTHR) {
-        const int j = i / PK, mp = i % PK, m = mp / NO2, pl = mp % NO2;
-        T acc = T(0);
+    for (int u = 0; u < NSL; ++u) {
+      const int i = min(tid + NTHR * u, KT * PU - 1), j = i / PU, o = i - j * PU;
+      const size_t k = (size_t)(side ? p.kpx : p.kx) * Lf + column(side, p.ky0 + j);
+      v[u] = ((const T2 *)(PAIR ? pir + k * PK : band + k * NC + NO))[o];
+    }
+  };
+  auto store_pi = [&](T2 (*dst)[PU], const T2 (&v)[NSL]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int n = 0; n < NB; ++n) acc = fma(sL[j][m][n], sX[j][n * NO2 + pl], acc);
-        unpack_store<T, NO>(&sW[j][m][0], pl, acc);
+    for (int u = 0; u < NSL; ++u) {
+      const int i = tid + NTHR * u;
+      if (i < KT * PU) (&dst[0][0])[i] = v[u];
+    }
+  };
+  auto load_e = [&](int t) __attribute__((always_inline)) {
+    const Pos p = pos(t);
+#pragma unroll
+    for (int u = 0; u < NSE; ++u) {
+      const int i = min(tid + NTHR * u, KT * 2 * EKV - 1), j = i / (2 * EKV), v = i - j * 2 * EKV;
+      const int side = v / EKV, r = v - side * EKV;
+      const size_t k = (size_t)(side ? p.kpx : p.kx) * Lf + column(side, p.ky0 + j);
+      const T *src = r < NB ? band + k * NC + MS * r : kv + k * NO + MS * (r - NB);
+      if (SHELL && r >= 2 * NB) {
+        const int c = r - 2 * NB;  // (a_m, b_m) of summed band c / 2
+        src = cvp + k * 2 * NO + 2 * MS * (c >> 1) + (c & 1);
       }
-      __syncthreads();
-      const int kt = min(KT, Lf - ky0);
-      for (int j = 0; j < kt; ++j) {
-        // the same for every lane: scalar loads
-        const T *ph = phy + (size_t)(ky0 + j) * (2 * NDY);
-        cx<T> M = cmake(T(0), T(0));
+      re[u] = *src;
+    }
+  };
+  auto store_e = [&](int bf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < NSE; ++u) {
+      const int i = tid + NTHR * u;
+      if (i < KT * 2 * EKV) (&sE[bf][0][0][0])[i] = re[u];
+    }
+  };
+  // loop kernels L_mn = sg * DD[K](e_m(k), -sg e_n(k')), the row's weight included
+  auto loop_kernels = [&](int t, int bf) __attribute__((always_inline)) {
+    // from wave 2 on: of six waves, 2 and 3 have a SIMD of their own
+    for (int i = tid >= 128 ? tid - 128 : tid + NTHR - 128; i < KT * NB * NB; i += NTHR) {
+      const int j = i / (NB * NB), m = (i / NB) % NB, n = i % NB, kx = pos(t).kx;
+      const T(&e0)[EKV] = sE[bf][j][0], (&e1)[EKV] = sE[bf][j][1];
+      T l = (kx == hx0 || kx == hx1 ? T(0.5) * sg : sg) *
+            divided_difference(e0[m], -sg * e1[n], e0[NB + m], -sg * e1[NB + n], lam, dd_scheme(SCHEME), deriv);
+      // shell scheme: times a_m(k) b_n(k') + b_m(k) a_n(k')
+      if constexpr (SHELL)
+        l *= fma(e0[2 * NB + 2 * m], e1[2 * NB + 2 * n + 1], e0[2 * NB + 2 * m + 1] * e1[2 * NB + 2 * n]);
+      sL[bf][j][m][n] = l;
+    }
+  };
+  // W_m = sum_n L_mn X_n
+  auto weights = [&](int bf) __attribute__((always_inline)) {
+    for (int i = tid; i < KT * PU; i += NTHR) {
+      const int j = i / PU, mp = i - j * PU, m = mp / (NO2 / 2), o = mp - m * (NO2 / 2);
+      T2 acc = T2{T(0), T(0)};
+#pragma unroll
+      for (int n = 0; n < NB; ++n) {
+        const T l = sL[bf][j][m][n];
+        const T2 x = sX[bf][j][n * (NO2 / 2) + o];
+        acc[0] = fma(l, x[0], acc[0]);
+        acc[1] = fma(l, x[1], acc[1]);
+      }
+      sW[bf][j][mp] = acc;
+    }
+  };
+  cx<T> S = cmake(T(0), T(0)), A[NDY], B[NDY];
+#pragma unroll
+  for (int j = 0; j < NDY; ++j) A[j] = B[j] = cmake(T(0), T(0));
+  if (ntile > 0) load_e(0);  // none: a last chunk past the rows of this item
+  // one barrier per tile: products of tile t, W of t + 1, loop kernels of t + 2;
+  // the values of t + 1 (Pi), t + 2 (X), t + 3 (e, K) from registers into LDS, the
+  // next ones on their way meanwhile
+  for (int t = ntile > 0 ? -3 : ntile; t < ntile; ++t) {
+    store_e((t + 3) & 1);
+    if (t >= -2) store_pi(sX[t & 1], rx);
+    if (t >= -1) store_pi(sP[(t + 1) & 1], rp);
+    load_e(t + 4);
+    load_pi(t + 3, 1, rx);
+    load_pi(max(t + 2, 0), 0, rp);
+    if (t >= -2 && t + 2 < ntile) loop_kernels(t + 2, t & 1);
+    if (t >= -1 && t + 1 < ntile) weights((t + 1) & 1);
+    if (t >= 0) {
+      const Pos p = pos(t);
+      const int kt = min(KT, Lf - p.ky0);
+      const T *P = (const T *)sP[t & 1] + xo, *W = (const T *)sW[t & 1] + yo;
+#pragma unroll 2
+      for (int j = 0; j < kt; ++j, P += PK, W += PK) {
+        // the same for every lane: scalar loads (through LDS: 1.00 -> 1.20 ms)
+        const T *ph = phy + (size_t)(p.ky0 + j) * (2 * NDY);
+        T rr = T(0), ii = T(0), ri = T(0), ir = T(0);
 #pragma unroll
         for (int m = 0; m < NB; ++m) {
-          const c2<T> P = sP[j][m][xo], Wv = sW[j][m][yo];
-          cfma(M, cmake(P.re, P.im), cmake(Wv.re, Wv.im));
+          const T pr = P[m * NO2], pi = P[m * NO2 + 1], wr = W[m * NO2], wi = W[m * NO2 + 1];
+          rr = fma(pr, wr, rr);
+          ii = fma(pi, wi, ii);
+          ri = fma(pr, wi, ri);
+          ir = fma(pi, wr, ir);
         }
+        const cx<T> M = cmake(fma(-sxy, ii, rr), fma(sy, ri, sx * ir));
         S.re += M.re;
         S.im += M.im;
 #pragma unroll
@@ -237,27 +275,33 @@ __global__ __launch_bounds__(NTHR) void loop_gen_kernel(const T *__restrict__ ba
           B[dy].im = fma(sn, M.im, B[dy].im);
         }
       }
-    }
-    // row transform at +dy: A + iB, at -dy: A - iB; then the kx phase,
-    // one |dx| at a time
+      if (p.ky0 + KT >= Lf) {
+        // row transform at +dy: A + iB, at -dy: A - iB; then the kx phase,
+        // one |dx| at a time
 #pragma unroll
-    for (int adx = 0; adx <= NDY; ++adx) {
-      const int jj = (kx * adx) % Lf;
-      const cx<T> p = cmake((T)tw[2 * jj], (T)tw[2 * jj + 1]);
+        for (int adx = 0; adx <= NDY; ++adx) {
+          const int jj = (p.kx * adx) % Lf;
+          const cx<T> f = cmake((T)tw[2 * jj], (T)tw[2 * jj + 1]);
 #pragma unroll
-      for (int i = 0; i < NPT; ++i) {
-        const int dx = SH::dx(i), dy = SH::dy(i);
-        if ((dx < 0 ? -dx : dx) != adx) continue;
-        cx<T> Yv;
-        if (dy == 0) {
-          Yv = S;
-        } else {
-          const cx<T> Av = A[(dy > 0 ? dy : -dy) - 1], Bv = B[(dy > 0 ? dy : -dy) - 1];
-          Yv = dy > 0 ? cmake(Av.re - Bv.im, Av.im + Bv.re) : cmake(Av.re + Bv.im, Av.im - Bv.re);
+          for (int i = 0; i < NPT; ++i) {
+            const int dx = SH::dx(i), dy = SH::dy(i);
+            if ((dx < 0 ? -dx : dx) != adx) continue;
+            cx<T> Yv;
+            if (dy == 0) {
+              Yv = S;
+            } else {
+              const cx<T> Av = A[(dy > 0 ? dy : -dy) - 1], Bv = B[(dy > 0 ? dy : -dy) - 1];
+              Yv = dy > 0 ? cmake(Av.re - Bv.im, Av.im + Bv.re) : cmake(Av.re + Bv.im, Av.im - Bv.re);
+            }
+            cfma(Z[i], dx < 0 ? cmake(f.re, -f.im) : f, Yv);
+          }
         }
-        cfma(Z[i], dx < 0 ? cmake(p.re, -p.im) : p, Yv);
+        S = cmake(T(0), T(0));
+#pragma unroll
+        for (int j = 0; j < NDY; ++j) A[j] = B[j] = cmake(T(0), T(0));
       }
     }
+    __syncthreads();
   }
   if (!active) return;
   // partial[item][kx chunk][dx][dy + NDY][tau] for dx >= 0; the partner entry from

@@ -84,7 +84,8 @@ constexpr int small_nD(int nt) { return nt == 1 ? 13 : nt == 2 ? 57 : 81; }
 constexpr int small_waves(int nt) { return nt < 3 ? 4 : 8; }
 
 struct BundleSmall {
-  const double *V[2], *Lc[2];
+  const void *V[2];
+  const double *Lc[2];
   double *out[2];
   double f[2];
 };
@@ -102,12 +103,9 @@ __global__ __launch_bounds__(64 * small_waves(NT)) void bundle_small_kernel(int 
   __shared__ int sD[16 * NT * NT];
   const int q = blockIdx.x, ch = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int BB = B * B;
-  const double2 *Vq = (const double2 *)p.V[ch] + (size_t)q * BB;
+  const C2<T> *Vq = (const C2<T> *)p.V[ch] + (size_t)q * BB;
   const double2 *Lq = (const double2 *)p.Lc[ch] + (size_t)q * nD * 16;
-  for (int i = tid; i < BB; i += NTHR) {
-    const double2 v = Vq[i];
-    sV[(i / B) * LD + i % B] = C2<T>{(T)v.x, (T)v.y};
-  }
+  for (int i = tid; i < BB; i += NTHR) sV[(i / B) * LD + i % B] = Vq[i];
   for (int i = tid; i < nD * 16; i += NTHR) {
     const double2 v = Lq[i];
     sL[i] = C2<T>{(T)v.x, (T)v.y};
@@ -195,18 +193,18 @@ __device__ inline C2<float> ld_t(i32x4 r, unsigned off, float) {
 }  // namespace
 
 // AL: tmp[q] = L[q] V[q], A = L expanded from its compact form (FP64), B = V
-// (FP64), C in the arithmetic type; else out[q] = alpha V[q] tmp[q].
+// and C in the arithmetic type; else out[q] = alpha V[q] tmp[q].
 // Vector instructions beside the products cost nearly their full time on
 // gfx950, so a loading thread takes six values in a row of memory (A: half a row
 // of the panel) or sixteen apart (B) behind one offset, which one addition per
 // step advances.  t2g 10 x 10, 13 form factors (B = 468, 100 q): 5.0-5.2 ms for
 // the two products of both channels in FP64 against 10.2 on the vector units,
 // where the rate of a large FP64 product here (70 TFLOP/s) allows 4.7; FP32, 11 x 11,
-// 9 form factors: 3.2 -> 1.67 ms.
+// 9 form factors: 3.2 -> 1.67 ms, with V in FP32 from the projections 1.54.
 template <typename T, bool AL, int NO2>
 __global__ __launch_bounds__(256, 2) void bundle_gemm_kernel(int B, int n_ff, int nD, int n_q,
                                                              const int *__restrict__ didx,
-                                                             const double2 *__restrict__ A,
+                                                             const void *__restrict__ Av,
                                                              const void *__restrict__ Bv, double alpha,
                                                              void *__restrict__ Cv) {
   __shared__ C2<T> sA[2][TK * TLD], sB[2][TK * TLD];
@@ -219,10 +217,10 @@ __global__ __launch_bounds__(256, 2) void bundle_gemm_kernel(int B, int n_ff, in
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const size_t BB = (size_t)B * B;
   constexpr int no4 = NO2 * NO2;
-  constexpr unsigned BSZ = AL ? 16 : (unsigned)sizeof(C2<T>);  // bytes per element of the right factor
-  const auto ra = AL ? bundle_rsrc(A + (size_t)q * nD * no4, (unsigned)nD * no4 * 16u)
-                     : bundle_rsrc(A + (size_t)q * BB, (unsigned)BB * 16u);
-  const auto rb = bundle_rsrc((const char *)Bv + (size_t)q * BB * BSZ, (unsigned)BB * BSZ);
+  constexpr unsigned SZ = (unsigned)sizeof(C2<T>), ASZ = AL ? 16 : SZ;  // bytes per element: L FP64, V and tmp in T
+  const auto ra = AL ? bundle_rsrc((const double2 *)Av + (size_t)q * nD * no4, (unsigned)nD * no4 * 16u)
+                     : bundle_rsrc((const C2<T> *)Av + (size_t)q * BB, (unsigned)BB * SZ);
+  const auto rb = bundle_rsrc((const C2<T> *)Bv + (size_t)q * BB, (unsigned)BB * SZ);
   const int wi = (wv >> 1) * 48, wj = (wv & 1) * 48;
   const bool busy = i0 + wi < B && j0 + wj < B;
   // loading threads: A row i0 + tid / 2, K 6 (tid % 2) + n; B row tid / 16, columns j0 + tid % 16 + 16 n
@@ -233,8 +231,8 @@ __global__ __launch_bounds__(256, 2) void bundle_gemm_kernel(int B, int n_ff, in
     for (int e = tid; e < n_ff * n_ff; e += 256) sD[e] = didx[e];
     __syncthreads();
   }
-  unsigned ao = 0, bo = ((unsigned)bk * B + j0 + bj) * BSZ;
-  if (!AL) ao = ((unsigned)i * B + ak) * 16u;
+  unsigned ao = 0, bo = ((unsigned)bk * B + j0 + bj) * SZ;
+  if (!AL) ao = ((unsigned)i * B + ak) * SZ;
   C2<T> fa[TH], fb[TH];
   auto fetch = [&](int k0) {
     if constexpr (AL && NO2 == 36) {
@@ -250,13 +248,12 @@ __global__ __launch_bounds__(256, 2) void bundle_gemm_kernel(int B, int n_ff, in
         const bool in = i < B && k < B;
         const unsigned d = in ? (unsigned)sD[(i / NO2) * n_ff + k / NO2] : 0u;
         fa[n] = ld_f64<T>(ra, in ? (d * no4 + (unsigned)(i % NO2) * NO2 + (unsigned)(k % NO2)) * 16u : 0xfffff000u);
-      } else {
+      } else if constexpr (AL) {
         fa[n] = ld_f64<T>(ra, ao + 16u * n);
+      } else {
+        fa[n] = ld_t(ra, ao + ASZ * n, T(0));
       }
-      if constexpr (AL)
-        fb[n] = ld_f64<T>(rb, bo + 256u * n);
-      else
-        fb[n] = ld_t(rb, bo + 16u * BSZ * n, T(0));
+      fb[n] = ld_t(rb, bo + 16u * SZ * n, T(0));
     }
     // B not a multiple of 12 (two spin-orbitals): the row part past it is the next row's
     if constexpr (!AL && NO2 != 36) {
@@ -264,8 +261,8 @@ __global__ __launch_bounds__(256, 2) void bundle_gemm_kernel(int B, int n_ff, in
       for (int n = 0; n < TH; ++n)
         if (k0 + ak + n >= B) fa[n] = C2<T>{T(0), T(0)};
     }
-    if (!AL) ao += 16u * TK;
-    bo += (unsigned)TK * B * BSZ;
+    if (!AL) ao += SZ * TK;
+    bo += (unsigned)TK * B * SZ;
   };
   CAcc<T> acc[3][3];
 #pragma unroll
@@ -336,15 +333,15 @@ static hipError_t launch_small(int n_ff, int B, int nD, int n_q, const int *didx
 }
 
 template <typename T, int NO2>
-static hipError_t launch_gemm(int n_ff, int B, int nD, int n_q, const int *didx, const double *V,
+static hipError_t launch_gemm(int n_ff, int B, int nD, int n_q, const int *didx, const void *V,
                               const double *Lc, double factor, double *out, double *tmp, hipStream_t st) {
   const int nt = (B + TB - 1) / TB;
   const long long nb = 8LL * nt * nt * ((n_q + 7) / 8);
   if (nb > 0x7fffffffLL) return hipErrorInvalidValue;
   hipLaunchKernelGGL((bundle_gemm_kernel<T, true, NO2>), dim3((unsigned)nb), dim3(256), 0, st, B, n_ff, nD, n_q, didx,
-                     (const double2 *)Lc, V, 1.0, tmp);
+                     Lc, V, 1.0, tmp);
   hipLaunchKernelGGL((bundle_gemm_kernel<T, false, NO2>), dim3((unsigned)nb), dim3(256), 0, st, B, n_ff, nD, n_q, didx,
-                     (const double2 *)V, tmp, factor, out);
+                     V, tmp, factor, out);
   return hipGetLastError();
 }
 
@@ -366,7 +363,8 @@ hipError_t launch_bundle(int prec, int n_o, int n_ff, int B, int nD, int n_q, co
   if (!tmp) return hipErrorInvalidValue;
   if (n_ff > 25 || (n_o != 2 && n_o != 6)) return hipErrorInvalidValue;
   for (int c = 0; c < n_ch; ++c) {
-    const double *V = a[c].V, *Lc = a[c].Lc;
+    const void *V = a[c].V;
+    const double *Lc = a[c].Lc;
     double *out = a[c].out;
     const double f = a[c].f;
     const hipError_t e =

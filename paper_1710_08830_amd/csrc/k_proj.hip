@@ -233,8 +233,8 @@ __device__ inline double2 gather_one(const GatherTables &t, const int *grid, int
 }
 
 // VX(qx, qy)[e] = X[e] + X[V0][e] + sum_rho e^{iq.rho} G_X(rho)[e]; G gathered
-// from X(rho) (SRC 0, 1) or given (SRC 2); V in FP64 or for SRC 1 in split planes,
-// the operands of the BF16 bundle products.  The element blocks run in reverse: the
+// from X(rho) or given (SRC 2); V in FP64, or in the form of the bundle products
+// that read it: SRC 1 split planes of BF16, SRC 3 FP32.  The element blocks run in reverse: the
 // last ones that ft read are still in the last-level cache.
 template <int EW, int NP, int SRC>
 __global__ __launch_bounds__(NTHR) void assemble_kernel(int BB, int Lq, int nD, int nw, int parts,
@@ -277,6 +277,7 @@ __global__ __launch_bounds__(NTHR) void assemble_kernel(int BB, int Lq, int nD, 
   const double2 v0 = (w == 0 ? v0p : v0c)[ec];
   const double2 *X = (w == 0 ? P : C) + ec;
   double2 *V = (double2 *)(w == 0 ? VP : VC) + ec;
+  float2 *F = (float2 *)(w == 0 ? VP : VC) + ec;
   unsigned short *S = (unsigned short *)(w == 0 ? VP : VC) + (ec & ~3) + (size_t)(el & 3) * BB;  // BB a multiple of four
   const bool valid = e < BB;
   for (int unit = g; unit < Lq * parts; unit += NG) {
@@ -334,6 +335,8 @@ __global__ __launch_bounds__(NTHR) void assemble_kernel(int BB, int Lq, int nD, 
           const unsigned re = __builtin_amdgcn_perm(w1, w0, 0x05040100), im = __builtin_amdgcn_perm(w1, w0, 0x07060302);
           const unsigned o2 = __builtin_amdgcn_mov_dpp((int)(upper ? re : im), 0x4E, 0xf, 0xf, true);  // lane ^ 2
           if (valid) *(uint2 *)(S + 4 * (base + (size_t)(q + u) * BB)) = upper ? make_uint2(o2, im) : make_uint2(re, o2);
+        } else if constexpr (SRC == 3) {
+          if (valid) F[base + (size_t)(q + u) * BB] = make_float2((float)vr, (float)vi);
         } else {
           if (valid) V[base + (size_t)(q + u) * BB] = make_double2(vr, vi);
         }
@@ -428,12 +431,13 @@ hipError_t launch_ft(const ProjArgs &a, const double *P, const double *C, double
 }
 
 hipError_t launch_assemble(const ProjArgs &a, const double *P, const double *C, const double *real,
-                           const double *v0p, const double *v0c, void *VP, void *VC, int planes, hipStream_t st) {
+                           const double *v0p, const double *v0c, void *VP, void *VC, VForm form, hipStream_t st) {
   if (!proj_ok(a)) return hipErrorInvalidValue;
   const ProjSplit sp = proj_split(a);
-#define TUFRG_AS_CALL(EW, NP)                                                             \
-  planes ? assemble_launch<EW, NP, 1>(a, sp.parts, P, C, real, v0p, v0c, VP, VC, 2, st)   \
-         : assemble_launch<EW, NP, 0>(a, sp.parts, P, C, real, v0p, v0c, VP, VC, 2, st)
+#define TUFRG_AS_CALL(EW, NP)                                                                                 \
+  form == V_PLANES ? assemble_launch<EW, NP, V_PLANES>(a, sp.parts, P, C, real, v0p, v0c, VP, VC, 2, st)    \
+  : form == V_FP32 ? assemble_launch<EW, NP, V_FP32>(a, sp.parts, P, C, real, v0p, v0c, VP, VC, 2, st)      \
+                   : assemble_launch<EW, NP, V_FP64>(a, sp.parts, P, C, real, v0p, v0c, VP, VC, 2, st)
   TUFRG_PROJ(TUFRG_AS_CALL)
 #undef TUFRG_AS_CALL
   return hipGetLastError();

@@ -133,10 +133,12 @@ struct ProjArgs {
 hipError_t launch_ft(const ProjArgs &a, const double *P, const double *C, double *real, hipStream_t st);
 // D [Nq][B][B] (layout of C) from C: D_{n1n2n3n4} = -C_{n1n2n4n3}
 hipError_t launch_channel_d(int n_o, int B, int Nq, const double *C, double *D, hipStream_t st);
-// VP, VC from the transforms P(rho), C(rho) at real: FP64, or with planes as
-// split planes [Nq][4][B][B] of BF16 (Re hi, Re lo, Im hi, Im lo; x = hi + lo)
+// VP, VC from the transforms P(rho), C(rho) at real, in the form the bundle
+// products take them: complex FP64 or FP32, or split planes [Nq][4][B][B] of BF16
+// (Re hi, Re lo, Im hi, Im lo; x = hi + lo)
+enum VForm { V_FP64 = 0, V_PLANES = 1, V_FP32 = 3 };
 hipError_t launch_assemble(const ProjArgs &a, const double *P, const double *C, const double *real,
-                           const double *v0p, const double *v0c, void *VP, void *VC, int planes, hipStream_t st);
+                           const double *v0p, const double *v0c, void *VP, void *VC, VForm form, hipStream_t st);
 // the same from the gathers G [nw][nD][B][B]; nw = 1: only VP from P and G[0]
 hipError_t launch_assemble_gathered(const ProjArgs &a, const double *P, const double *C, const double *G,
                                     const double *v0p, const double *v0c, double *VP, double *VC, hipStream_t st,
@@ -145,7 +147,8 @@ hipError_t launch_assemble_gathered(const ProjArgs &a, const double *P, const do
 // a6: bundle products  out = f * V L V  per q, L expanded from compact form, of
 // n_ch channels; bundles larger than 64 need a workspace tmp of n_q * B * B complex
 struct BundleArgs {
-  const double *V, *Lc;
+  const void *V;  // complex FP64 for prec 0, FP32 otherwise (launch_assemble)
+  const double *Lc;
   double f;
   double *out;
 };

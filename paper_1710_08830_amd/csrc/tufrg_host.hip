@@ -1327,8 +1327,8 @@ static tufrg_status surrogate_loops(tufrg_ctx *c, double lam) {
 }
 
 // projections with the buffer of the transforms given (real, [2][nD][B][B]
-// complex); planes: VP, VC as split planes of BF16
-static tufrg_status project_with(tufrg_ctx *c, const double *P, const double *C, double *VP, double *VC, int planes,
+// complex) and the form of VP, VC
+static tufrg_status project_with(tufrg_ctx *c, const double *P, const double *C, double *VP, double *VC, VForm form,
                                  double *real) {
   ProjArgs a = proj_args(c);
   HIPCHK(c, timer_mark(c, TUFRG_TIMER_PROJECT));
@@ -1345,14 +1345,14 @@ static tufrg_status project_with(tufrg_ctx *c, const double *P, const double *C,
     P = c->d_peff;
   }
   HIPCHK(c, launch_ft(a, P, C, real, c->st));
-  HIPCHK(c, launch_assemble(a, P, C, real, c->d_v0p, c->d_v0c, VP, VC, planes, c->st));
+  HIPCHK(c, launch_assemble(a, P, C, real, c->d_v0p, c->d_v0c, VP, VC, form, c->st));
   HIPCHK(c, timer_mark(c, TUFRG_TIMER_PROJECT));
   return TUFRG_OK;
 }
 
 static tufrg_status project_internal(tufrg_ctx *c, const double *P, const double *C, double *VP, double *VC,
-                                     int planes) {
-  return project_with(c, P, C, VP, VC, planes, c->d_real);
+                                     VForm form) {
+  return project_with(c, P, C, VP, VC, form, c->d_real);
 }
 
 // dP = scale VP Lpp VP, dC = 2 scale VC Lph VC; a masked channel gets zero
@@ -1383,7 +1383,7 @@ static tufrg_status rhs_products(tufrg_ctx *c, const double *P, const double *C,
   const size_t BB = (size_t)c->B * c->B;
   // mixed precision: the large bundles in BF16 split products
   const bool mx = c->prec == TUFRG_BF16X3 && c->B > 64;
-  TRY(project_internal(c, P, C, c->d_VP, c->d_VC, mx));
+  TRY(project_internal(c, P, C, c->d_VP, c->d_VC, mx ? V_PLANES : c->prec == TUFRG_FP64 ? V_FP64 : V_FP32));
   const size_t lsz = 2 * (size_t)c->Nq * c->nD * c->no4;
   HIPCHK(c, timer_mark(c, TUFRG_TIMER_BUNDLE));
   BundleArgs ba[2];
@@ -1582,7 +1582,7 @@ extern "C" tufrg_status tufrg_project(tufrg_ctx *c, const tufrg_c64 *P, const tu
   if (c->n_o == 1) return fail(c, TUFRG_E_UNSUPPORTED, "one-orbital contexts run the SU(2)-reduced calls");
   if (!is_device_ptr(P) || !is_device_ptr(C) || !is_device_ptr(VP) || !is_device_ptr(VC))
     return fail(c, TUFRG_E_INVAL, "P, C, VP, VC must be device pointers");
-  return project_internal(c, (const double *)P, (const double *)C, (double *)VP, (double *)VC, 0);
+  return project_internal(c, (const double *)P, (const double *)C, (double *)VP, (double *)VC, V_FP64);
 }
 
 extern "C" tufrg_status tufrg_channel_d(tufrg_ctx *c, const tufrg_c64 *C, tufrg_c64 *D) {
@@ -1613,7 +1613,7 @@ extern "C" tufrg_status tufrg_project_static(tufrg_ctx *c, const tufrg_c64 *P, c
     return fail(c, TUFRG_E_UNSUPPORTED,
                 "static scratch of 32 MiB holds 3 * 4 * n_dR * B^2 doubles at most; this setup needs " +
                     std::to_string(3 * unit * sizeof(double)) + " bytes");
-  return project_with(c, (const double *)P, (const double *)C, (double *)VP, (double *)VC, 0, scr);
+  return project_with(c, (const double *)P, (const double *)C, (double *)VP, (double *)VC, V_FP64, scr);
 }
 
 extern "C" tufrg_status tufrg_set_initial_c(tufrg_ctx *c, const tufrg_c64 *C0) {

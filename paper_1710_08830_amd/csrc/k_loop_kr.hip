@@ -27,9 +27,13 @@
 //   deep with one barrier per tile.  Two q per wave halve the LDS reads of A: at
 //   one, they (54 KB per wave and tile at 128 bytes per clock) would take longer
 //   than the products.  t2g 32 x 32 refined 16 x (512 x 512 points, 513 items a
-//   channel): 4.1 ms a channel, where the 36-coordinate kernel takes 7.4 ms.  The
-//   products are 28 % of that, the loop kernels and fragments 36 %, the LDS reads
-//   the rest: the eight waves meet at each tile's barrier and do these in turn.
+//   channel): 3.4 ms a channel, where the 36-coordinate kernel takes 7.4 ms.  The
+//   matrix cores are busy a third of that, the vector unit (loop kernels and
+//   fragments) as long; the rest is latency: two waves a SIMD at 256 registers.
+//   The energies of the next tile are loaded once those of this one are used, and
+//   the LDS reads are ordered one step ahead (4.1 -> 3.4 ms).  Waves 4..7 half a tile
+//   behind waves 0..3, so that one does products beside the other's loop kernels,
+//   took 4.8 ms.
 // loop_kr_rowsum_kernel: the kx sums with the kx phases in FP64 over the half
 //   plane of difference vectors.
 // loop_kr_finalize_kernel: back to the entries (a, b, c, d), completed by
@@ -295,11 +299,13 @@ __global__ __launch_bounds__(NTHR, 1) void loop_kr_kernel(const float *__restric
     f32x2 x[QPW][8];       // x_0^beta, x_1^beta at k' of this lane's eight ky
     f32x4 e[1 + QPW][EV];  // ek at k and at k' of ky = lane % 32
   } pt;
-  auto fetch = [&](int t) __attribute__((always_inline)) {
+  // no conditions here and in the loads of A (past the last tile: that tile
+  // again): they cost registers
+  auto fetch_e = [&](int t) __attribute__((always_inline)) {
     const int kx = kx0 + t / ntk, T = t - (t / ntk) * ntk;
     // opaque: the offsets are formed here and not kept in registers across tiles
-    int kb = min(T * KT + 8 * lg, Lf - 1), kye = min(T * KT + (lane & 31), Lf - 1);
-    asm volatile("" : "+v"(kb), "+v"(kye));
+    int kye = min(T * KT + (lane & 31), Lf - 1);
+    asm volatile("" : "+v"(kye));
 #pragma unroll
     for (int v = 0; v < EV; ++v)
       pt.e[0][v] = kr_buffer_load_v4(re, (int)(kye * EB + 16 * v), (int)((unsigned)kx * Lf * EB), 0);
@@ -309,6 +315,15 @@ __global__ __launch_bounds__(NTHR, 1) void loop_kr_kernel(const float *__restric
 #pragma unroll
       for (int v = 0; v < EV; ++v)
         pt.e[1 + j][v] = kr_buffer_load_v4(re, (int)(kpe * EB + 16 * v), (int)((unsigned)kpx * Lf * EB), 0);
+    }
+  };
+  auto fetch_x = [&](int t) __attribute__((always_inline)) {
+    const int kx = kx0 + t / ntk, T = t - (t / ntk) * ntk;
+    int kb = min(T * KT + 8 * lg, Lf - 1);
+    asm volatile("" : "+v"(kb));
+#pragma unroll
+    for (int j = 0; j < QPW; ++j) {
+      const int kpx = kprime(qfx[j], kx);
       // the k' of ky kb .. kb + 7 lie in a row of x, from its column of kb (ph) or
       // of kb + 7 (pp); those past the mesh meet zero rows of A
       const int xo = (kprime(qfy[j], kb) + (ch == 0 ? XP - 7 : XP)) * (XS * 4) + beta * 8;
@@ -318,8 +333,7 @@ __global__ __launch_bounds__(NTHR, 1) void loop_kr_kernel(const float *__restric
     }
   };
   // A operand of a tile: the wave's units into registers, then into LDS, in two
-  // halves (waves past the units repeat the last one).  No conditions here and in
-  // the fetches (past the last tile: that tile again): they cost registers.
+  // halves (waves past the units repeat the last one)
   u32x4 ar[UPH];
   auto load_a = [&](int t, int hf) __attribute__((always_inline)) {
     const u32x4 *src = apre + (size_t)(kx0 * ntk + t) * (UNITS * 64) + lane;
@@ -408,12 +422,19 @@ __global__ __launch_bounds__(NTHR, 1) void loop_kr_kernel(const float *__restric
         }
         bh[j] = __builtin_bit_cast(bf16x8, h);
         bl[j] = __builtin_bit_cast(bf16x8, l);
+        // the loop kernels of two ky before the sums of the two before
+        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          __builtin_amdgcn_sched_group_barrier(0x002, 12, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        }
         // keeps the live loop kernels and point data within the registers
         __builtin_amdgcn_sched_barrier(0);
       }
       // the point data are used up: those of the next tile arrive during the last products
       if (p == NP - 1) {
-        fetch(min(t + 1, ntile - 1));
+        fetch_x(min(t + 1, ntile - 1));
         __builtin_amdgcn_sched_barrier(0);
       }
       const u32x4 *A = &sA[bf][p * NPHI * 128 + lane];
@@ -433,8 +454,15 @@ __global__ __launch_bounds__(NTHR, 1) void loop_kr_kernel(const float *__restric
         for (int j = 0; j < QPW; ++j) acc[f][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh[j], acc[f][j], 0, 0, 0);
         ah = nh;
         al = nl;
-        __builtin_amdgcn_sched_barrier(0);
       }
+      // the reads of a row tile before the products of the one before
+      __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma unroll
+      for (int f = 0; f < NPHI; ++f) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 3 * QPW, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
       if (p == 0) {
         store_a(bf ^ 1, 0);
         load_a(min(t + 1, ntile - 1), 1);
@@ -444,7 +472,8 @@ __global__ __launch_bounds__(NTHR, 1) void loop_kr_kernel(const float *__restric
     store_a(bf ^ 1, 1);
   };
 
-  fetch(0);
+  fetch_e(0);
+  fetch_x(0);
 #pragma unroll
   for (int hf = 0; hf < 2; ++hf) {
     load_a(0, hf);
@@ -462,6 +491,8 @@ __global__ __launch_bounds__(NTHR, 1) void loop_kr_kernel(const float *__restric
       // filled during the tile
       load_a(min(t + 1, ntile - 1), 0);
       loop_kernels(t);
+      fetch_e(min(t + 1, ntile - 1));  // the energies are used up; these arrive during the products
+      __builtin_amdgcn_sched_barrier(0);
       products(t & 1, t);
       __syncthreads();
     }

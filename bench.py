@@ -16,9 +16,9 @@ HBM before the timed region.
 
 Printed: one JSON line with the headline value (loop entries/s over the whole
 step, 2 Nq B^2 per step) and compact loop entries/s, flow steps/s, the
-roofline of the loop kernel (survey's algorithmic flop count, event-timed
-inside the library over the timed region), the FP64-plain form over the first
-steps with its relative error and the speed-up of the mixed form, the
+roofline of the loop kernel (BF16X3: executed matrix-core flops, else the
+algorithmic count of the bands summed; event-timed inside the library over the
+timed region), the FP64-plain form over the first steps with its relative error and the speed-up of the mixed form, the
 surrogate-assisted form over the timed window, the two-orbital Rashba line
 (24 x 24 refined 24x, FP32) as an extra key, and a CPU baseline of the FP64
 oracle (one thread and all cores) on a bounded sample.
@@ -67,6 +67,12 @@ def mfma_flops_per_pair(ndy, n_o=6, n_b=None):
     return 3 * 2 * rows * (n_o * n_o) * n_b
 
 
+def mfma_flops_per_pair_15(ndy):
+    """The same for models with time reversal times inversion: three band pairs
+    with 15 real coordinates each, a 16-row tile per phase and a 16-column tile."""
+    return 3 * 2 * (2 * ndy + 1) * 16 * 16 * 3
+
+
 def credited_loop_flops_per_pair(n_o, ndy, n_b=None):
     """Algorithmic flops of one loop entry set per (q, k, channel) in the
     survey's count: the form-factor contraction 8 n_dRy n_o^4 with the
@@ -86,9 +92,16 @@ def _box(ff):
 # its launch shape (chunking) in tufrg_host.hip
 # the loop kernel of a workload: BF16X3 (six spin-orbitals, matrix cores),
 # two spin-orbitals, or six on the vector units
-LOOP_SOURCES = {"bf16x3": (("k_loop_rb.hip", "common.h"), ("loops_range_mfma", "ensure_apre")),
-                "no2": (("k_loop.hip", "common.h"), ("loops_range",)),
-                "gen": (("k_loop_gen.hip", "common.h"), ("loops_range",))}
+LOOP_SOURCES = {"bf16x3": (("k_loop_rb.hip", "k_loop_kr.hip", "loop_sym.h", "common.h"),
+                           ("loops_range_mfma", "ensure_apre")),
+                "no2": (("k_loop.hip", "loop_sym.h", "common.h"), ("loops_range",)),
+                "gen": (("k_loop_gen.hip", "loop_sym.h", "common.h"), ("loops_range",))}
+# name parts of the loop kernels of a precision and workload in a profile
+LOOP_KERNELS = {"bf16x3": ("loop_rb_kernel", "loop_kr_kernel"), "no2": ("loop_no2_kernel",),
+                "gen": ("loop_gen_kernel",)}
+# share of the (q, k) pairs of a channel that the kernels sum for a model with
+# time reversal (all workloads here): one of each k, q - k and of each q, -q
+SUMMED = 0.25
 
 
 def _loop_kind(workload, prec):
@@ -438,14 +451,20 @@ def six_orbital_line(T, torch, w, prec, K, W, fp64_steps=2, surrogate=True, n_ro
     # achieved rate); the same count for the bands the kernel sums beside it
     credited = credited_loop_flops_per_pair(w["n_o"], ndy)
     credited_summed = credited_loop_flops_per_pair(w["n_o"], ndy, n_b)
-    flops_step = 2.0 * Nq * Nf * credited
+    flops_step = 2.0 * Nq * Nf * SUMMED * credited
     launches = loop_n / K
     loop_step_s = loop_ms / K * 1e-3
-    achieved = flops_step / loop_step_s  # = credited flops per launch / average launch time
+    rate = flops_step / loop_step_s  # on the survey's count
+    executed = None
     if prec == "bf16x3":
+        # against the peak: what the matrix cores execute (the count above is of more
+        # work than the kernels do once bands are paired)
         bound, peak = "mfma", PEAK_BF16_MFMA
+        executed = (mfma_flops_per_pair_15(ndy) if n_b == 3 and w["n_o"] == 6
+                    else mfma_flops_per_pair(ndy, w["n_o"], n_b))
+        achieved = rate * executed / credited
     else:
-        bound, peak = "alu", PEAK_FP32_VECTOR
+        bound, peak, achieved = "alu", PEAK_FP32_VECTOR, rate * credited_summed / credited
     out = {
         "metric": METRIC, "value": entries * K / dt, "unit": "loop entries/s", "n_gpus": 1, "steps": K,
         "warmup": W, "ms_per_step": dt / K * 1e3, "higher_is_better": True, "scaling": "weak",
@@ -464,10 +483,9 @@ def six_orbital_line(T, torch, w, prec, K, W, fp64_steps=2, surrogate=True, n_ro
         "loop_entries_per_s_kernel": entries / loop_step_s,
         "roofline": {"bound": bound, "achieved": achieved / 1e12, "peak": peak / 1e12, "unit": "TFLOP/s",
                      "frac": achieved / peak, "traffic": None if moved or six_bands else _traffic(w["name"], prec),
-                     "flops_per_pair": credited, "bands_summed": n_b,
-                     "frac_with_bands_summed": (achieved * credited_summed / credited) / peak,
-                     "executed_matrix_flops_per_pair": (mfma_flops_per_pair(ndy, w["n_o"], n_b)
-                                                        if prec == "bf16x3" else None)},
+                     "share_of_pairs_summed": SUMMED, "executed_matrix_flops_per_pair": executed,
+                     "survey_flops_per_pair": credited, "survey_tflops": rate / 1e12, "bands_summed": n_b,
+                     "survey_tflops_of_bands_summed": rate * credited_summed / credited / 1e12},
         "flow_result": res,
     }
     if tuned is not None:
@@ -723,10 +741,10 @@ def two_orbital_line(T, torch, w, args, K, W, extras=True, cpu=True):
     launches = loop_n / K
     ndx, ndy = _box(w["ff"])
     if prec == "bf16x3":
-        flops_step = 2.0 * Nq * Nf * credited_loop_flops_per_pair(w["n_o"], ndy)
+        flops_step = 2.0 * Nq * Nf * SUMMED * credited_loop_flops_per_pair(w["n_o"], ndy)
         bound, peak = "mfma", PEAK_BF16_MFMA
     else:
-        flops_step = 2.0 * Nq * Nf * loop_flops_per_pair(w["n_o"], ndx, ndy, w["cutoff"] == "shell")
+        flops_step = 2.0 * Nq * Nf * SUMMED * loop_flops_per_pair(w["n_o"], ndx, ndy, w["cutoff"] == "shell")
         bound, peak = "alu", PEAK_FP32_VECTOR
     achieved = flops_step / launches / loop_avg_s
     # the committed counters were taken with the workload's own regulator
@@ -746,7 +764,8 @@ def two_orbital_line(T, torch, w, args, K, W, extras=True, cpu=True):
         "loop_launches_per_step": launches,
         "loop_entries_per_s_kernel": entries / (loop_avg_s * launches),
         "roofline": {"bound": bound, "achieved": achieved / 1e12, "peak": peak / 1e12,
-                     "unit": "TFLOP/s", "frac": achieved / peak, "traffic": traffic},
+                     "unit": "TFLOP/s", "frac": achieved / peak, "share_of_pairs_summed": SUMMED,
+                     "traffic": traffic},
     }
     if not no_extras:
         # the same steps with HIP graphs of 8 steps each (one host
@@ -812,21 +831,21 @@ def two_orbital_line(T, torch, w, args, K, W, extras=True, cpu=True):
 
 
 
-def _counter_per_dispatch(csv_path, name_part, counter):
+def _counter_per_dispatch(csv_path, name_parts, counter):
     """Per-dispatch values of one counter for the kernels whose name contains
-    name_part, from a rocprofv3 counter_collection.csv."""
+    one of name_parts, from a rocprofv3 counter_collection.csv."""
     import csv
     vals = {}
     names = set()
     with open(csv_path, newline="") as fh:
         for r in csv.DictReader(fh):
-            if r["Counter_Name"] != counter or name_part not in r["Kernel_Name"]:
+            if r["Counter_Name"] != counter or not any(p in r["Kernel_Name"] for p in name_parts):
                 continue
             d = r["Dispatch_Id"]
             vals[d] = vals.get(d, 0.0) + float(r["Counter_Value"])
             names.add(r["Kernel_Name"])
     if not vals:
-        raise RuntimeError(f"no {counter} rows for kernels matching {name_part!r} in {csv_path}")
+        raise RuntimeError(f"no {counter} rows for kernels matching {name_parts!r} in {csv_path}")
     return list(vals.values()), sorted(names)
 
 
@@ -836,15 +855,13 @@ def summarize_traffic(args):
     --calibrate-copy): KiB per dispatch of the loop kernel, each scaled by
     what the counter reads per byte of a plain 1 GiB device copy."""
     f_dir, w_dir, cf_dir, cw_dir = args.summarize_traffic
-    # the main loop kernel of the precision (two orbitals: loop_no2, six: loop_gen)
-    kname = "loop_rb_kernel" if args.prec == "bf16x3" else (
-        "loop_gen_kernel" if args.workload.startswith("t2g") else "loop_no2_kernel")
+    kname = LOOP_KERNELS[_loop_kind(args.workload, args.prec)]
     pick = lambda d, nm: os.path.join(d, nm + "_counter_collection.csv")
     fetch, names = _counter_per_dispatch(pick(f_dir, "fetch"), kname, "FETCH_SIZE")
     write, _ = _counter_per_dispatch(pick(w_dir, "write"), kname, "WRITE_SIZE")
     # the 1 GiB copies are the largest dispatches of the calibration run
-    cf, _ = _counter_per_dispatch(pick(cf_dir, "fetch"), "", "FETCH_SIZE")
-    cw, _ = _counter_per_dispatch(pick(cw_dir, "write"), "", "WRITE_SIZE")
+    cf, _ = _counter_per_dispatch(pick(cf_dir, "fetch"), ("",), "FETCH_SIZE")
+    cw, _ = _counter_per_dispatch(pick(cw_dir, "write"), ("",), "WRITE_SIZE")
     cf = sorted(cf)[-3:]
     cw = sorted(cw)[-3:]
     n = 1 << 30
@@ -909,14 +926,13 @@ def summarize_trace(args):
 def summarize_counters(args):
     """A markdown table of the SQ counters of a rocprofv3 --pmc run, summed
     over the dispatches of the loop kernel and divided by their number, with
-    the instruction counts per wave and tile of 16 ky (BF16X3 loop kernel)."""
+    the instruction counts per wave and tile of 16 ky (BF16X3 kernel in 36 coordinates)."""
     csv_path, cmd, out_path = args.summarize_counters
-    kname = "loop_rb_kernel" if args.prec == "bf16x3" else (
-        "loop_gen_kernel" if args.workload.startswith("t2g") else "loop_no2_kernel")
+    kname = LOOP_KERNELS[_loop_kind(args.workload, args.prec)]
     import csv
     names, disp = set(), set()
     with open(csv_path, newline="") as fh:
-        rows = [r for r in csv.DictReader(fh) if kname in r["Kernel_Name"]]
+        rows = [r for r in csv.DictReader(fh) if any(p in r["Kernel_Name"] for p in kname)]
     if not rows:
         raise RuntimeError(f"no rows for kernels matching {kname!r} in {csv_path}")
     tot = {}
@@ -930,7 +946,7 @@ def summarize_counters(args):
              "| counter | per dispatch |", "|---|---|"]
     for k in sorted(tot):
         lines.append(f"| {k} | {tot[k] / n:.4g} |")
-    if args.prec == "bf16x3" and "SQ_WAVES" in tot:
+    if any("loop_rb_kernel" in nm for nm in names) and "SQ_WAVES" in tot:
         from synth import workload
         w = workload(args.workload)
         lf = w["Lq"] * w["n_ref"]

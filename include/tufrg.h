@@ -288,8 +288,9 @@ tufrg_status tufrg_autotune(tufrg_ctx *ctx, double lambda, const char *cache_pat
  * every k of the fine mesh (time reversal with inversion symmetry; checked at
  * creation: splittings at most 1e-10 max(1, max |e|)), the loops sum each
  * degenerate pair first: three energies and three summed projectors (BF16X3:
- * also L_f even; half the matrix-core work per k; FP32 and FP64: half the
- * band sum and a quarter of the W build per k).  Exact for exactly degenerate
+ * also L_f even; half the matrix-core work per k, a tenth where H(k) = T H(k)*
+ * T^t with T = i sigma_y in each orbital; FP32 and FP64: half the band sum and
+ * a quarter of the W build per k).  Exact for exactly degenerate
  * bands; the eigensolver's splittings (about 1e-14) change the loops far
  * below the rounding of FP32 and BF16X3 and within 1e-11 in FP64.
  * enable = 1 (the default) uses the pairs where they were found, 0 always

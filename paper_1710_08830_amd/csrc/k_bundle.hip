@@ -94,8 +94,9 @@ struct BundleSmall {
 // B / 4 K steps: B is a multiple of 4 (4 n_ff for two spin-orbitals).  Rows and
 // columns past B hold whatever is in LDS: they reach only results past B.
 template <typename T, int NT>
-__global__ __launch_bounds__(64 * small_waves(NT)) void bundle_small_kernel(int n_ff, int B, int nD, const int *__restrict__ didx,
-                                                           BundleSmall p) {
+__global__ __launch_bounds__(64 * small_waves(NT)) void bundle_small_kernel(int n_ff, int B, int nD,
+                                                                            const int *__restrict__ didx,
+                                                                            BundleSmall p) {
   constexpr int LD = 16 * NT + 1, NW = small_waves(NT), NTHR = 64 * NW;
   constexpr int NTW = (NT * NT + NW - 1) / NW;  // LD: row stride (odd: banks spread); tiles per wave
   // FP64, NT = 4: 154 of the 160 KB

@@ -292,6 +292,12 @@ __device__ inline void loop_no2_body(const T *__restrict__ ekv, const T *__restr
 // share rows in its L2.
 constexpr int N_XCD = 8;
 
+// waves per SIMD that the sums of a lane leave room for
+template <typename T, int NDX>
+constexpr int no2_waves() {
+  return NDX > 3 ? (sizeof(T) == 8 ? 1 : 2) : (sizeof(T) == 8 ? 2 : 4);
+}
+
 template <typename T>
 struct loop_waves {
   static constexpr int v = (sizeof(T) == 4) ? 4 : 2;
@@ -458,7 +464,9 @@ __device__ __forceinline__ void loop_no2_item(const T *__restrict__ ekv, const T
 }
 
 template <typename T, int NDX, int NDY, int SCHEME, int QW>
-__global__ __launch_bounds__(64 * QW, (NDX > 3 ? (sizeof(T) == 8 ? 1 : 2) : (sizeof(T) == 8 ? 2 : 4))) void loop_no2_kernel(const T *__restrict__ ekv, const T *__restrict__ pi4, const T *__restrict__ cvp,
+__global__ __launch_bounds__(64 * QW, (no2_waves<T, NDX>())) void loop_no2_kernel(const T *__restrict__ ekv,
+                                                           const T *__restrict__ pi4,
+                                                           const T *__restrict__ cvp,
                                                            const double *__restrict__ tw, const T *__restrict__ twk,
                                                            int Lq, int n_ref, int Lf, int nkyb, int kxper, int nparts,
                                                            int half, const int *__restrict__ items, int n_pp,
@@ -479,7 +487,8 @@ __global__ __launch_bounds__(64 * QW, (NDX > 3 ? (sizeof(T) == 8 ? 1 : 2) : (siz
 // channels over all its items; the same work items and partial sums as its
 // own launch.
 template <typename T, int NDX, int NDY, int SCHEME, int QW>
-__global__ __launch_bounds__(64 * QW, (NDX > 3 ? (sizeof(T) == 8 ? 1 : 2) : (sizeof(T) == 8 ? 2 : 4))) void loop_no2_batch_kernel(const No2Inst *__restrict__ inst, int n_inst, int n_work) {
+__global__ __launch_bounds__(64 * QW, (no2_waves<T, NDX>())) void loop_no2_batch_kernel(const No2Inst *__restrict__ inst,
+                                                                               int n_inst, int n_work) {
   __shared__ T bufs[QW][32][LDB];
   __shared__ T phy[2 * NDY + 1][64];
   const int xcd = blockIdx.x % N_XCD, slot = blockIdx.x / N_XCD;
@@ -634,7 +643,8 @@ hipError_t launch_loop(const LoopArgs &a, hipStream_t st) {
 // completed from the reversed entry; the value goes to the item's own slot of
 // the output and, transformed, to that of -q.
 template <typename PT, int QS>
-__global__ __launch_bounds__(256) void loop_finalize_kernel(LoopSym sy, int n_o, int n_items, int nparts, int valid_pp, int valid_ph, int ndx,
+__global__ __launch_bounds__(256) void loop_finalize_kernel(LoopSym sy, int n_o, int n_items, int nparts,
+                                                            int valid_pp, int valid_ph, int ndx,
                                      int ndy, int nD, int ch_first, int n_q_out, const int *__restrict__ items,
                                      const int2 *__restrict__ dst, const int *__restrict__ dlist, double inv_nf,
                                      const PT *__restrict__ partial, double *__restrict__ compact) {

@@ -130,7 +130,8 @@ __device__ __forceinline__ void gemm_tile(const GemmF32 &p, int b, float *smem, 
     const int ao = so + bf * BUF + (lane >> 5) * GPA + (lane & 31);
     const int bo = so + bf * BUF + GK * GPA + (lane >> 5) * GPB + wn + (lane & 31);
 #pragma unroll
-    for (int k = 0; k < GK; k += 2) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(smem[ao + k * GPA], smem[bo + k * GPB], acc, 0, 0, 0);
+    for (int k = 0; k < GK; k += 2)
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(smem[ao + k * GPA], smem[bo + k * GPB], acc, 0, 0, 0);
     if (cs && t < GM) {
 #pragma unroll
       for (int k = 0; k < GK; ++k) colsum += smem[so + bf * BUF + k * GPA + t];

@@ -315,11 +315,11 @@ static int kx_chunks(const tufrg_ctx *c, int kxper) {
 // kx chunks of the vector loop kernels: the work (waves for one and two
 // orbitals, workgroups for six) runs in rounds of what is resident at once, half
 // a round idle at the end of several, and each chunk costs its rows and the
-// end's contraction of the ky phases, as long as about 8 rows (six orbitals:
+// end's contraction of the ky phases, set to 8 rows (about 7; six orbitals:
 // the write of the partial sums).  The shortest time is taken; two orbitals:
 // among chunks whose k rows take at most about 3 MB of an XCD's 4 MB L2, since
-// each XCD sweeps one chunk over many q.  rashba_s9_L24 FP32 (5 chunks): 0.56 ms
-// against 1.11 (2 uneven ones), 0.77 (1) and 0.66 ms (8).
+// each XCD sweeps one chunk over many q.  rashba_s9_L24 FP32 (4 chunks): 476 us,
+// 2: 520, 3: 475, 6: 500, 8: 523.
 static int default_kx_chunks(const tufrg_ctx *c) {
   const int rows = loop_rows_max(c->Lf, 1);
   const bool f64 = c->prec == TUFRG_FP64, wide = c->ndx > 3;
@@ -719,7 +719,9 @@ extern "C" tufrg_status tufrg_create(const tufrg_model *m, const tufrg_setup *s,
     for (int i = 0; i < c->nD; ++i)
       if (std::find(ys.begin(), ys.end(), c->dlist[2 * i + 1]) == ys.end()) ys.push_back(c->dlist[2 * i + 1]);
     // 0, then the pairs +-y (D = S - S holds both)
-    std::sort(ys.begin(), ys.end(), [](int a, int b) { return std::abs(a) != std::abs(b) ? std::abs(a) < std::abs(b) : a > b; });
+    std::sort(ys.begin(), ys.end(), [](int a, int b) {
+      return std::abs(a) != std::abs(b) ? std::abs(a) < std::abs(b) : a > b;
+    });
     if (c->ny != (int)ys.size() || c->ny > 9) {  // D lies in [-4, 4]^2 for form factors with |R| <= 2
       c->err = "more than nine distinct rho_y in D";
       return bail(TUFRG_E_UNSUPPORTED);

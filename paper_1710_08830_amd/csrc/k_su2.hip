@@ -71,11 +71,24 @@ __global__ __launch_bounds__(64 * QW) void loop1_kernel(int Lq, int n_ref, int L
     A[d] = Bv[d] = 0.0;
     jd[d] = (int)(((long long)kx * (d + 1)) % Lf);
   }
+  // the values of a row one row ahead (the branches of the divided difference keep
+  // the compiler from it): 24 x 24 refined 12 x, 9 form factors, 101 -> 83 us
+  struct Row {
+    double ek, ep, vk, vp;
+  };
+  auto load = [&](int x, int xp) __attribute__((always_inline)) {
+    const size_t o = (size_t)x * Lf, op = (size_t)xp * Lf;
+    return Row{e[o + ky], e[op + kpy], kv[o + ky], kv[op + kpy]};
+  };
+  Row next = load(kx, kpx);
 #pragma unroll 2
   for (int i = 0; i < nx; ++i) {
-    const double *ek = e + (size_t)kx * Lf, *ep = e + (size_t)kpx * Lf;
-    const double *vk = kv + (size_t)kx * Lf, *vp = kv + (size_t)kpx * Lf;
-    double l = sg * divided_difference(ek[ky], -sg * ep[kpy], vk[ky], -sg * vp[kpy], lam, scheme, deriv);
+    const Row c = next;
+    const int kn = kx + 1 == Lf ? 0 : kx + 1;
+    kpx += ch == 0 ? -1 : 1;
+    kpx = kpx < 0 ? kpx + Lf : (kpx >= Lf ? kpx - Lf : kpx);
+    next = load(kn, kpx);
+    double l = sg * divided_difference(c.ek, -sg * c.ep, c.vk, -sg * c.vp, lam, scheme, deriv);
     if (kx == hx0 || kx == hx1) l *= 0.5;
     S += l;
 #pragma unroll
@@ -85,9 +98,7 @@ __global__ __launch_bounds__(64 * QW) void loop1_kernel(int Lq, int n_ref, int L
       A[d] = fma(tw[2 * j], l, A[d]);  // e^{-i kx dx}, wave-uniform
       Bv[d] = fma(tw[2 * j + 1], l, Bv[d]);
     }
-    kx = kx + 1 == Lf ? 0 : kx + 1;
-    kpx += ch == 0 ? -1 : 1;
-    kpx = kpx < 0 ? kpx + Lf : (kpx >= Lf ? kpx - Lf : kpx);
+    kx = kn;
   }
   const double on = ky_raw < Lf ? 1.0 : 0.0;
   buf[wv][0][lane] = on * S;

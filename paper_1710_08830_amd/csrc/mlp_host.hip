@@ -92,15 +92,17 @@ bool on_device(const void *p) {
     }                                                                              \
   } while (0)
 
-// K ranges of the weight gradient (out x in, summed over rows): enough
-// workgroups to fill the chip, none with fewer than 256 rows (a 256 x 256 layer
-// has 32 tiles: 8 ranges at 2048 rows); more rows never take fewer ranges, so
-// the workspace for the most rows serves all
+// K ranges of the weight gradient (out x in, summed over rows): as many
+// workgroups as the chip holds (three a CU), none with fewer than 256 rows (a 256 x
+// 256 layer has 32 tiles: 8 ranges at 2048 rows; 256 x 2592 has 324: two, with
+// which and the data gradient first its backward products take 76 us, with one
+// range 87); more rows never take fewer ranges, so the workspace for the most
+// rows serves all
 int weight_splits(int out, int in, int rows) {
   GemmF32 g;
   g.M = out;
   g.N = in;
-  return std::max(1, std::min({256 / std::max(1, gemm_f32_blocks(g)), rows / 256, 8}));
+  return std::max(1, std::min({768 / std::max(1, gemm_f32_blocks(g)), rows / 256, 8}));
 }
 
 // workspaces for chunks of up to rows rows

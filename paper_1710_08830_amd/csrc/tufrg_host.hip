@@ -42,7 +42,8 @@ struct tufrg_ctx {
   hipStream_t st = nullptr;
   int device = 0;  // the device current at creation
   int n_o = 0, n_ff = 0, B = 0, Lq = 0, n_ref = 0, Lf = 0, Nq = 0, Nf = 0, no2 = 0, no4 = 0;
-  int nD = 0, ndx = 0, ndy = 0, scheme = 0, prec = 0, nkyb = 0, nkxc = 0;
+  int nD = 0, ndx = 0, ndy = 0, scheme = 0, prec = 0, nkyb = 0;
+  int kxper = 0, nkxc = 0;  // kx rows per chunk of the vector loop kernels; chunks of the longest item
   // loop sums (loop_sym.h): time reversal of the model, channels whose kx rows
   // are halved, and the items (channel, coarse q) of a full evaluation with
   // their output slots; n_item[ch] of channel 0, then of channel 1
@@ -301,18 +302,21 @@ static int time_reversal(const tufrg_model *m) {
   return 0;
 }
 
-// Rows per chunk for n kx chunks of the longest item, and back.  A channel whose
-// rows are not halved has twice the chunks, so that the halved rows (Lf / 2 + 1)
-// of the other divide evenly too.
-static int kx_rows_per_chunk(const tufrg_ctx *c, int n) {
-  const int rows = loop_rows_max(c->Lf, 1), m = c->half == 3 ? n : (n + 1) / 2;
+// Rows per chunk that divide the halved rows (Lf / 2 + 1) into m even chunks; a
+// channel whose rows are not halved has chunks of the same rows, about twice as
+// many.  The rows are what a context keeps: they do not follow from the number of
+// chunks of the longest item.
+static int even_kx_rows(const tufrg_ctx *c, int m) {
+  const int rows = loop_rows_max(c->Lf, 1);
+  m = std::max(1, std::min(m, rows));
   return (rows + m - 1) / m;
 }
+// chunks of the longest item
 static int kx_chunks(const tufrg_ctx *c, int kxper) {
   return (loop_rows_max(c->Lf, c->half == 3) + kxper - 1) / kxper;
 }
 
-// kx chunks of the vector loop kernels: the work (waves for one and two
+// Rows per kx chunk of the vector loop kernels: the work (waves for one and two
 // orbitals, workgroups for six) runs in rounds of what is resident at once, half
 // a round idle at the end of several, and each chunk costs its rows and the
 // end's contraction of the ky phases, set to 8 rows (about 7; six orbitals:
@@ -320,7 +324,7 @@ static int kx_chunks(const tufrg_ctx *c, int kxper) {
 // among chunks whose k rows take at most about 3 MB of an XCD's 4 MB L2, since
 // each XCD sweeps one chunk over many q.  rashba_s9_L24 FP32 (4 chunks): 476 us,
 // 2: 520, 3: 475, 6: 500, 8: 523.
-static int default_kx_chunks(const tufrg_ctx *c) {
+static int default_kx_rows(const tufrg_ctx *c) {
   const int rows = loop_rows_max(c->Lf, 1);
   const bool f64 = c->prec == TUFRG_FP64, wide = c->ndx > 3;
   long long slots, items[2], end = 8;
@@ -337,7 +341,7 @@ static int default_kx_chunks(const tufrg_ctx *c) {
   int best = rows;
   double best_t = INFINITY;
   for (int m = 1; m <= rows; ++m) {
-    const int per = (rows + m - 1) / m;
+    const int per = even_kx_rows(c, m);
     if (per > l2 && per > 4) continue;
     if (per < 4 && m > 1) break;
     double w = 0.0;
@@ -349,7 +353,7 @@ static int default_kx_chunks(const tufrg_ctx *c) {
       best = per;
     }
   }
-  return kx_chunks(c, best);
+  return best;
 }
 
 // Time reversal times inversion, H(k) = T H(k)^* T^t with T = i sigma_y in each
@@ -510,12 +514,12 @@ extern "C" tufrg_status tufrg_create(const tufrg_model *m, const tufrg_setup *s,
   }
   if (c->n_o == 1 || c->n_o == 2) {
     c->nkyb = (c->Lf + 63) / 64;
-    c->nkxc = default_kx_chunks(c);
+    c->kxper = default_kx_rows(c);
   } else {
     // the multi-orbital loop kernel sums a kx chunk of an item in one workgroup
     // (FP64: two), one at a time per CU
     c->nkyb = 1;
-    c->nkxc = c->prec == TUFRG_BF16X3 ? 1 : default_kx_chunks(c);
+    c->kxper = c->prec == TUFRG_BF16X3 ? c->Lf : default_kx_rows(c);
     if (!(c->ndx == 5 && c->ndy == 4) && !(c->ndx == 3 && c->ndy == 2)) {
       c->ndx = 3;
       c->ndy = 2;
@@ -535,6 +539,7 @@ extern "C" tufrg_status tufrg_create(const tufrg_model *m, const tufrg_setup *s,
       }
     }
   }
+  c->nkxc = kx_chunks(c, c->kxper);
   {
     // distinct rho_y over D (the projections' qy phases); D lies in [-4, 4]^2
     // for form factors with |R| <= 2
@@ -851,7 +856,7 @@ static LoopArgs loop_args(tufrg_ctx *c, double lam, int deriv, const LoopItems &
   a.ndx = c->ndx;
   a.ndy = c->ndy;
   a.nkyb = c->nkyb;
-  a.kxper = kx_rows_per_chunk(c, c->nkxc);
+  a.kxper = c->kxper;
   a.nparts = c->nkyb * c->nkxc;
   a.kxr = c->mfma_kxr;
   a.pair = pairs_active(c);
@@ -1052,12 +1057,12 @@ static void dfree(tufrg_ctx *c, void *p) {
   (void)hipFree(p);
 }
 
-// n kx chunks of the two-orbital loop kernel as they divide its rows
-static int normalized_kx_chunks(const tufrg_ctx *c, int n) {
-  return kx_chunks(c, kx_rows_per_chunk(c, std::max(1, std::min(n, c->Lf))));
-}
-
-static tufrg_status set_kx_chunks(tufrg_ctx *c, int n) {
+// per rows per kx chunk of the two-orbital loop kernel, as even chunks of the halved rows
+static tufrg_status set_kx_rows(tufrg_ctx *c, int per) {
+  const int rows = loop_rows_max(c->Lf, 1);
+  per = std::max(1, std::min(per, rows));
+  per = even_kx_rows(c, (rows + per - 1) / per);
+  const int n = kx_chunks(c, per);
   const size_t need = 2 * c->items.size() * c->nkyb * n * c->ndx * (2 * c->ndy + 1) * c->no4;
   if (need > c->partial_cap) {
     HIPCHK(c, hipStreamSynchronize(c->st));
@@ -1067,6 +1072,7 @@ static tufrg_status set_kx_chunks(tufrg_ctx *c, int n) {
     TRY(dalloc(c, &c->d_partial, need));
     c->partial_cap = need;
   }
+  c->kxper = per;
   c->nkxc = n;
   return TUFRG_OK;
 }
@@ -1128,9 +1134,9 @@ extern "C" tufrg_status tufrg_autotune(tufrg_ctx *c, double lambda, const char *
   res->mfma_kx_rows = c->mfma_kxr;
   if (!no2 && !mx) return TUFRG_OK;  // one workgroup per (q, channel): no launch shape to tune
   res->tunable = 1;
-  const char *pname = no2 ? "loop_kx_chunks" : "mfma_kx_rows";
+  const char *pname = no2 ? "loop_kx_rows" : "mfma_kx_rows";
   auto apply = [&](int v) -> tufrg_status {
-    if (no2) return set_kx_chunks(c, normalized_kx_chunks(c, v));
+    if (no2) return set_kx_rows(c, v);
     c->mfma_kxr = std::max(1, std::min(v, 8));
     return TUFRG_OK;
   };
@@ -1153,12 +1159,14 @@ extern "C" tufrg_status tufrg_autotune(tufrg_ctx *c, double lambda, const char *
   // candidates around the default: the two-orbital kernel's kx chunking (the
   // default balances filling the chip against the L2 share of a chunk), the
   // matrix-core kernel's kx rows per work item
-  const int def = no2 ? c->nkxc : c->mfma_kxr;
+  const int def = no2 ? c->kxper : c->mfma_kxr;
   std::vector<int> cand;
   if (no2) {
-    for (int v : {def, def / 2, def * 2, def * 4, 1}) {
-      const int n = normalized_kx_chunks(c, std::max(1, std::min(v, std::max(def, c->Lf / 8))));
-      if (std::find(cand.begin(), cand.end(), n) == cand.end()) cand.push_back(n);
+    // in chunks of the halved rows, of four rows or more (or the default's)
+    const int m = (loop_rows_max(c->Lf, 1) + def - 1) / def;
+    for (int v : {m, m / 2, m * 2, m * 4, 1}) {
+      const int per = even_kx_rows(c, std::max(1, std::min(v, std::max(m, c->Lf / 8))));
+      if (std::find(cand.begin(), cand.end(), per) == cand.end()) cand.push_back(per);
     }
   } else {
     for (int v : {def, 1, 2, 4})
@@ -1173,7 +1181,7 @@ extern "C" tufrg_status tufrg_autotune(tufrg_ctx *c, double lambda, const char *
     if (v == def) res->default_ms = ms;
     if (ms < best) {
       best = ms;
-      best_v = no2 ? c->nkxc : c->mfma_kxr;
+      best_v = v;
     }
   }
   TRY(apply(best_v));
@@ -1183,6 +1191,7 @@ extern "C" tufrg_status tufrg_autotune(tufrg_ctx *c, double lambda, const char *
   res->mfma_kx_rows = c->mfma_kxr;
   if (cache_path) {
     cache[key] = {{pname, (double)best_v}, {"loop_ms", best}, {"default_ms", res->default_ms}};
+    if (no2) cache[key]["loop_kx_chunks"] = c->nkxc;
     std::string err;
     if (!tune_cache_write(cache_path, cache, err)) return fail(c, TUFRG_E_INVAL, err);
   }

@@ -831,6 +831,9 @@ static int pairs_active(const tufrg_ctx *c) {
   return c->prec == TUFRG_BF16X3 ? c->Lf % 2 == 0 : 1;
 }
 
+// the kind of matrix-core loops that runs: 0 six bands, 1 pairs, 2 pairs in 15 coordinates
+static int mfma_kind(const tufrg_ctx *c) { return pairs_active(c) ? (c->kr ? 2 : 1) : 0; }
+
 // The items of one evaluation: device lists, their numbers per channel, and the
 // number of output slots per channel.
 struct LoopItems {
@@ -938,7 +941,7 @@ static void dfree(tufrg_ctx *c, void *p);
 // the matrix-core loop's A operand and buffers for the current pairing (rebuilt
 // when the pairing changed since they were made)
 static tufrg_status ensure_apre(tufrg_ctx *c) {
-  const int kind = pairs_active(c) ? (c->kr ? 2 : 1) : 0;
+  const int kind = mfma_kind(c);
   if (c->mfma_kind != kind) {
     HIPCHK(c, hipStreamSynchronize(c->st));
     dfree(c, c->d_apre);
@@ -1077,6 +1080,8 @@ static tufrg_status set_kx_rows(tufrg_ctx *c, int per) {
   return TUFRG_OK;
 }
 
+// what the time of a shape depends on: the problem, the channels whose kx rows are
+// halved, the kind of matrix-core loops
 static std::string tune_key(const tufrg_ctx *c) {
   hipDeviceProp_t prop;
   std::string arch = "unknown";
@@ -1089,9 +1094,9 @@ static std::string tune_key(const tufrg_ctx *c) {
   }
   char buf[256];
   std::snprintf(buf, sizeof(buf),
-                "%s:%dcu|n_o=%d|prec=%d|scheme=%d|Lq=%d|n_ref=%d|n_ff=%d|nD=%d|ndx=%d|ndy=%d|pairs=%d",
+                "%s:%dcu|n_o=%d|prec=%d|scheme=%d|Lq=%d|n_ref=%d|n_ff=%d|nD=%d|ndx=%d|ndy=%d|half=%d|kind=%d",
                 arch.c_str(), cus, c->n_o, c->prec, c->scheme, c->Lq, c->n_ref, c->n_ff, c->nD, c->ndx, c->ndy,
-                pairs_active(c));
+                c->half, mfma_kind(c));
   return buf;
 }
 

@@ -598,80 +598,90 @@ __global__ __launch_bounds__(256) void loop_rb_rowsum_kernel(const float *__rest
   }
 }
 
-// real-basis coordinates of the matrix entry (a, c): one (diagonal) or two
-// (real part, imaginary part times +-i) coordinates
-__device__ inline int rb_coords(int a, int c, int *alpha, double *ci) {
+// real-basis coordinates of the matrix entry (a, c): r its real part, m its
+// imaginary part times ci = +-1 (diagonal: ci = 0)
+__device__ inline void rb_coords(int a, int c, int &r, int &m, double &ci) {
   if (a == c) {
-    alpha[0] = a;
-    ci[0] = 0.0;
-    return 1;
+    r = m = a;
+    ci = 0.0;
+    return;
   }
-  const int lo = a < c ? a : c, hi = a < c ? c : a;
-  int p = 0;
-  for (int x = 0; x < lo; ++x) p += NO - 1 - x;
-  p += hi - lo - 1;
-  alpha[0] = NO + 2 * p;
-  alpha[1] = NO + 2 * p + 1;
-  ci[0] = 0.0;
-  ci[1] = a < c ? 1.0 : -1.0;  // coefficient of the second coordinate: i ci[1]
-  return 2;
+  const int lo = min(a, c), hi = max(a, c);
+  r = NO + 2 * (lo * (2 * NO - 1 - lo) / 2 + hi - lo - 1);
+  m = r + 1;
+  ci = a < c ? 1.0 : -1.0;
 }
 
 // compact loops from lambda: H[dR][(a b c d)] = sum E^alpha_ac E^beta_bd
 // lambda^{alpha beta}(item, +-dR), a halved sum completed from its partner
-// entry, to the slots of q and -q
+// entry, to the slots of q and -q.  One workgroup per (item, dR) with the 36 x 36
+// coordinates in LDS and, for -q, the finished entries, so that both blocks are
+// written in order.  Bound by HBM: 13 form factors, 81 and 41 items, 32 and
+// 18 us; a thread per entry that read its (up to eight) coordinates from memory
+// and wrote the entry of -q where its indices led took 72 and 39.
 template <int NDY>
-__global__ __launch_bounds__(256) void loop_rb_finalize_kernel(LoopSym sy, int ch, int n_q, int nD, int n_q_out,
+__global__ __launch_bounds__(256) void loop_rb_finalize_kernel(LoopSym sy, int ch, int nD, int n_q_out,
                                                                const int *__restrict__ items,
                                                                const int2 *__restrict__ dst,
                                                                const int *__restrict__ hmap,
                                                                const int *__restrict__ dlist, double inv_nf,
-                                                               const double *__restrict__ lam,
-                                                               double *__restrict__ compact) {
+                                                               const double2 *__restrict__ lam,
+                                                               double2 *__restrict__ out) {
   using H = Half<NDY>;
-  constexpr int NO2 = NO * NO, NO3 = NO2 * NO, NO4 = NO2 * NO2;
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (long long)n_q * nD * NO4) return;
-  const int tau = (int)(i % NO4);
-  const int iD = (int)((i / NO4) % nD);
-  const int it = (int)(i / ((long long)NO4 * nD));
-  const int hm = hmap[iD], h = hm & 0xffff;
+  constexpr int NO2 = NO * NO, NO3 = NO2 * NO, NO4 = NO2 * NO2, NV = (NO4 + 255) / 256;
+  static_assert(NO4 == NA * NA, "the entries take the place of the coordinates");
+  __shared__ double2 sl[NO4];
+  const int it = blockIdx.x / nD, iD = blockIdx.x % nD, tid = threadIdx.x;
+  const int hm = hmap[iD];
   const bool cj = (hm >> 16) != 0;  // the other half plane: lambda(-dR) = conj lambda(dR)
+  const double2 *src = lam + ((size_t)it * H::N + (hm & 0xffff)) * NO4;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int e = tid + 256 * i;
+    if (e < NO4) {
+      const double2 x = src[e];
+      sl[e] = make_double2(x.x, cj ? -x.y : x.y);
+    }
+  }
+  __syncthreads();
   auto entry = [&](int t) {
-    const int a = t / NO3, b = (t / NO2) % NO, c = (t / NO) % NO, d = t % NO;
-    int al[2], be[2];
-    double ca[2], cb[2];
-    const int na = rb_coords(a, c, al, ca), nb = rb_coords(b, d, be, cb);
-    double sr = 0.0, si = 0.0;
-    for (int x = 0; x < na; ++x)
-      for (int y = 0; y < nb; ++y) {
-        const size_t o = (((size_t)it * H::N + h) * NA + al[x]) * NA + be[y];
-        const double lr = lam[2 * o], li = cj ? -lam[2 * o + 1] : lam[2 * o + 1];
-        // coefficient (x ? i ca : 1) (y ? i cb : 1)
-        if (x == 0 && y == 0) {
-          sr += lr;
-          si += li;
-        } else if (x == 1 && y == 1) {
-          const double f = -ca[1] * cb[1];
-          sr += f * lr;
-          si += f * li;
-        } else {
-          const double f = x == 1 ? ca[1] : cb[1];  // times i
-          sr -= f * li;
-          si += f * lr;
-        }
-      }
-    return make_double2(sr, si);
+    int r1, m1, r2, m2;
+    double c1, c2;
+    rb_coords(t / NO3, (t / NO) % NO, r1, m1, c1);
+    rb_coords((t / NO2) % NO, t % NO, r2, m2, c2);
+    const double2 rr = sl[r1 * NA + r2], rm = sl[r1 * NA + m2], mr = sl[m1 * NA + r2], mm = sl[m1 * NA + m2];
+    // (r + i c1 m)(r + i c2 m)
+    const double f = -c1 * c2;
+    return make_double2(rr.x - c2 * rm.y - c1 * mr.y + f * mm.x, rr.y + c2 * rm.x + c1 * mr.x + f * mm.y);
   };
   const int q = items[it] & LOOP_ITEM_Q, dx = dlist[2 * iD], dy = dlist[2 * iD + 1];
-  double2 v = entry(tau);
-  if ((sy.half >> ch) & 1) {
-    double sgn;
-    const double2 p = entry(loop_partner_tau(sy, NO, ch, tau, sgn));
-    loop_add_partner(sy, q, dx, dy, sgn, p, v);
+  const int2 d = dst[it];
+  const bool half = (sy.half >> ch) & 1;
+  const size_t blk = (size_t)nD * NO4, off = (size_t)iD * NO4;
+  double2 v[NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int tau = min(tid + 256 * i, NO4 - 1);
+    v[i] = entry(tau);
+    if (half) {
+      double sgn;
+      const double2 p = entry(loop_partner_tau(sy, NO, ch, tau, sgn));
+      loop_add_partner(sy, q, dx, dy, sgn, p, v[i]);
+    }
+    v[i] = make_double2(v[i].x * inv_nf, v[i].y * inv_nf);
+    if (d.x >= 0 && tid + 256 * i < NO4) out[(size_t)d.x * blk + off + tau] = v[i];
   }
-  loop_store(sy, NO, ch, q, dx, dy, tau, make_double2(v.x * inv_nf, v.y * inv_nf), dst[it], 0, n_q_out,
-             (size_t)nD * NO4, (size_t)iD * NO4, (double2 *)compact);
+  if (d.y < 0) return;
+  __syncthreads();  // every coordinate is read
+#pragma unroll
+  for (int i = 0; i < NV; ++i)
+    if (tid + 256 * i < NO4) sl[tid + 256 * i] = v[i];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int t = tid + 256 * i;
+    if (t < NO4) out[(size_t)d.y * blk + off + t] = loop_mirror(sy, NO, q, dx, dy, t, sl);
+  }
 }
 
 size_t loop_rb_rowbuf_floats(int ndy, int Lf) {
@@ -800,21 +810,21 @@ hipError_t launch_loop_rb_sums(const LoopArgs &a, const float *Y, double *lamb, 
     return hipErrorInvalidValue;
   const int n_groups = (n_q + NQG - 1) / NQG;
   const long long nt = (long long)n_groups * NQG * NA * NA;
-  const long long nf = (long long)n_q * nD * NO * NO * NO * NO;
+  const long long nf = (long long)n_q * nD;
   const double inv = 1.0 / ((double)a.Lf * a.Lf);
   const LoopSym sy{a.trs, a.half, a.Lq, (const double2 *)a.twq};
   const int half = (a.half >> ch) & 1;
-  const dim3 gs((unsigned)((nt + 255) / 256)), gf((unsigned)((nf + 255) / 256)), block(256);
+  const dim3 gs((unsigned)((nt + 255) / 256)), gf((unsigned)nf), block(256);
   if (a.ndy == 4) {
     hipLaunchKernelGGL(loop_rb_rowsum_kernel<4>, gs, block, 0, st, Y, a.tw, a.Lq, a.n_ref, a.Lf, a.items, n_q, half, ch,
                        lamb);
-    hipLaunchKernelGGL(loop_rb_finalize_kernel<4>, gf, block, 0, st, sy, ch, n_q, nD, a.n_q_out, a.items, a.dst, hmap,
-                       dlist, inv, lamb, out);
+    hipLaunchKernelGGL(loop_rb_finalize_kernel<4>, gf, block, 0, st, sy, ch, nD, a.n_q_out, a.items, a.dst, hmap, dlist,
+                       inv, (const double2 *)lamb, (double2 *)out);
   } else if (a.ndy == 2) {
     hipLaunchKernelGGL(loop_rb_rowsum_kernel<2>, gs, block, 0, st, Y, a.tw, a.Lq, a.n_ref, a.Lf, a.items, n_q, half, ch,
                        lamb);
-    hipLaunchKernelGGL(loop_rb_finalize_kernel<2>, gf, block, 0, st, sy, ch, n_q, nD, a.n_q_out, a.items, a.dst, hmap,
-                       dlist, inv, lamb, out);
+    hipLaunchKernelGGL(loop_rb_finalize_kernel<2>, gf, block, 0, st, sy, ch, nD, a.n_q_out, a.items, a.dst, hmap, dlist,
+                       inv, (const double2 *)lamb, (double2 *)out);
   } else {
     return hipErrorInvalidValue;
   }

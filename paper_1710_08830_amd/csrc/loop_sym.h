@@ -87,6 +87,18 @@ __device__ inline void loop_add_partner(const LoopSym &s, int q, int dx, int dy,
   v.y -= p.x * hi + p.y * hr;
 }
 
+// entry t of the block of -q from the entries v of that of q (the maps of the
+// entries are their own inverses, and the signs square to one)
+__device__ inline double2 loop_mirror(const LoopSym &s, int n_o, int q, int dx, int dy, int t, const double2 *v) {
+  double sgn;
+  if (s.trs) {
+    const double2 x = v[loop_tau(n_o, t, false, s.trs == 2, sgn)];
+    return make_double2(sgn * x.x, -sgn * x.y);
+  }
+  const double2 x = v[loop_tau(n_o, t, true, false, sgn)], p = loop_phase(s, q, dx, dy);
+  return make_double2(p.x * x.x - p.y * x.y, p.x * x.y + p.y * x.x);
+}
+
 // stores entry tau of the item's block (at element off of the blocks of blk
 // elements) to the slot of q, and transformed to the slot of -q
 __device__ inline void loop_store(const LoopSym &s, int n_o, int ch, int q, int dx, int dy, int tau, double2 v,

@@ -777,12 +777,14 @@ extern "C" tufrg_status tufrg_create(const tufrg_model *m, const tufrg_setup *s,
     for (int p = 0; p < 3; ++p)
       for (size_t k = 0; k < Nf; ++k) split = std::max(split, std::fabs(e[(2 * p) * Nf + k] - e[(2 * p + 1) * Nf + k]));
     if (split <= 1e-10 * std::max(1.0, emax)) {
-      c->kr = c->prec == TUFRG_BF16X3 && time_reversal_inversion(m);
+      // the matrix-core kernels sum pairs on even meshes only
+      const bool unused = c->prec == TUFRG_BF16X3 && c->Lf % 2;
+      c->kr = c->prec == TUFRG_BF16X3 && !unused && time_reversal_inversion(m);
       if (c->kr) {
         CTRY(dalloc(c, &c->d_krx, kr_x_floats(c->Lf)));
         CTRY(dalloc(c, &c->d_ek, Nf * (c->scheme == CUT_SHELL ? 16 : 8)));
         CHIP(launch_kr_x(c->Lf, c->d_band64, c->d_krx, st));
-      } else {
+      } else if (!unused) {
         if (c->prec == TUFRG_FP64)
           CTRY(dalloc(c, &c->d_pir64, Nf * 3 * 36));
         else
@@ -932,7 +934,7 @@ static tufrg_status compute_kval(tufrg_ctx *c, double lam, int deriv) {
   else
     HIPCHK(c, launch_kval(c->n_o * c->Nf, c->Nf, c->n_o, c->d_band64, rl, rs, rd, c->d_kv64, c->d_kv32, c->st));
   if (shell) HIPCHK(c, launch_shell_ab(c->n_o, c->Nf, c->d_band64, lam, deriv, c->d_cv64, c->d_cv32, c->st));
-  if (c->kr) HIPCHK(c, launch_kr_ek(c->Nf, shell, c->d_bandk32, c->d_kv32, c->d_cv32, c->d_ek, c->st));
+  if (mfma_kind(c) == 2) HIPCHK(c, launch_kr_ek(c->Nf, shell, c->d_bandk32, c->d_kv32, c->d_cv32, c->d_ek, c->st));
   return TUFRG_OK;
 }
 

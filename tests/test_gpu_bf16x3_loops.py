@@ -55,3 +55,25 @@ def test_loops_against_fp64(kind, model, S, Lq, n_ref, cutoff):
             err = float((got[ch] - ref[ch]).abs().max() / ref[ch].abs().max())
             print(f"deriv {deriv} channel {ch}: {err:.2e}, bar {bar:.2e}", flush=True)
             assert err < bar
+
+
+def test_switching_the_pairs_leaves_no_stale_operand():
+    """Pairs off and on again, at another scale in between: the loops of a context that never switched."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1710_08830_amd import tufrg as T
+    for cutoff in ("temperature", "shell"):
+        print(f"bf16x3 loops: pairs switched, t2g S5 6x6 refined 4x {cutoff}", flush=True)
+        ctx = [T.Context(R, TT, -0.3, kanamori_V0(2.0, 0.3), ff_shell(5), 6, 4, cutoff, "bf16x3",
+                         temperature=0.1 if cutoff == "shell" else None) for _ in range(2)]
+        x = [torch.empty((2, c.Nq, c.n_dR, 6 ** 4), dtype=torch.complex128, device="cuda") for c in ctx]
+        T.tufrg_loops_compact(ctx[0], 0.7, 1, x[0])
+        T.tufrg_pair_bands(ctx[0], False)
+        T.tufrg_loops_compact(ctx[0], 0.5, 1, x[0])
+        assert T.tufrg_pair_bands(ctx[0], True)
+        for c, y in zip(ctx, x):
+            T.tufrg_loops_compact(c, 0.4, 1, y)
+        torch.cuda.synchronize()
+        assert torch.equal(x[0], x[1])
+        for c in ctx:
+            c.close()

@@ -218,30 +218,35 @@ hipError_t launch_kr_apre(int ndy, const float *x, const float *phy, int Lf, voi
   return hipGetLastError();
 }
 
-// ek[k] = (e_0, e_1, e_2, K_0, K_1, K_2, 0, 0) of the pairs (first band of each),
-// shell scheme: and (a_0, a_1, a_2, b_0, b_1, b_2, 0, 0) of the shell factors
-__global__ void kr_ek_kernel(int Nf, int shell, const float *__restrict__ band, const float *__restrict__ kv,
-                             const float *__restrict__ cv, float *__restrict__ ek) {
-  const int per = shell ? 16 : 8;
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (long long)Nf * per) return;
-  const int r = (int)(i % per);
-  const long long k = i / per;
-  const int j = r & 7, n = j % 3, second = j / 3;
-  float v = 0.f;
-  if (j < 6) {
-    if (r < 8)
-      v = second ? kv[k * NO + 2 * n] : band[k * (NO + NO * NA) + 2 * n];
-    else
-      v = cv[k * 2 * NO + 4 * n + second];
+// ek[k] = (e_0, e_1, e_2, K_0, K_1, K_2, 0, 0) of the pairs (first band of each;
+// shell scheme: K the J of the temperature vlam) and, shell scheme, (a_0, a_1, a_2,
+// b_0, b_1, b_2, 0, 0) of the shell factors at lam; evaluated in FP64.  In place of
+// the tables of all six bands that the other kernels read: with both, three
+// launches for one (t2g, one form factor, 2 x 2 points, with the split below: 44 ->
+// 36 us an evaluation).
+__global__ void kr_ek_kernel(int Nf, int shell, const double *__restrict__ band, double vlam, int vscheme, int vderiv,
+                             double lam, int deriv, float *__restrict__ ek) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= 3 * Nf) return;
+  const int n = i / Nf, k = i - n * Nf;
+  const double e = band[(size_t)(2 * n) * Nf + k];
+  float *o = ek + (size_t)k * (shell ? 16 : 8);
+  o[n] = (float)e;
+  o[3 + n] = (float)cut_val(e, vlam, vscheme, vderiv);
+  if (n < 2) o[6 + n] = 0.f;
+  if (shell) {
+    double a, b;
+    shell_ab(e, lam, deriv, a, b);
+    o[8 + n] = (float)a;
+    o[11 + n] = (float)b;
+    if (n < 2) o[14 + n] = 0.f;
   }
-  ek[i] = v;
 }
 
-hipError_t launch_kr_ek(int Nf, int shell, const float *band, const float *kv, const float *cv, float *ek,
-                        hipStream_t st) {
-  const long long n = (long long)Nf * (shell ? 16 : 8);
-  hipLaunchKernelGGL(kr_ek_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, Nf, shell, band, kv, cv, ek);
+hipError_t launch_kr_ek(int Nf, int shell, const double *band, double vlam, int vscheme, int vderiv, double lam,
+                        int deriv, float *ek, hipStream_t st) {
+  hipLaunchKernelGGL(kr_ek_kernel, dim3((3 * Nf + 255) / 256), dim3(256), 0, st, Nf, shell, band, vlam, vscheme, vderiv,
+                     lam, deriv, ek);
   return hipGetLastError();
 }
 
@@ -574,8 +579,8 @@ __global__ __launch_bounds__(256) void loop_kr_rowsum_kernel(const float *__rest
   }
 }
 
-// one workgroup per (item, dR): the 15 x 15 coordinates in LDS, then the 1296 entries
-template <int NDY>
+// SPLIT workgroups per (item, dR): the 15 x 15 coordinates in LDS, then the 1296 entries
+template <int NDY, int SPLIT>
 __global__ __launch_bounds__(256) void loop_kr_finalize_kernel(LoopSym sy, int ch, int nD, int n_q_out,
                                                                const int *__restrict__ items,
                                                                const int2 *__restrict__ dst,
@@ -608,7 +613,7 @@ __global__ __launch_bounds__(256) void loop_kr_finalize_kernel(LoopSym sy, int c
     const double A = cr1 * cr2, B = cr1 * ci2, C = ci1 * cr2, E = -ci1 * ci2;
     return make_double2(A * rr.x + E * mm.x - B * rm.y - C * mr.y, A * rr.y + E * mm.y + B * rm.x + C * mr.x);
   };
-  for (int tau = threadIdx.x; tau < NO4; tau += 256) {
+  for (int tau = threadIdx.x + (SPLIT > 1 ? 256 * blockIdx.y : 0); tau < NO4; tau += 256 * SPLIT) {
     double2 v = entry(tau);
     if ((sy.half >> ch) & 1) {
       double sgn;
@@ -676,18 +681,25 @@ hipError_t launch_loop_kr_sums(const LoopArgs &a, const float *Y, double *lam, c
   const double inv = 1.0 / ((double)a.Lf * a.Lf);
   const LoopSym sy{a.trs, a.half, a.Lq, (const double2 *)a.twq};
   const int half = (a.half >> ch) & 1;
-  const dim3 gs(n_q, 4), gf((unsigned)((long long)n_q * nD)), block(256);
-  if (a.ndy == 4) {
-    hipLaunchKernelGGL(loop_kr_rowsum_kernel<4>, gs, block, 0, st, Y, a.tw, a.Lq, a.n_ref, a.Lf, a.items, half, ch,
-                       (double2 *)lam);
-    hipLaunchKernelGGL(loop_kr_finalize_kernel<4>, gf, block, 0, st, sy, ch, nD, a.n_q_out, a.items, a.dst, hmap, dlist,
-                       inv, (const double2 *)lam, (double2 *)out);
+  // few blocks: the entries of each over several workgroups, which then take the
+  // time of one entry (one block: 6.0 -> 3.5 us); many fill the chip as they are
+  const long long nb = (long long)n_q * nD;
+  const dim3 gs(n_q, 4), block(256);
+#define TUFRG_KR_SUMS(D, SPLIT)                                                                                      \
+  hipLaunchKernelGGL(loop_kr_rowsum_kernel<D>, gs, block, 0, st, Y, a.tw, a.Lq, a.n_ref, a.Lf, a.items, half, ch,     \
+                     (double2 *)lam);                                                                                \
+  hipLaunchKernelGGL((loop_kr_finalize_kernel<D, SPLIT>), dim3((unsigned)nb, SPLIT), block, 0, st, sy, ch, nD,        \
+                     a.n_q_out, a.items, a.dst, hmap, dlist, inv, (const double2 *)lam, (double2 *)out)
+  if (a.ndy == 4 && nb < 256) {
+    TUFRG_KR_SUMS(4, 6);
+  } else if (a.ndy == 4) {
+    TUFRG_KR_SUMS(4, 1);
+  } else if (nb < 256) {
+    TUFRG_KR_SUMS(2, 6);
   } else {
-    hipLaunchKernelGGL(loop_kr_rowsum_kernel<2>, gs, block, 0, st, Y, a.tw, a.Lq, a.n_ref, a.Lf, a.items, half, ch,
-                       (double2 *)lam);
-    hipLaunchKernelGGL(loop_kr_finalize_kernel<2>, gf, block, 0, st, sy, ch, nD, a.n_q_out, a.items, a.dst, hmap, dlist,
-                       inv, (const double2 *)lam, (double2 *)out);
+    TUFRG_KR_SUMS(2, 1);
   }
+#undef TUFRG_KR_SUMS
   return hipGetLastError();
 }
 

@@ -929,12 +929,15 @@ static tufrg_status compute_kval(tufrg_ctx *c, double lam, int deriv) {
   const bool shell = c->scheme == CUT_SHELL;
   const double rl = shell ? c->temp : lam;
   const int rs = shell ? CUT_TEMPERATURE : c->scheme, rd = shell ? 0 : deriv;
+  if (mfma_kind(c) == 2) {  // its kernels read nothing else
+    HIPCHK(c, launch_kr_ek(c->Nf, shell, c->d_band64, rl, rs, rd, lam, deriv, c->d_ek, c->st));
+    return TUFRG_OK;
+  }
   if (c->n_o == 2)
     HIPCHK(c, launch_ekv4(c->Nf, c->d_band64, rl, rs, rd, c->d_ekv64, c->d_ekv32, c->st));
   else
     HIPCHK(c, launch_kval(c->n_o * c->Nf, c->Nf, c->n_o, c->d_band64, rl, rs, rd, c->d_kv64, c->d_kv32, c->st));
   if (shell) HIPCHK(c, launch_shell_ab(c->n_o, c->Nf, c->d_band64, lam, deriv, c->d_cv64, c->d_cv32, c->st));
-  if (mfma_kind(c) == 2) HIPCHK(c, launch_kr_ek(c->Nf, shell, c->d_bandk32, c->d_kv32, c->d_cv32, c->d_ek, c->st));
   return TUFRG_OK;
 }
 

@@ -140,6 +140,7 @@ struct tufrg_ctx {
   float *d_pir32 = nullptr;   // [Nf][3][36] pair sums of the packed projectors (FP32, BF16X3)
   double *d_pir64 = nullptr;  // the same in FP64
   size_t partial_cap = 0;  // doubles allocated at d_partial
+  int part_items = 0;      // items whose partial sums fit there at a time
   unsigned long long *h_sbits = nullptr;       // pinned
   // Euler steps in HIP graphs: the executable graph, the capture stream (the
   // context's stream, or a private one when that is the null stream), one
@@ -354,6 +355,12 @@ static int default_kx_rows(const tufrg_ctx *c) {
     }
   }
   return best;
+}
+
+// doubles of the partial sums of an item in n kx chunks (complex, in the arithmetic type)
+static size_t partial_doubles(const tufrg_ctx *c, int n) {
+  const size_t parts = (size_t)c->nkyb * n * c->ndx * (2 * c->ndy + 1) * c->no4;
+  return c->prec == TUFRG_FP64 ? 2 * parts : parts;
 }
 
 // Time reversal times inversion, H(k) = T H(k)^* T^t with T = i sigma_y in each
@@ -644,8 +651,17 @@ extern "C" tufrg_status tufrg_create(const tufrg_model *m, const tufrg_setup *s,
   CTRY(dalloc(c, &c->d_twf32, 2 * (size_t)c->Lf));
   CTRY(dalloc(c, &c->d_twq, 2 * (size_t)c->Lq));
   CTRY(dalloc(c, &c->d_dtab, c->nD + 81));
-  const size_t nparts = (size_t)c->nkyb * c->nkxc;
-  c->partial_cap = 2 * c->items.size() * nparts * c->ndx * (2 * c->ndy + 1) * c->no4;
+  // One and six orbitals: at most 1 and 2 GB of partial sums (six orbitals: or two
+  // a coarse q), which is many rounds of resident workgroups, the items in slices.
+  // All at once they would take 35 GB at one orbital, 512 x 512 refined 8x, 13 form
+  // factors (a state: 0.7 GB).  Two orbitals: all items, as a batch sums them in
+  // one launch (at most 1.5 times two parts per coarse q at the largest meshes).
+  const size_t per_item = partial_doubles(c, c->nkxc);
+  size_t fit = c->items.size();
+  if (c->n_o == 1) fit = ((size_t)1 << 27) / per_item;
+  if (c->n_o == 6) fit = std::max((size_t)1 << 28, 2 * c->Nq * partial_doubles(c, 1)) / per_item;
+  c->part_items = (int)std::max<size_t>(1, std::min(fit, c->items.size()));
+  c->partial_cap = c->prec == TUFRG_BF16X3 ? 0 : c->part_items * per_item;  // BF16X3: row buffers instead
   CTRY(dalloc(c, &c->d_partial, c->partial_cap));
   CTRY(dalloc(c, &c->d_loop, 2 * 2 * (size_t)c->Nq * c->nD * c->no4));
   CTRY(dalloc(c, &c->d_real, 2 * 2 * (size_t)c->nD * BB));
@@ -1040,11 +1056,26 @@ static tufrg_status loops_range_mfma(tufrg_ctx *c, double lam, int deriv, const 
 
 static tufrg_status loops_range(tufrg_ctx *c, double lam, int deriv, const LoopItems &li, double *dst) {
   if (c->prec == TUFRG_BF16X3) return loops_range_mfma(c, lam, deriv, li, dst);
-  const LoopArgs a = loop_args(c, lam, deriv, li);
-  HIPCHK(c, timer_mark(c, TUFRG_TIMER_LOOP));
-  HIPCHK(c, c->n_o == 1 ? launch_loop1(a, c->st) : launch_loop(a, c->st));
-  HIPCHK(c, timer_mark(c, TUFRG_TIMER_LOOP));
-  HIPCHK(c, launch_loop_finalize(a, c->nD, c->d_dlist, dst, c->st));
+  auto part = [&](const LoopItems &p, double *out) -> tufrg_status {
+    const LoopArgs a = loop_args(c, lam, deriv, p);
+    HIPCHK(c, timer_mark(c, TUFRG_TIMER_LOOP));
+    HIPCHK(c, c->n_o == 1 ? launch_loop1(a, c->st) : launch_loop(a, c->st));
+    HIPCHK(c, timer_mark(c, TUFRG_TIMER_LOOP));
+    HIPCHK(c, launch_loop_finalize(a, c->nD, c->d_dlist, out, c->st));
+    return TUFRG_OK;
+  };
+  if (li.n[0] + li.n[1] <= c->part_items) return part(li, dst);
+  double *out = dst;
+  for (int ch = 0; ch < 2; ++ch) {
+    const int first = ch ? li.n[0] : 0, n = li.n[ch], slices = (n + c->part_items - 1) / c->part_items;
+    for (int s = 0; s < slices; ++s) {
+      const int i0 = (int)((long long)n * s / slices), i1 = (int)((long long)n * (s + 1) / slices);
+      LoopItems p{li.items + first + i0, li.dst + first + i0, {0, 0}, li.n_q_out};
+      p.n[ch] = i1 - i0;
+      TRY(part(p, out));
+    }
+    if (n) out += 2 * (size_t)li.n_q_out * c->nD * c->no4;
+  }
   return TUFRG_OK;
 }
 
@@ -1071,7 +1102,7 @@ static tufrg_status set_kx_rows(tufrg_ctx *c, int per) {
   per = std::max(1, std::min(per, rows));
   per = even_kx_rows(c, (rows + per - 1) / per);
   const int n = kx_chunks(c, per);
-  const size_t need = 2 * c->items.size() * c->nkyb * n * c->ndx * (2 * c->ndy + 1) * c->no4;
+  const size_t need = c->items.size() * partial_doubles(c, n);
   if (need > c->partial_cap) {
     HIPCHK(c, hipStreamSynchronize(c->st));
     dfree(c, c->d_partial);
@@ -1079,6 +1110,7 @@ static tufrg_status set_kx_rows(tufrg_ctx *c, int per) {
     c->partial_cap = 0;
     TRY(dalloc(c, &c->d_partial, need));
     c->partial_cap = need;
+    c->part_items = (int)c->items.size();
   }
   c->kxper = per;
   c->nkxc = n;

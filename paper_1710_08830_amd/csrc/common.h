@@ -9,8 +9,8 @@
 // combination 1 - 2 f(e).  Omega scheme at T = 0 (propagator times
 // w^2 / (w^2 + Omega^2)): J = e (2|e| + Omega) / (4 (|e| + Omega)^2).
 // At coinciding arguments the divided difference is the mean of K' over the
-// interval, from K' and its second derivative at the middle (Omega scheme, FP64
-// or with e = 0 inside: two-point Gauss-Legendre, split at 0).
+// interval: K' and its derivatives at the middle (Omega scheme in FP64: the two-point
+// Gauss-Legendre rule).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -92,6 +92,13 @@ __device__ inline double rcp_fast(double d) {
 }
 __device__ inline float rcp_fast(float d) { return __builtin_amdgcn_rcpf(d); }
 
+// 1 / x to about half an ulp (FP64: one), hardware estimate and Newton steps
+__device__ inline double rcp_newton(double x) { return rcp_fast(x); }
+__device__ inline float rcp_newton(float x) {
+  const float r = rcp_fast(x);
+  return fmaf(fmaf(-x, r, 1.f), r, r);
+}
+
 // 1 / x: exact division in FP64, the hardware reciprocal in FP32
 __device__ inline double rdiv(double x) { return 1.0 / x; }
 __device__ inline float rdiv(float x) { return __builtin_amdgcn_rcpf(x); }
@@ -101,7 +108,7 @@ template <typename T>
 __device__ inline void sech2_tanh(T x, T &sech2, T &th) {
   T ax = fabs(x);
   T s = exp(T(-2) * ax);
-  T inv = rdiv(T(1) + s);
+  T inv = T(1) / (T(1) + s);
   sech2 = T(4) * s * inv * inv;
   th = copysign((T(1) - s) * inv, x);
 }
@@ -146,32 +153,51 @@ __device__ inline T gl2_mean(T a, T b, T lam, int scheme, int deriv) {
   return T(0.5) * (cut_der(m - c * h, lam, scheme, deriv) + cut_der(m + c * h, lam, scheme, deriv));
 }
 
-// Mean of f = cut_der over [x, y] from its middle m: f(m) + (x - y)^2 / 24 times
-// its second derivative, the next term being (x - y)^4 / 1920 of the fourth (at
-// the switch widths below 2e-7 of f in FP32, 1e-15 with the temperature scheme
-// in FP64).  One exponential or reciprocal instead of the two of the two-point
-// rule: near Lambda = 1 a fifth to a half of the waves of a loop kernel hold
-// such a pair (FP32 Rashba loops, 13 form factors, L 24: 603 -> 553 us).
+// Mean of f = cut_der over [x, y] from its middle m: f(m) + d^2 / 24 f''(m) +
+// d^4 / 1920 f''''(m), d = x - y.  At the switch widths the last term is 2.6e-15 of f
+// in FP64 and 2e-7 with the Omega scheme in FP32 (with the temperature scheme it is
+// below FP32 rounding and left out), the next one below 1e-8 of that.  One
+// exponential or reciprocal instead of the two of the two-point rule, which took
+// 603 us where one takes 553 (FP32 Rashba loops, 13 form factors, L 24): near
+// Lambda = 1 a fifth to a half of the waves of a loop kernel hold such a pair.
+// Written so that the rounding stays below that rule's, which averages two
+// evaluations (600 000 pairs, largest error relative to the largest f, that rule's
+// and this one's: FP64 1.4e-15 and 6.7e-16, FP32 2.9e-7 and 2.4e-7, Omega 3.8e-7 and
+// 2.3e-7): sech^2 as 4 z, z = p - p^2 with p = 1 / (1 + e^{2|u|}), in
+// which an error of p falls out where sech^2 is largest; with the Omega scheme the
+// polynomial of K' in |m| / D and not in Lambda / D, without its cancellation.
 template <typename T>
 __device__ inline T mid_mean(T x, T y, T lam, int scheme, int deriv) {
   const T m = T(0.5) * (x + y), d = x - y, w = d * d * T(1.0 / 24.0);
   if (scheme == CUT_TEMPERATURE) {
-    const T r = rdiv(lam + lam), u = m * r, w4 = w * r * r;  // derivatives in u = e / 2T
-    T s, t;
-    sech2_tanh(u, s, t);
+    // derivatives in u = e / 2T, r = 1 / 2T, s = sech^2 u, t = tanh u
+    const T il = rcp_newton(lam), u = fabs(m) * (T(0.5) * il), w4 = w * (T(0.25) * il * il);
+    const T ex = exp(T(-2) * u), p = ex * rcp_newton(T(1) + ex), z = fma(-p, p, p);
     if (deriv) {
-      // f = -s (1 - 2 u t) r^2, second derivative -(12 s - 18 s^2 + u t s (24 s - 8)) r^2
-      const T ut = u * t;
-      return -s * r * r * (T(1) - T(2) * ut + w4 * (T(12) - T(18) * s + ut * (T(24) * s - T(8))));
+      // f = -s (1 - 2 u t) r^2, second derivative -(12 s - 18 s^2 + u t s (24 s - 8)) r^2,
+      // fourth -s (80 - 600 s + 600 s^2 + u t (-32 + 480 s - 720 s^2)) r^2, times 0.3 w4^2
+      const T ut = u * fma(T(-2), p, T(1));
+      T g = fma(ut, fma(T(96), z, T(-8)), fma(T(-72), z, T(12)));
+      if (sizeof(T) == 8)
+        g = fma(w4, fma(ut, fma(fma(T(-3456), z, T(576)), z, T(-9.6)), fma(fma(T(2880), z, T(-720)), z, T(24))), g);
+      const T il2 = sizeof(T) == 8 ? il * il : rcp_newton(lam * lam);
+      return -(z * il2) * fma(w4, g, fma(T(-2), ut, T(1)));
     }
-    // f = s r / 2, second derivative (4 s - 6 s^2) r / 2
-    return T(0.5) * s * r * (T(1) + w4 * (T(4) - T(6) * s));
+    // f = s r / 2, second derivative (4 s - 6 s^2) r / 2, fourth (16 s - 120 s^2 + 120 s^3) r / 2
+    T g = fma(T(-24), z, T(4));
+    if (sizeof(T) == 8) g = fma(w4, fma(fma(T(576), z, T(-144)), z, T(4.8)), g);
+    return z * il * fma(w4, g, T(1));
   }
-  // D = |e| + Lambda, g = Lambda / D: f = (3 - 10 g + 6 g^2) / 4 D^2 (of K) or (3 g - 2 g^2) / 4 D (of J)
-  const T i = rdiv(fabs(m) + lam), g = lam * i, w2 = w * i * i;
-  if (deriv)
-    return T(0.25) * i * i * (fma(fma(T(6), g, T(-10)), g, T(3)) + w2 * fma(fma(T(120), g, T(-120)), g, T(18)));
-  return T(0.25) * i * g * (fma(T(-2), g, T(3)) + w2 * fma(T(-24), g, T(18)));
+  // D = |e| + Lambda, g = Lambda / D, h = |e| / D = 1 - g:
+  // f = (3 - 10 g + 6 g^2) / 4 D^2 = (6 h^2 - 2 h - 1) / 4 D^2 (of K) or (3 g - 2 g^2) / 4 D (of J)
+  const T i = rcp_newton(fabs(m) + lam), g = lam * i, w2 = w * i * i;
+  if (deriv) {
+    const T h = fabs(m) * i;
+    const T f2 = fma(fma(T(120), g, T(-120)), g, T(18)), f4 = fma(fma(T(1512), g, T(-1080)), g, T(108));
+    return T(0.25) * (i * i) * fma(w2, fma(w2, f4, f2), fma(fma(T(6), h, T(-2)), h, T(-1)));
+  }
+  const T f2 = fma(T(-24), g, T(18)), f4 = fma(T(-216), g, T(108));
+  return T(0.25) * i * g * fma(w2, fma(w2, f4, f2), fma(T(-2), g, T(3)));
 }
 
 // Relative width below which the divided difference switches to the mean of
@@ -190,23 +216,18 @@ struct degen_rel<float> {
   static constexpr float v = 2e-2f;
 };
 
-// Mean of K' over [x, y], x and y closer than the switch.  Omega scheme: K' is
-// even with a kink at 0, an interval around 0 is the two from 0 to |x| and |y|.
+// Mean of K' over [x, y], x and y closer than the switch.
 template <typename T>
 __device__ inline T near_mean(T x, T y, T lam, int scheme, int deriv) {
-  if (scheme == CUT_OMEGA && x * y < T(0)) {
-    const T a = fabs(x), b = fabs(y), w = a / (a + b);
-    if (sizeof(T) == 8)
-      return w * gl2_mean(a, T(0), lam, scheme, deriv) + (T(1) - w) * gl2_mean(T(0), b, lam, scheme, deriv);
-    return w * mid_mean(a, T(0), lam, scheme, deriv) + (T(1) - w) * mid_mean(T(0), b, lam, scheme, deriv);
-  }
   if (sizeof(T) == 8 && scheme == CUT_OMEGA) return gl2_mean(x, y, lam, scheme, deriv);
   return mid_mean(x, y, lam, scheme, deriv);
 }
 
-// x - y = d too small for the quotient
+// x - y = d too small for the quotient.  Omega scheme: K' is even with a kink at 0;
+// around 0 the quotient (K(|x|) + K(|y|)) / (|x| + |y|) has no cancellation.
 template <typename T>
 __device__ inline bool near_degenerate(T d, T x, T y, T lam, int scheme) {
+  if (scheme == CUT_OMEGA && x * y < T(0)) return false;
   const T scale = scheme == CUT_TEMPERATURE ? lam : lam + fabs(x) + fabs(y);
   return !(fabs(d) > degen_rel<T>::v * scale);
 }

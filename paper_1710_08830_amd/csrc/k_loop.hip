@@ -175,7 +175,7 @@ __device__ inline void loop_no2_body(const T *__restrict__ ekv, const T *__restr
         for (int m = 0; m < 2; ++m)
 #pragma unroll
           for (int n = 0; n < 2; ++n)
-            if (near_degenerate(den[m][n], ekm[m], epn[n], lam, dd_scheme(SCHEME)))
+            if (near_degenerate(den[m][n], ekm[m], -sg * epn[n], lam, dd_scheme(SCHEME)))
               L[m][n] = sg * near_mean(ekm[m], -sg * epn[n], lam, dd_scheme(SCHEME), deriv);
       }
       if constexpr (SHELL) {

@@ -136,9 +136,20 @@ __host__ __device__ constexpr int kr_dy(int h) {
 
 size_t kr_x_floats(int Lf) { return (size_t)Lf * (Lf + 2 * XP) * XS; }
 
+// coordinate b (0..14) of the sum of pair n's projectors at k
+__device__ inline double kr_pair_sum(const double *__restrict__ band, int Nf, int n, int b, int k) {
+  const int p = kr_packed(b);
+  return band[(size_t)(NO + 2 * n * NA + p) * Nf + k] + band[(size_t)(NO + (2 * n + 1) * NA + p) * Nf + k];
+}
+
 // x[kx][ky + XP][beta][n], n = 0, 1, -XP <= ky < Lf + XP (mod Lf): pair sums of
-// the projectors in the 15 coordinates (beta = 15: 0), summed in FP64; the third
-// is what is left of the unit matrix (1 for beta < 3, else 0)
+// the projectors in the 15 coordinates (beta = 15: 0), summed in FP64; the loop
+// kernel takes the third as what they leave of the unit matrix (1 for beta < 3, else
+// 0), off by an FP32 rounding of that.  The loops are as far from FP64 ones as the
+// 36-coordinate kernel's (root mean squares 3.15e-7 to 8.0e-7 of the loops', the two
+// within 2 % over t2g and random models, meshes of 60 to 160, three regulators); with
+// the third sum loaded as well their errors are the same, and the kernel spills
+// registers (t2g 32 x 32 loops: 8.7 -> 11.5 ms).
 __global__ void kr_x_kernel(int Lf, const double *__restrict__ band, float *__restrict__ x) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= (long long)Lf * (Lf + 2 * XP) * XS) return;
@@ -146,10 +157,7 @@ __global__ void kr_x_kernel(int Lf, const double *__restrict__ band, float *__re
   const int kx = (int)(i / XS / (Lf + 2 * XP)), kyp = (int)(i / XS % (Lf + 2 * XP));
   const int k = kx * Lf + (kyp - XP + XP * Lf) % Lf;
   double v = 0.0;
-  if (b < NQ) {
-    const int p = kr_packed(b);
-    v = band[(size_t)(NO + 2 * n * NA + p) * Nf + k] + band[(size_t)(NO + (2 * n + 1) * NA + p) * Nf + k];
-  }
+  if (b < NQ) v = kr_pair_sum(band, Nf, n, b, k);
   x[i] = (float)v;
 }
 
@@ -163,8 +171,8 @@ hipError_t launch_kr_x(int Lf, const double *band, float *x, hipStream_t st) {
 // alpha = l % 16 and ky = 32 tile + 8 (l / 16) + t, t = 0..7: phi(ky) pi_p^alpha(ky),
 // split; zero past the coordinates and the mesh
 template <int NDY>
-__global__ __launch_bounds__(256) void kr_apre_kernel(const float *__restrict__ x, const float *__restrict__ phy, int Lf,
-                                                      u32x4 *__restrict__ apre) {
+__global__ __launch_bounds__(256) void kr_apre_kernel(const double *__restrict__ band, const float *__restrict__ phy,
+                                                      int Lf, u32x4 *__restrict__ apre) {
   using S = KR<NDY>;
   const int ntk = (Lf + KT - 1) / KT;
   const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -188,8 +196,7 @@ __global__ __launch_bounds__(256) void kr_apre_kernel(const float *__restrict__ 
         f = ph == 0     ? 1.f
             : ph <= NDY ? phy[((size_t)ky * NDY + ph - 1) * 2]
                         : -phy[((size_t)ky * NDY + ph - NDY - 1) * 2 + 1];
-        const float *xp = x + ((size_t)kx * (Lf + 2 * XP) + ky + XP) * XS + (lane & 15) * 2;
-        pv = p < 2 ? xp[p] : ((lane & 15) < 3 ? 1.f : 0.f) - xp[0] - xp[1];
+        if ((lane & 15) < NQ) pv = (float)kr_pair_sum(band, Lf * Lf, p, lane & 15, kx * Lf + ky);
       }
       v[u] = pv * f;
     }
@@ -207,14 +214,14 @@ size_t kr_apre_bytes(int ndy, int Lf) {
   return (size_t)Lf * ((Lf + KT - 1) / KT) * NP * (2 * ndy + 1) * 2 * 64 * 16;
 }
 
-hipError_t launch_kr_apre(int ndy, const float *x, const float *phy, int Lf, void *apre, hipStream_t st) {
-  if (!x || !phy || !apre || (ndy != 2 && ndy != 4)) return hipErrorInvalidValue;
+hipError_t launch_kr_apre(int ndy, const double *band, const float *phy, int Lf, void *apre, hipStream_t st) {
+  if (!band || !phy || !apre || (ndy != 2 && ndy != 4)) return hipErrorInvalidValue;
   const long long n = (long long)Lf * ((Lf + KT - 1) / KT) * NP * (2 * ndy + 1) * 64;
   const dim3 grid((unsigned)((n + 255) / 256));
   if (ndy == 4)
-    hipLaunchKernelGGL(kr_apre_kernel<4>, grid, dim3(256), 0, st, x, phy, Lf, (u32x4 *)apre);
+    hipLaunchKernelGGL(kr_apre_kernel<4>, grid, dim3(256), 0, st, band, phy, Lf, (u32x4 *)apre);
   else
-    hipLaunchKernelGGL(kr_apre_kernel<2>, grid, dim3(256), 0, st, x, phy, Lf, (u32x4 *)apre);
+    hipLaunchKernelGGL(kr_apre_kernel<2>, grid, dim3(256), 0, st, band, phy, Lf, (u32x4 *)apre);
   return hipGetLastError();
 }
 

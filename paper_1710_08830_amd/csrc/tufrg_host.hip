@@ -988,11 +988,18 @@ static tufrg_status ensure_apre(tufrg_ctx *c) {
   if (c->d_yrow && c->d_lamb) return TUFRG_OK;
   // items per launch: the larger channel's in equal chunks of whole groups (a
   // short last chunk would leave most compute units idle for the time of a
-  // launch); 36 coordinates: at most 384 items (96 groups of four); 15: row
-  // buffers of at most 4 GB
+  // launch).  36 coordinates: at most 384 items (96 groups of four), 256 where
+  // their row buffers would take more than 16 GB.  Chunks whose groups fill the 32
+  // compute units of an XCD evenly (128, 256, 384, 512) read less from memory, since
+  // the groups of a kx block then start together, but the time hardly follows:
+  // 32 x 32 refined 16x in a field, 1024 and 513 items: 3 x 344 and 2 x 260 take
+  // 105.9 ms, 256 each 106.2, 384 each 104.5; with time reversal, 513 and 513: 2 x 260
+  // 53.9, 256 each (a third launch of one item) 55.7, 384 each 54.2.  15: row buffers of
+  // at most 4 GB
   const int most = std::max(c->n_item[0], c->n_item[1]), group = kind == 2 ? 16 : 4;
   const size_t per_item = kr_rowbuf_floats(c->ndy, c->Lf) * sizeof(float);
-  const int cap = kind == 2 ? (int)std::max<size_t>(16, std::min<size_t>(most, ((size_t)4 << 30) / per_item)) : 384;
+  const int cap = kind == 2 ? (int)std::max<size_t>(16, std::min<size_t>(most, ((size_t)4 << 30) / per_item))
+                            : loop_rb_rowbuf_floats(c->ndy, c->Lf) * 96 * sizeof(float) <= ((size_t)16 << 30) ? 384 : 256;
   const int nch = (most + cap - 1) / cap;
   c->mfma_chunk = ((most + nch - 1) / nch + group - 1) / group * group;
   int hx[32], hy[32];

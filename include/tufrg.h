@@ -253,8 +253,9 @@ tufrg_status tufrg_set_initial_p(tufrg_ctx *ctx, const tufrg_c64 *P0);
 
 /* Result of tufrg_autotune. */
 typedef struct {
-  int32_t tunable;        /* 0: this setup has no launch shape to tune (six spin-orbitals on
-                             the vector units: one workgroup per q and channel) */
+  int32_t tunable;        /* 0: this setup has no launch shape to tune (one orbital, and six
+                             spin-orbitals on the vector units: their kx chunks follow a
+                             cost rule alone) */
   int32_t from_cache;     /* 1: the shape came from the cache file; nothing was timed */
   int32_t loop_kx_chunks; /* two spin-orbitals: kx chunks of the loop kernel now in use */
   int32_t mfma_kx_rows;   /* six spin-orbitals, BF16X3: kx rows per work item now in use */

@@ -16,7 +16,8 @@
 // L is read from the planes of its nD distinct n_o^2 x n_o^2 blocks, a granule of
 // four K never crossing a block (n_o^2 is a multiple of four); its 425 KB per q (13
 // form factors, six orbitals) stay in L2.  tmp is in transposed planes of Bp x Bp,
-// Bp = B rounded up to the 96-wide output tile, zero outside B x B.
+// Bp = B rounded up to the 96-wide output tile: zero for K (its rows) past B; columns
+// past B hold other values, and what follows from them is not stored.
 //   bundle_split_compact_kernel: compact loop (FP64) -> planes of its blocks
 //   bundle_mfma_kernel<0>:       tmp = L V  -> transposed planes of tmp
 //   bundle_mfma_kernel<1>:       out = f V tmp -> FP64

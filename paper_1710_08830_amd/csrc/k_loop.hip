@@ -55,19 +55,10 @@ namespace tufrg {
 namespace {
 
 // distinct entries: 4 real (tau = 0, 5, 10, 15) and 6 complex representatives
-// (tau = 1, 11, 2, 7, 3, 6) with partners (4, 14, 8, 13, 12, 9)
+// (tau = 1, 11, 2, 7, 3, 6) with partners (4, 14, 8, 13, 12, 9); see TAU_VALUE
 constexpr int NREAL = 4, NCPLX = 6;
-__device__ constexpr int REAL_TAU[NREAL] = {0, 5, 10, 15};
-__device__ constexpr int CPLX_TAU[NCPLX] = {1, 11, 2, 7, 3, 6};
-__device__ constexpr int CPLX_PARTNER[NCPLX] = {4, 14, 8, 13, 12, 9};
 
 }  // namespace
-
-template <typename T>
-__device__ inline T ldb(const T *base, unsigned byte_off) {
-  // base pointer is wave-uniform, the offset a 32-bit lane value
-  return *(const T *)((const char *)base + byte_off);
-}
 
 // four consecutive values at index i of a k-major array of 4-vectors
 template <typename T>
@@ -269,8 +260,9 @@ __device__ inline void loop_no2_body(const T *__restrict__ ekv, const T *__restr
     if (i < nx) point(ak, ap, kx);
   } else {
     // plain order, one register set: FP32 with dx < 3 then fits four waves per
-    // SIMD, which hide the load latency better than the second set did at three
-    // (rashba_s9_L24: 2.26 -> 2.18 ms); FP64 is at one or two waves per SIMD anyway
+    // SIMD, which hide the load latency better than the second set does at three
+    // (Rashba loops, 9 form factors, 24 x 24 refined 24x: 479 us with it, 455);
+    // FP64 is at one or two waves per SIMD anyway
     int kx = x0;
     for (int i = 0; i < nx; ++i) {
       Pt ck, cp;

@@ -323,8 +323,8 @@ static int kx_chunks(const tufrg_ctx *c, int kxper) {
 // end's contraction of the ky phases, set to 8 rows (about 7; six orbitals:
 // the write of the partial sums).  The shortest time is taken; two orbitals:
 // among chunks whose k rows take at most about 3 MB of an XCD's 4 MB L2, since
-// each XCD sweeps one chunk over many q.  rashba_s9_L24 FP32 (4 chunks): 476 us,
-// 2: 520, 3: 475, 6: 500, 8: 523.
+// each XCD sweeps one chunk over many q.  rashba_s9_L24 FP32 (4 chunks): 455 us,
+// 2: 488, 3: 453, 6: 475, 8: 495.
 static int default_kx_rows(const tufrg_ctx *c) {
   const int rows = loop_rows_max(c->Lf, 1);
   const bool f64 = c->prec == TUFRG_FP64, wide = c->ndx > 3;
@@ -1181,7 +1181,7 @@ extern "C" tufrg_status tufrg_autotune(tufrg_ctx *c, double lambda, const char *
   const bool no2 = c->n_o == 2, mx = c->prec == TUFRG_BF16X3;
   res->loop_kx_chunks = c->nkxc;
   res->mfma_kx_rows = c->mfma_kxr;
-  if (!no2 && !mx) return TUFRG_OK;  // one workgroup per (q, channel): no launch shape to tune
+  if (!no2 && !mx) return TUFRG_OK;  // their kx chunks are the cost rule's, nothing is tuned
   res->tunable = 1;
   const char *pname = no2 ? "loop_kx_rows" : "mfma_kx_rows";
   auto apply = [&](int v) -> tufrg_status {
@@ -2505,7 +2505,6 @@ extern "C" tufrg_status tufrg_batch_flow(tufrg_batch *b, const tufrg_flow_opts *
       if (!active[i]) continue;
       tufrg_ctx *c = b->ctx[i];
       double *Pi = (double *)P[i], *Ci = (double *)C[i];
-      const long long ncx = (long long)c->B * c->B * c->Nq;
       if ((fused ? rhs_products(c, Pi, Ci, c->d_dP, c->d_dC, 1.0, mask)
                  : rhs_internal(c, l0, Pi, Ci, c->d_dP, c->d_dC, 1.0, mask)) != TUFRG_OK)
         return inst_fail(i);

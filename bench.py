@@ -31,6 +31,8 @@ import os
 import sys
 import time
 
+import numpy as np
+
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
@@ -99,9 +101,38 @@ LOOP_SOURCES = {"bf16x3": (("k_loop_rb.hip", "k_loop_kr.hip", "loop_sym.h", "com
 # name parts of the loop kernels of a precision and workload in a profile
 LOOP_KERNELS = {"bf16x3": ("loop_rb_kernel", "loop_kr_kernel"), "no2": ("loop_no2_kernel",),
                 "gen": ("loop_gen_kernel",)}
-# share of the (q, k) pairs of a channel that the kernels sum for a model with
-# time reversal (all workloads here): one of each k, q - k and of each q, -q
-SUMMED = 0.25
+
+
+def _hoppings_by_bond(w):
+    t = {}
+    for R, m in zip(w["hop_R"], np.asarray(w["hop_t"])):
+        R = tuple(int(v) for v in R)
+        t[R] = t.get(R, 0) + m
+    return t
+
+
+def summed_share(w):
+    """Share of the (q, k) pairs of a channel that the loop kernels sum: with time
+    reversal (T = 1, or i sigma_y in each orbital, on the hopping table) one of each
+    k, q - k and one of each q, -q in both channels, else one of the two each."""
+    t = _hoppings_by_bond(w)
+    big = max(np.abs(m).max() for m in t.values())
+    n = next(iter(t.values())).shape[0]
+    kinds = [np.eye(n)] + ([np.kron(np.eye(n // 2), [[0, 1], [-1, 0]])] if n % 2 == 0 else [])
+    return 0.25 if any(all(np.abs(m - T @ m.conj() @ T.T).max() <= 4e-16 * big for m in t.values()) for T in kinds) else 0.5
+
+
+def fifteen_coordinates(w, paired):
+    """Whether paired BF16X3 loops run in 15 coordinates: H(k) = T H(k)* T^t, T = i
+    sigma_y in each orbital (t(-R) = T t(R)* T^t)."""
+    t = _hoppings_by_bond(w)
+    big = max(np.abs(m).max() for m in t.values())
+    n = next(iter(t.values())).shape[0]
+    if not paired or n != 6:
+        return False
+    T = np.kron(np.eye(n // 2), [[0, 1], [-1, 0]])
+    return all(np.abs(t.get((-R[0], -R[1]), np.zeros((n, n))) - T @ m.conj() @ T.T).max() <= 4e-16 * big
+               for R, m in t.items())
 
 
 def _loop_kind(workload, prec):
@@ -451,7 +482,8 @@ def six_orbital_line(T, torch, w, prec, K, W, fp64_steps=2, surrogate=True, n_ro
     # achieved rate); the same count for the bands the kernel sums beside it
     credited = credited_loop_flops_per_pair(w["n_o"], ndy)
     credited_summed = credited_loop_flops_per_pair(w["n_o"], ndy, n_b)
-    flops_step = 2.0 * Nq * Nf * SUMMED * credited
+    share = summed_share(w)
+    flops_step = 2.0 * Nq * Nf * share * credited
     launches = loop_n / K
     loop_step_s = loop_ms / K * 1e-3
     rate = flops_step / loop_step_s  # on the survey's count
@@ -460,7 +492,7 @@ def six_orbital_line(T, torch, w, prec, K, W, fp64_steps=2, surrogate=True, n_ro
         # against the peak: what the matrix cores execute (the count above is of more
         # work than the kernels do once bands are paired)
         bound, peak = "mfma", PEAK_BF16_MFMA
-        executed = (mfma_flops_per_pair_15(ndy) if n_b == 3 and w["n_o"] == 6
+        executed = (mfma_flops_per_pair_15(ndy) if fifteen_coordinates(w, paired)
                     else mfma_flops_per_pair(ndy, w["n_o"], n_b))
         achieved = rate * executed / credited
     else:
@@ -483,7 +515,7 @@ def six_orbital_line(T, torch, w, prec, K, W, fp64_steps=2, surrogate=True, n_ro
         "loop_entries_per_s_kernel": entries / loop_step_s,
         "roofline": {"bound": bound, "achieved": achieved / 1e12, "peak": peak / 1e12, "unit": "TFLOP/s",
                      "frac": achieved / peak, "traffic": None if moved or six_bands else _traffic(w["name"], prec),
-                     "share_of_pairs_summed": SUMMED, "executed_matrix_flops_per_pair": executed,
+                     "share_of_pairs_summed": share, "executed_matrix_flops_per_pair": executed,
                      "survey_flops_per_pair": credited, "survey_tflops": rate / 1e12, "bands_summed": n_b,
                      "survey_tflops_of_bands_summed": rate * credited_summed / credited / 1e12},
         "flow_result": res,
@@ -740,11 +772,12 @@ def two_orbital_line(T, torch, w, args, K, W, extras=True, cpu=True):
     loop_avg_s = loop_ms / loop_n * 1e-3
     launches = loop_n / K
     ndx, ndy = _box(w["ff"])
+    share = summed_share(w)
     if prec == "bf16x3":
-        flops_step = 2.0 * Nq * Nf * SUMMED * credited_loop_flops_per_pair(w["n_o"], ndy)
+        flops_step = 2.0 * Nq * Nf * share * credited_loop_flops_per_pair(w["n_o"], ndy)
         bound, peak = "mfma", PEAK_BF16_MFMA
     else:
-        flops_step = 2.0 * Nq * Nf * SUMMED * loop_flops_per_pair(w["n_o"], ndx, ndy, w["cutoff"] == "shell")
+        flops_step = 2.0 * Nq * Nf * share * loop_flops_per_pair(w["n_o"], ndx, ndy, w["cutoff"] == "shell")
         bound, peak = "alu", PEAK_FP32_VECTOR
     achieved = flops_step / launches / loop_avg_s
     # the committed counters were taken with the workload's own regulator
@@ -764,7 +797,7 @@ def two_orbital_line(T, torch, w, args, K, W, extras=True, cpu=True):
         "loop_launches_per_step": launches,
         "loop_entries_per_s_kernel": entries / (loop_avg_s * launches),
         "roofline": {"bound": bound, "achieved": achieved / 1e12, "peak": peak / 1e12,
-                     "unit": "TFLOP/s", "frac": achieved / peak, "share_of_pairs_summed": SUMMED,
+                     "unit": "TFLOP/s", "frac": achieved / peak, "share_of_pairs_summed": share,
                      "traffic": traffic},
     }
     if not no_extras:

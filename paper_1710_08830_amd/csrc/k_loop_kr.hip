@@ -136,12 +136,6 @@ __host__ __device__ constexpr int kr_dy(int h) {
 
 size_t kr_x_floats(int Lf) { return (size_t)Lf * (Lf + 2 * XP) * XS; }
 
-// coordinate b (0..14) of the sum of pair n's projectors at k
-__device__ inline double kr_pair_sum(const double *__restrict__ band, int Nf, int n, int b, int k) {
-  const int p = kr_packed(b);
-  return band[(size_t)(NO + 2 * n * NA + p) * Nf + k] + band[(size_t)(NO + (2 * n + 1) * NA + p) * Nf + k];
-}
-
 // x[kx][ky + XP][beta][n], n = 0, 1, -XP <= ky < Lf + XP (mod Lf): pair sums of
 // the projectors in the 15 coordinates (beta = 15: 0), summed in FP64; the loop
 // kernel takes the third as what they leave of the unit matrix (1 for beta < 3, else
@@ -157,7 +151,10 @@ __global__ void kr_x_kernel(int Lf, const double *__restrict__ band, float *__re
   const int kx = (int)(i / XS / (Lf + 2 * XP)), kyp = (int)(i / XS % (Lf + 2 * XP));
   const int k = kx * Lf + (kyp - XP + XP * Lf) % Lf;
   double v = 0.0;
-  if (b < NQ) v = kr_pair_sum(band, Nf, n, b, k);
+  if (b < NQ) {
+    const int p = kr_packed(b);
+    v = band[(size_t)(NO + 2 * n * NA + p) * Nf + k] + band[(size_t)(NO + (2 * n + 1) * NA + p) * Nf + k];
+  }
   x[i] = (float)v;
 }
 
@@ -169,9 +166,10 @@ hipError_t launch_kr_x(int Lf, const double *band, float *x, hipStream_t st) {
 
 // A operand, [kx][ky tile][p][phi][hi, lo][lane] of 8 BF16: lane l holds row
 // alpha = l % 16 and ky = 32 tile + 8 (l / 16) + t, t = 0..7: phi(ky) pi_p^alpha(ky),
-// split; zero past the coordinates and the mesh
+// split; zero past the coordinates and the mesh.  The pair sums in FP64 from the
+// bands at k (bandk [Nf][6 + 216])
 template <int NDY>
-__global__ __launch_bounds__(256) void kr_apre_kernel(const double *__restrict__ band, const float *__restrict__ phy,
+__global__ __launch_bounds__(256) void kr_apre_kernel(const double *__restrict__ bandk, const float *__restrict__ phy,
                                                       int Lf, u32x4 *__restrict__ apre) {
   using S = KR<NDY>;
   const int ntk = (Lf + KT - 1) / KT;
@@ -196,7 +194,10 @@ __global__ __launch_bounds__(256) void kr_apre_kernel(const double *__restrict__
         f = ph == 0     ? 1.f
             : ph <= NDY ? phy[((size_t)ky * NDY + ph - 1) * 2]
                         : -phy[((size_t)ky * NDY + ph - NDY - 1) * 2 + 1];
-        if ((lane & 15) < NQ) pv = (float)kr_pair_sum(band, Lf * Lf, p, lane & 15, kx * Lf + ky);
+        if ((lane & 15) < NQ) {
+          const double *b = bandk + (size_t)(kx * Lf + ky) * (NO + NO * NA) + NO + 2 * p * NA + kr_packed(lane & 15);
+          pv = (float)(b[0] + b[NA]);
+        }
       }
       v[u] = pv * f;
     }
@@ -214,14 +215,14 @@ size_t kr_apre_bytes(int ndy, int Lf) {
   return (size_t)Lf * ((Lf + KT - 1) / KT) * NP * (2 * ndy + 1) * 2 * 64 * 16;
 }
 
-hipError_t launch_kr_apre(int ndy, const double *band, const float *phy, int Lf, void *apre, hipStream_t st) {
-  if (!band || !phy || !apre || (ndy != 2 && ndy != 4)) return hipErrorInvalidValue;
+hipError_t launch_kr_apre(int ndy, const double *bandk, const float *phy, int Lf, void *apre, hipStream_t st) {
+  if (!bandk || !phy || !apre || (ndy != 2 && ndy != 4)) return hipErrorInvalidValue;
   const long long n = (long long)Lf * ((Lf + KT - 1) / KT) * NP * (2 * ndy + 1) * 64;
   const dim3 grid((unsigned)((n + 255) / 256));
   if (ndy == 4)
-    hipLaunchKernelGGL(kr_apre_kernel<4>, grid, dim3(256), 0, st, band, phy, Lf, (u32x4 *)apre);
+    hipLaunchKernelGGL(kr_apre_kernel<4>, grid, dim3(256), 0, st, bandk, phy, Lf, (u32x4 *)apre);
   else
-    hipLaunchKernelGGL(kr_apre_kernel<2>, grid, dim3(256), 0, st, band, phy, Lf, (u32x4 *)apre);
+    hipLaunchKernelGGL(kr_apre_kernel<2>, grid, dim3(256), 0, st, bandk, phy, Lf, (u32x4 *)apre);
   return hipGetLastError();
 }
 

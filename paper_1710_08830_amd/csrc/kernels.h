@@ -100,7 +100,7 @@ int loop_rb_half_points(int ndy, int *dx, int *dy);
 size_t kr_x_floats(int Lf);
 hipError_t launch_kr_x(int Lf, const double *band, float *x, hipStream_t st);
 size_t kr_apre_bytes(int ndy, int Lf);
-hipError_t launch_kr_apre(int ndy, const double *band, const float *phy, int Lf, void *apre, hipStream_t st);
+hipError_t launch_kr_apre(int ndy, const double *bandk, const float *phy, int Lf, void *apre, hipStream_t st);
 hipError_t launch_kr_ek(int Nf, int shell, const double *band, double vlam, int vscheme, int vderiv, double lam,
                         int deriv, float *ek, hipStream_t st);
 size_t kr_rowbuf_floats(int ndy, int Lf);

@@ -977,7 +977,7 @@ static tufrg_status ensure_apre(tufrg_ctx *c) {
     unsigned char *ap = nullptr;
     TRY(dalloc(c, &ap, kind == 2 ? kr_apre_bytes(c->ndy, c->Lf) : loop_rb_apre_bytes(c->ndy, c->Lf, kind)));
     c->d_apre = ap;
-    const hipError_t e = kind == 2 ? launch_kr_apre(c->ndy, c->d_band64, c->d_phy32, c->Lf, ap, c->st)
+    const hipError_t e = kind == 2 ? launch_kr_apre(c->ndy, c->d_bandk64, c->d_phy32, c->Lf, ap, c->st)
                                    : launch_loop_rb_apre(c->ndy, kind, c->d_bandk32, c->d_pir32, c->d_phy32, c->Lf, ap, c->st);
     if (e != hipSuccess) {
       dfree(c, ap);

@@ -274,7 +274,8 @@ typedef struct {
  * regroups the k sum: BF16X3 results are unchanged bit for bit, two-orbital
  * ones change by FP32 rounding of the chunk partials.  cache_path (may be
  * NULL) names a JSON file {"version": 1, "entries": {"<key>": {...}}} keyed
- * by GPU architecture, compute units and problem shape: an entry for this
+ * by GPU architecture, compute units, problem shape, the channels whose kx
+ * rows are halved and the kind of matrix-core loops: an entry for this
  * shape is applied without timing; otherwise the result is added and the
  * file rewritten (through a temporary file and a rename).  Synchronous.  The
  * chosen shape stays until the context is destroyed or tuned again.  Errors:
@@ -436,8 +437,9 @@ tufrg_status tufrg_su2_flow(tufrg_ctx *ctx, const tufrg_flow_opts *opts, tufrg_c
 
 /* Optional per-kernel timing with HIP events recorded on the context stream
  * around the launches of one part of the right-hand side:
- *   TUFRG_TIMER_LOOP     the loop kernel launch (both channels in one launch; with
- *                        TUFRG_BF16X3 one interval per matrix-core launch, one per
+ *   TUFRG_TIMER_LOOP     the loop kernel launches (both channels in one; one or six
+ *                        orbitals whose partial sums exceed the workspace: one per
+ *                        channel and slice of coarse q; with TUFRG_BF16X3 one per
  *                        channel and chunk of coarse q)
  *   TUFRG_TIMER_PROJECT  real-space transform, gathers and assembly
  *   TUFRG_TIMER_BUNDLE   the two bundle products

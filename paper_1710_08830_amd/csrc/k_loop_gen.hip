@@ -26,7 +26,8 @@
 // the values from memory one tile ahead in registers: waiting for each tile's
 // loads and at four barriers the kernel took 1.73 ms (t2g, 13 form factors, FP64,
 // L 10 refined 6) and 1.45 ms (Zeeman, 9, FP32, L 11 refined 5), now 0.98 and
-// 0.74 ms: FP32 is then bound by vector issue and LDS reads, FP64 (13 form factors:
+// 0.74 ms (the first 0.76 since its pairs around zero energy, Omega scheme, take the
+// quotient): FP32 is then bound by vector issue and LDS reads, FP64 (13 form factors:
 // 41 complex sums a thread, six waves a CU) by the latency of the stages.
 //
 // Kramers pairs (PAIR): when bands (0,1), (2,3), (4,5) are degenerate at every

@@ -616,10 +616,11 @@ __device__ inline void rb_coords(int a, int c, int &r, int &m, double &ci) {
 // lambda^{alpha beta}(item, +-dR), a halved sum completed from its partner
 // entry, to the slots of q and -q.  One workgroup per (item, dR) with the 36 x 36
 // coordinates in LDS and, for -q, the finished entries, so that both blocks are
-// written in order.  Bound by HBM: 13 form factors, 81 and 41 items, 32 and
+// written in order.  Few blocks: SPLIT = 6 workgroups of 256 entries for each, which
+// write the entry of -q where its indices lead.  Bound by HBM: 13 form factors, 81 and 41 items, 32 and
 // 18 us; a thread per entry that read its (up to eight) coordinates from memory
 // and wrote the entry of -q where its indices led took 72 and 39.
-template <int NDY>
+template <int NDY, int SPLIT>
 __global__ __launch_bounds__(256) void loop_rb_finalize_kernel(LoopSym sy, int ch, int nD, int n_q_out,
                                                                const int *__restrict__ items,
                                                                const int2 *__restrict__ dst,
@@ -628,7 +629,9 @@ __global__ __launch_bounds__(256) void loop_rb_finalize_kernel(LoopSym sy, int c
                                                                const double2 *__restrict__ lam,
                                                                double2 *__restrict__ out) {
   using H = Half<NDY>;
-  constexpr int NO2 = NO * NO, NO3 = NO2 * NO, NO4 = NO2 * NO2, NV = (NO4 + 255) / 256;
+  constexpr int NO2 = NO * NO, NO3 = NO2 * NO, NO4 = NO2 * NO2, NC = (NO4 + 255) / 256;
+  constexpr int NV = SPLIT > 1 ? 1 : NC;
+  static_assert(SPLIT == 1 || SPLIT == NC, "an entry per thread");
   static_assert(NO4 == NA * NA, "the entries take the place of the coordinates");
   __shared__ double2 sl[NO4];
   const int it = blockIdx.x / nD, iD = blockIdx.x % nD, tid = threadIdx.x;
@@ -636,7 +639,7 @@ __global__ __launch_bounds__(256) void loop_rb_finalize_kernel(LoopSym sy, int c
   const bool cj = (hm >> 16) != 0;  // the other half plane: lambda(-dR) = conj lambda(dR)
   const double2 *src = lam + ((size_t)it * H::N + (hm & 0xffff)) * NO4;
 #pragma unroll
-  for (int i = 0; i < NV; ++i) {
+  for (int i = 0; i < NC; ++i) {
     const int e = tid + 256 * i;
     if (e < NO4) {
       const double2 x = src[e];
@@ -661,7 +664,7 @@ __global__ __launch_bounds__(256) void loop_rb_finalize_kernel(LoopSym sy, int c
   double2 v[NV];
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
-    const int tau = min(tid + 256 * i, NO4 - 1);
+    const int t = tid + 256 * (SPLIT > 1 ? (int)blockIdx.y : i), tau = min(t, NO4 - 1);
     v[i] = entry(tau);
     if (half) {
       double sgn;
@@ -669,9 +672,13 @@ __global__ __launch_bounds__(256) void loop_rb_finalize_kernel(LoopSym sy, int c
       loop_add_partner(sy, q, dx, dy, sgn, p, v[i]);
     }
     v[i] = make_double2(v[i].x * inv_nf, v[i].y * inv_nf);
-    if (d.x >= 0 && tid + 256 * i < NO4) out[(size_t)d.x * blk + off + tau] = v[i];
+    if constexpr (SPLIT > 1) {
+      if (t < NO4) loop_store(sy, NO, ch, q, dx, dy, tau, v[i], d, 0, n_q_out, blk, off, out);
+    } else {
+      if (d.x >= 0 && t < NO4) out[(size_t)d.x * blk + off + tau] = v[i];
+    }
   }
-  if (d.y < 0) return;
+  if (SPLIT > 1 || d.y < 0) return;
   __syncthreads();  // every coordinate is read
 #pragma unroll
   for (int i = 0; i < NV; ++i)
@@ -814,20 +821,26 @@ hipError_t launch_loop_rb_sums(const LoopArgs &a, const float *Y, double *lamb, 
   const double inv = 1.0 / ((double)a.Lf * a.Lf);
   const LoopSym sy{a.trs, a.half, a.Lq, (const double2 *)a.twq};
   const int half = (a.half >> ch) & 1;
-  const dim3 gs((unsigned)((nt + 255) / 256)), gf((unsigned)nf), block(256);
-  if (a.ndy == 4) {
-    hipLaunchKernelGGL(loop_rb_rowsum_kernel<4>, gs, block, 0, st, Y, a.tw, a.Lq, a.n_ref, a.Lf, a.items, n_q, half, ch,
-                       lamb);
-    hipLaunchKernelGGL(loop_rb_finalize_kernel<4>, gf, block, 0, st, sy, ch, nD, a.n_q_out, a.items, a.dst, hmap, dlist,
-                       inv, (const double2 *)lamb, (double2 *)out);
+  const dim3 gs((unsigned)((nt + 255) / 256)), block(256);
+#define TUFRG_RB_SUMS(D, SPLIT)                                                                                      \
+  hipLaunchKernelGGL(loop_rb_rowsum_kernel<D>, gs, block, 0, st, Y, a.tw, a.Lq, a.n_ref, a.Lf, a.items, n_q, half, ch, \
+                     lamb);                                                                                          \
+  hipLaunchKernelGGL((loop_rb_finalize_kernel<D, SPLIT>), dim3((unsigned)nf, SPLIT), block, 0, st, sy, ch, nD,        \
+                     a.n_q_out, a.items, a.dst, hmap, dlist, inv, (const double2 *)lamb, (double2 *)out)
+  // one block: 5.8 us whole, 4.0 split; 169 blocks: 6.5, 7.2; 900: 14.2, 18.3
+  const bool few = nf < 64;
+  if (a.ndy == 4 && few) {
+    TUFRG_RB_SUMS(4, 6);
+  } else if (a.ndy == 4) {
+    TUFRG_RB_SUMS(4, 1);
+  } else if (a.ndy == 2 && few) {
+    TUFRG_RB_SUMS(2, 6);
   } else if (a.ndy == 2) {
-    hipLaunchKernelGGL(loop_rb_rowsum_kernel<2>, gs, block, 0, st, Y, a.tw, a.Lq, a.n_ref, a.Lf, a.items, n_q, half, ch,
-                       lamb);
-    hipLaunchKernelGGL(loop_rb_finalize_kernel<2>, gf, block, 0, st, sy, ch, nD, a.n_q_out, a.items, a.dst, hmap, dlist,
-                       inv, (const double2 *)lamb, (double2 *)out);
+    TUFRG_RB_SUMS(2, 1);
   } else {
     return hipErrorInvalidValue;
   }
+#undef TUFRG_RB_SUMS
   return hipGetLastError();
 }
 

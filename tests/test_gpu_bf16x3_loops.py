@@ -28,6 +28,9 @@ HOP = {"t2g": (R, TT), "t2g, spin slowest": (R, np.ascontiguousarray(TT[:, SLOW]
 CASES = [(0, "t2g in a field", 13, 9, 7, "temperature"), (0, "t2g in a field", 9, 16, 4, "omega"),
          (0, "t2g", 5, 9, 7, "shell"), (0, "t2g", 13, 9, 8, "omega"),
          (1, "t2g, spin slowest", 13, 9, 8, "temperature"), (1, "t2g, spin slowest", 9, 8, 8, "shell"),
+         # one form factor: few final blocks, shared by several workgroups
+         (0, "t2g in a field", 1, 4, 16, "omega"), (0, "t2g", 1, 3, 21, "temperature"),
+         (1, "t2g, spin slowest", 1, 5, 12, "shell"), (2, "t2g", 1, 4, 16, "temperature"),
          # a last tile of 8, 10, 16 and 32 ky; 13 to 85 items in groups of 16; few final blocks and many
          (2, "t2g", 13, 9, 8, "temperature"), (2, "t2g", 5, 5, 14, "omega"), (2, "t2g", 9, 10, 10, "shell"),
          (2, "t2g", 9, 13, 6, "temperature"), (2, "quaternionic", 5, 5, 20, "shell"),
@@ -46,7 +49,7 @@ def test_loops_against_fp64(kind, model, S, Lq, n_ref, cutoff):
     # the random model's bands are three times as wide: a third of the points at the peak
     bar *= np.sqrt(3.0) if model == "quaternionic" else 1.0
     for prec in ("fp64", "bf16x3"):
-        ctx = T.Context(*HOP[model], -0.3, kanamori_V0(2.0, 0.3), ff_shell(S), Lq, n_ref, cutoff, prec,
+        ctx = T.Context(*HOP[model], -0.3, kanamori_V0(2.0, 0.3), ff_shell(max(S, 5))[:S], Lq, n_ref, cutoff, prec,
                         temperature=0.1 if cutoff == "shell" else None)
         if prec == "bf16x3":
             assert T.tufrg_pair_bands(ctx, kind > 0) is (kind > 0)

@@ -1112,11 +1112,17 @@ static tufrg_status set_kx_rows(tufrg_ctx *c, int per) {
   const size_t need = c->items.size() * partial_doubles(c, n);
   if (need > c->partial_cap) {
     HIPCHK(c, hipStreamSynchronize(c->st));
+    const size_t held = c->partial_cap;
     dfree(c, c->d_partial);
     c->d_partial = nullptr;
-    c->partial_cap = 0;
-    TRY(dalloc(c, &c->d_partial, need));
+    const tufrg_status st = dalloc(c, &c->d_partial, need);
     c->partial_cap = need;
+    if (st != TUFRG_OK) {
+      // the buffer of the shape in use again: later loops need it
+      const std::string msg = c->err;
+      c->partial_cap = dalloc(c, &c->d_partial, held) == TUFRG_OK ? held : 0;
+      return fail(c, st, msg);
+    }
     c->part_items = (int)c->items.size();
   }
   c->kxper = per;
